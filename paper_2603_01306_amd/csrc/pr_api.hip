@@ -49,6 +49,7 @@ struct pr_ctx {
   std::vector<uint32_t> h_stp;
   NodeBufs nb{};
   ProbBufs B{};
+  XBuf xb{};                     // exchange area of the steps over several workgroups
   int32_t *iota = nullptr;
   int32_t *d_np = nullptr;       // holds p (dense column list length)
   double *d_u = nullptr;         // n
@@ -201,7 +202,8 @@ void free_ctx(pr_ctx *c) {
                   c->nb.abuf, c->nb.sidx, c->nb.sval, c->nb.ybt, c->nb.gbt, c->B.uy, c->B.dsum, c->B.r, c->B.gm,
                   c->B.ucur, c->B.uprev,
                   c->B.zbest, c->B.h1, c->B.h2, c->B.part, c->B.rbsum, c->iota,
-                  c->d_np, c->d_u, c->d_v, c->d_w, c->d_scal, c->d_lam, c->d_vprev, c->d_regscratch};
+                  c->d_np, c->d_u, c->d_v, c->d_w, c->d_scal, c->d_lam, c->d_vprev, c->d_regscratch, c->xb.slots,
+                  c->xb.round};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   if (c->h_state) (void)hipHostFree(c->h_state);
@@ -284,12 +286,14 @@ hipError_t enqueue_unit(pr_ctx *c, hipStream_t s, int unit) {
                               nullptr, s);
   if (e != hipSuccess) return e;
   // the register-resident node step leaves g_N of its new iterate to an extra
-  // workgroup of this product (the strided step evaluates it itself)
+  // workgroup of this product (the steps over longer vectors evaluate it themselves)
   const bool reg = node_ept(c->P.p) != 0;
   e = launch_gemv_t(c->P, c->B.r, c->P.loss == kLsq ? nullptr : c->B.gm, c->B.h1, c->B.h2,
                     &c->d_state->done, s, reg ? c->d_prm : nullptr, c->d_state, c->nb.sidx, c->nb.sval,
                     &c->d_state->nsupp, (reg && c->step_bt) ? c->B.dsum : nullptr, c->B.nfin);
   if (e != hipSuccess) return e;
+  if (const XShape g = node_xshape(c->P.p); g.wgs)
+    return launch_node_step_x(c->d_prm, c->d_state, c->nb, c->B, a, g, c->xb, s);
   return launch_node_step(c->d_prm, c->d_state, c->nb, c->B, c->P.p, s, &a);
 }
 
@@ -1112,6 +1116,7 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && dalloc(&c->d_w, p) == hipSuccess && dalloc(&c->d_scal, 8) == hipSuccess;
   ok = ok && dalloc(&c->d_lam, 2 * kLanczosMax) == hipSuccess && dalloc(&c->d_vprev, p) == hipSuccess;
   ok = ok && dalloc(&c->d_regscratch, 3 * (size_t)p) == hipSuccess;
+  ok = ok && dalloc(&c->xb.slots, kXwgWords) == hipSuccess && dalloc(&c->xb.round, 1) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreate(&c->tev[0]) == hipSuccess && hipEventCreate(&c->tev[1]) == hipSuccess;
@@ -1125,6 +1130,8 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && hipMemsetAsync(c->B.r, 0, sizeof(double) * n, c->stream) == hipSuccess;
   ok = ok && hipMemsetAsync(c->B.gm, 0, sizeof(double) * n, c->stream) == hipSuccess;
   ok = ok && hipMemsetAsync(c->B.uy, 0, sizeof(double) * n, c->stream) == hipSuccess;
+  ok = ok && hipMemsetAsync(c->xb.slots, 0, sizeof(uint64_t) * kXwgWords, c->stream) == hipSuccess;
+  ok = ok && hipMemsetAsync(c->xb.round, 0, sizeof(uint32_t), c->stream) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->d_np, &pp, sizeof(int32_t), hipMemcpyHostToDevice, c->stream) == hipSuccess;
   ok = ok && launch_iota(c->iota, p, c->stream) == hipSuccess;
   ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
@@ -1420,7 +1427,10 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
   PR_TRY(hipMemcpyAsync(c->d_prm, &prm, sizeof(prm), hipMemcpyHostToDevice, c->stream));
   if (opts.method == kAcfgmGap || opts.method == kAcfgm)
     return solve_acfgm(c, &opts, L, beta0, beta_out, zeta_out, out);
-  PR_TRY(launch_node_init(c->d_prm, c->d_state, c->nb, beta0, L_init, p, c->stream));
+  if (const XShape g = node_xshape(p); g.wgs)
+    PR_TRY(launch_node_init_x(c->d_prm, c->d_state, c->nb, beta0, L_init, g, c->xb, c->stream));
+  else
+    PR_TRY(launch_node_init(c->d_prm, c->d_state, c->nb, beta0, L_init, p, c->stream));
   c->step_bt = is_bt(opts.method);
   rc = ensure_graph(c, opts.check_every);
   if (rc != PR_OK) return rc;
@@ -1432,11 +1442,13 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
   if (c->gram) {
     PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
     PR_TRY(hipStreamSynchronize(c->stream));
+    if (hs.status == kFailed) return PR_EDEVICE;
     return gram_certify(c, node, &opts, hs, beta_out, zeta_out, out);
   }
   PR_TRY(launch_zbest_final(c->d_state, c->B, c->P.loss, n, c->stream));
   PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
   PR_TRY(hipStreamSynchronize(c->stream));
+  if (hs.status == kFailed) return PR_EDEVICE;
   if (beta_out)
     PR_TRY(hipMemcpyAsync(beta_out, c->nb.xbest, sizeof(double) * p, hipMemcpyDeviceToDevice, c->stream));
   if (zeta_out)

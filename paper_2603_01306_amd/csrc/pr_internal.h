@@ -27,6 +27,7 @@ constexpr int32_t kJ0Flag = 1 << 29;
 constexpr int32_t kIdxMask = kJ0Flag - 1;
 enum : int32_t { kF64 = 0, kF32 = 1, kBF16 = 2 };
 enum : int32_t { kConverged = 1, kMaxIter = 2, kInfeasible = 3, kCutoffPrune = 4, kCutoffBranch = 5 };
+enum : int32_t { kFailed = -1 };  // NodeState::status: workgroups of a step lost each other (never in a result)
 
 // Per-node constants, device resident (written by the host before a solve).
 // iteration variants (pr_opts.method)
@@ -131,6 +132,15 @@ struct BatchBufs {
   const double *dsum;   // logistic backtracking: per (node, residual block) Bregman remainder [m][nfb]
 };
 
+// Exchange area of the kernels whose workgroups share one node (pr_xwg.h):
+// slots (zeroed once, kXwgWords 64-bit words) and the round reached so far.
+constexpr int kXwgMax = 64;          // workgroups of such a launch at most
+constexpr size_t kXwgWords = 2 * (2 * 16 + 2 * 64) * (size_t)kXwgMax;
+struct XBuf {
+  uint64_t *slots;
+  uint32_t *round;
+};
+
 // AC-FGM state of a single-node solve (pr_variants.hip), device resident.
 struct AcState {
   double L1;         // first-step curvature estimate (line search)
@@ -204,6 +214,15 @@ struct StepArgs {
 };
 hipError_t launch_node_step(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B,
                             int64_t p, hipStream_t s, const StepArgs *a = nullptr);
+// the node step and its start over several workgroups (pr_nodex.hip)
+struct XShape {
+  int wgs, ept;  // workgroups, entries per thread; {0, 0}: one workgroup takes the step (pr_node.hip)
+};
+XShape node_xshape(int64_t p);
+hipError_t launch_node_init_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const double *beta0, double L,
+                              XShape g, const XBuf &xb, hipStream_t s);
+hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B, const StepArgs &a,
+                              XShape g, const XBuf &xb, hipStream_t s);
 hipError_t launch_batch_init(const NodeParams *prm, NodeState *S, BatchBufs bb, const double *B0, double L,
                              int64_t p, hipStream_t s);
 hipError_t launch_batch_step(const NodeParams *prm, NodeState *S, BatchBufs bb, int64_t p, hipStream_t s);
