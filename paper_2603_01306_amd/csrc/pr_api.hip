@@ -1476,21 +1476,39 @@ int pr_gemm(void *stream, const uint16_t *A, int64_t lda, const double *B, int64
   return PR_OK;
 }
 
+// Status counts of a context-free call on vectors past reg_x_max(): the status
+// comes to the host, n1 = |J1|, nf = |J_f|.
+static int count_status(const int8_t *status, int64_t p, hipStream_t s, int64_t *n1, int64_t *nf) {
+  std::vector<int8_t> st((size_t)p);
+  PR_TRY(hipMemcpyAsync(st.data(), status, (size_t)p, hipMemcpyDeviceToHost, s));
+  PR_TRY(hipStreamSynchronize(s));
+  *n1 = *nf = 0;
+  for (int64_t j = 0; j < p; j++) {
+    if (st[(size_t)j] == kOne) (*n1)++;
+    else if (st[(size_t)j] == kFree) (*nf)++;
+    else if (st[(size_t)j] != kZero) return PR_EINVAL;
+  }
+  return PR_OK;
+}
+
 int pr_prox(void *stream, const double *v, int64_t p, double rho, int32_t k, double M,
             const int8_t *status, double *out) {
   if (!v || !out || !status || p < 1 || p >= ((int64_t)1 << 31) || !(rho > 0.0) || !isfinite(rho) ||
       !(M > 0.0) || k < 1)
     return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  std::vector<int8_t> st((size_t)p);
-  PR_TRY(hipMemcpyAsync(st.data(), status, (size_t)p, hipMemcpyDeviceToHost, s));
-  PR_TRY(hipStreamSynchronize(s));
-  int64_t n1 = 0, nf = 0;
-  for (int64_t j = 0; j < p; j++) {
-    if (st[(size_t)j] == kOne) n1++;
-    else if (st[(size_t)j] == kFree) nf++;
-    else if (st[(size_t)j] != kZero) return PR_EINVAL;
+  if (p <= reg_x_max()) {
+    XLease x;
+    const int rc = x.take(s);
+    if (rc != PR_OK) return rc;
+    PR_TRY(launch_prox_x(v, out, p, rho, k, M, status, &x.res->flag, x.xb, s));
+    PR_TRY(hipStreamSynchronize(s));
+    const int32_t flag = x.res->flag;
+    return flag == 0 ? PR_OK : (flag == 1 || flag == 2 ? PR_EINVAL : PR_EDEVICE);
   }
+  int64_t n1, nf;
+  const int rc = count_status(status, p, s, &n1, &nf);
+  if (rc != PR_OK) return rc;
   if (n1 > k) return PR_EINVAL;
   int64_t kb = (int64_t)k - n1;
   if (kb > nf) kb = nf;
@@ -1508,18 +1526,18 @@ int pr_time_prox(void *stream, const double *v, int64_t p, double rho, int32_t k
       !(M > 0.0) || k < 1 || reps < 1 || !ms_prox || !ms_g)
     return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  std::vector<int8_t> st((size_t)p);
-  PR_TRY(hipMemcpyAsync(st.data(), status, (size_t)p, hipMemcpyDeviceToHost, s));
-  PR_TRY(hipStreamSynchronize(s));
-  int64_t n1 = 0, nf = 0;
-  for (int64_t j = 0; j < p; j++) {
-    if (st[(size_t)j] == kOne) n1++;
-    else if (st[(size_t)j] == kFree) nf++;
-    else if (st[(size_t)j] != kZero) return PR_EINVAL;
-  }
+  int64_t n1, nf;
+  const int rc = count_status(status, p, s, &n1, &nf);
+  if (rc != PR_OK) return rc;
   if (n1 > k) return PR_EINVAL;
   int64_t kb = (int64_t)k - n1;
   if (kb > nf) kb = nf;
+  const bool wide = p <= reg_x_max();
+  XLease x;
+  if (wide) {
+    const int rx = x.take(s);
+    if (rx != PR_OK) return rx;
+  }
   double *abuf = nullptr, *g2 = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipMalloc((void **)&abuf, sizeof(double) * 3 * p) != hipSuccess) return PR_ENOMEM;
@@ -1527,21 +1545,29 @@ int pr_time_prox(void *stream, const double *v, int64_t p, double rho, int32_t k
     (void)hipFree(abuf);
     return PR_ENOMEM;
   }
+  auto prox = [&] {
+    return wide ? launch_prox_x(v, out, p, rho, k, M, status, nullptr, x.xb, s)
+                : launch_prox(v, out, p, rho, (int32_t)kb, M, status, abuf, nullptr, s);
+  };
+  auto reg = [&] {
+    return wide ? launch_regularizer_x(out, nullptr, p, k, M, status, g2, nullptr, x.xb, s)
+                : launch_regularizer(out, nullptr, p, (int32_t)kb, M, status, abuf, g2, s);
+  };
   hipError_t e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
   float ms = 0.0f;
   // prox: one untimed launch, then `reps` timed ones
-  if (e == hipSuccess) e = launch_prox(v, out, p, rho, (int32_t)kb, M, status, abuf, nullptr, s);
+  if (e == hipSuccess) e = prox();
   if (e == hipSuccess) e = hipEventRecord(e0, s);
-  for (int32_t i = 0; i < reps && e == hipSuccess; i++) e = launch_prox(v, out, p, rho, (int32_t)kb, M, status, abuf, nullptr, s);
+  for (int32_t i = 0; i < reps && e == hipSuccess; i++) e = prox();
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
   if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
   if (e == hipSuccess) *ms_prox = (double)ms / reps;
   // g_N at the prox output (a point of dom g_N)
-  if (e == hipSuccess) e = launch_regularizer(out, nullptr, p, (int32_t)kb, M, status, abuf, g2, s);
+  if (e == hipSuccess) e = reg();
   if (e == hipSuccess) e = hipEventRecord(e0, s);
-  for (int32_t i = 0; i < reps && e == hipSuccess; i++) e = launch_regularizer(out, nullptr, p, (int32_t)kb, M, status, abuf, g2, s);
+  for (int32_t i = 0; i < reps && e == hipSuccess; i++) e = reg();
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
   if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
@@ -1559,15 +1585,22 @@ int pr_regularizer(void *stream, const double *beta, const double *alpha, int64_
     return PR_EINVAL;
   if ((beta && !g_out) || (alpha && !gstar_out)) return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  std::vector<int8_t> st((size_t)p);
-  PR_TRY(hipMemcpyAsync(st.data(), status, (size_t)p, hipMemcpyDeviceToHost, s));
-  PR_TRY(hipStreamSynchronize(s));
-  int64_t n1 = 0, nf = 0;
-  for (int64_t j = 0; j < p; j++) {
-    if (st[(size_t)j] == kOne) n1++;
-    else if (st[(size_t)j] == kFree) nf++;
-    else if (st[(size_t)j] != kZero) return PR_EINVAL;
+  if (p <= reg_x_max()) {
+    XLease x;
+    const int rc = x.take(s);
+    if (rc != PR_OK) return rc;
+    PR_TRY(launch_regularizer_x(beta, alpha, p, k, M, status, x.res->v, &x.res->flag, x.xb, s));
+    PR_TRY(hipStreamSynchronize(s));
+    const XResult r = *x.res;
+    if (r.flag == 1) return PR_EINVAL;
+    if (r.flag != 0 && r.flag != 2) return PR_EDEVICE;
+    if (g_out) *g_out = r.flag == 2 ? INFINITY : r.v[0];
+    if (gstar_out) *gstar_out = r.flag == 2 ? -INFINITY : r.v[1];
+    return PR_OK;
   }
+  int64_t n1, nf;
+  const int rc = count_status(status, p, s, &n1, &nf);
+  if (rc != PR_OK) return rc;
   if (n1 > k) {
     if (g_out) *g_out = INFINITY;
     if (gstar_out) *gstar_out = -INFINITY;
@@ -1770,6 +1803,20 @@ FeatScalars feat_scalars(const pr_node *node, const std::vector<int8_t> &st, int
   }
   sc.kbar = kbar;
   return sc;
+}
+
+// prox_{rho g_N} and g_N / g_N* of the feasible node whose status is in
+// c->d_status, on the context's stream.
+hipError_t ctx_prox(pr_ctx *c, const pr_node &node, int32_t kbar, double rho, const double *v, double *out) {
+  if (c->P.p <= reg_x_max())
+    return launch_prox_x(v, out, c->P.p, rho, node.k, node.M, c->d_status, nullptr, c->xb, c->stream);
+  return launch_prox(v, out, c->P.p, rho, kbar, node.M, c->d_status, c->d_regscratch, nullptr, c->stream);
+}
+hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const double *beta, const double *alpha,
+                           double *out2) {
+  if (c->P.p <= reg_x_max())
+    return launch_regularizer_x(beta, alpha, c->P.p, node.k, node.M, c->d_status, out2, nullptr, c->xb, c->stream);
+  return launch_regularizer(beta, alpha, c->P.p, kbar, node.M, c->d_status, c->d_regscratch, out2, c->stream);
 }
 
 // Status of the node in c->d_status and w = X^T zeta, zeta = -grad F(X beta),
@@ -1981,14 +2028,12 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
                                s));
         PR_TRY(launch_mlp_forward(params, c->mF, p, c->mout, s));
         PR_TRY(launch_mlp_propose(bp, c->mout, p, c->mvhat, s));
-        PR_TRY(launch_prox(c->mvhat, c->mvhat, p, rho, kbars[(size_t)i], nodes[i].M, c->d_status, c->d_regscratch,
-                           nullptr, s));
+        PR_TRY(ctx_prox(c, nodes[i], kbars[(size_t)i], rho, c->mvhat, c->mvhat));
         rc = pr_dual_bound(c, &nodes[i], nullptr, c->mvhat, &lb, &ub);
         if (rc != PR_OK) return rc;
         gn = ub - lb;
       }
-      PR_TRY(launch_prox(bp, c->mx, p, rho, kbars[(size_t)i], nodes[i].M, c->d_status, c->d_regscratch, nullptr,
-                         s));
+      PR_TRY(ctx_prox(c, nodes[i], kbars[(size_t)i], rho, bp, c->mx));
       rc = pr_dual_bound(c, &nodes[i], nullptr, c->mx, &lb, &ub);
       if (rc != PR_OK) return rc;
       ga = ub - lb;
@@ -2038,12 +2083,12 @@ int pr_dual_bound(pr_ctx *c, const pr_node *node, const double *zeta, const doub
     // zeta induced from beta goes to B.zbest's twin: reuse B.gm as scratch
     PR_TRY(launch_loss_terms(c->P.loss, c->d_u, c->P.y, n, c->B.gm, scal, s));
     if (!zeta) z = c->B.gm;
-    PR_TRY(launch_regularizer(beta, nullptr, p, kbar, node->M, c->d_status, c->d_regscratch, scal + 2, s));
+    PR_TRY(ctx_regularizer(c, *node, kbar, beta, nullptr, scal + 2));
   }
   if (zeta) PR_TRY(launch_zeta_terms(c->P.loss, zeta, c->P.y, n, scal, s));
   PR_TRY(launch_gemv_t(c->P, z, nullptr, c->d_w, nullptr, nullptr, s));
   PR_TRY(launch_scale_copy(c->d_w, c->d_v, 0.5 / lam2, p, s));
-  PR_TRY(launch_regularizer(nullptr, c->d_v, p, kbar, node->M, c->d_status, c->d_regscratch, scal + 2, s));
+  PR_TRY(ctx_regularizer(c, *node, kbar, nullptr, c->d_v, scal + 2));
   double hs[4];
   PR_TRY(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
   PR_TRY(hipStreamSynchronize(s));

@@ -141,6 +141,28 @@ struct XBuf {
   uint32_t *round;
 };
 
+// What a kernel of a context-free entry point hands back, in pinned host memory.
+struct XResult {
+  double v[2];
+  int32_t flag;  // -1 until the kernel has written it
+};
+// An exchange area for one call of a context-free entry point on the current
+// device (pr_xpool.hip), given back by the destructor: the call has waited for
+// its stream by then.
+class XLease {
+ public:
+  int take(hipStream_t s);  // PR_OK or an error code
+  ~XLease();
+  XBuf xb{};
+  XResult *res = nullptr;
+
+ private:
+  int dev_ = 0, slot_ = 0;
+  uint64_t *own_ = nullptr;
+};
+// pr_prox_noalloc's own area and error flag (device memory) on the current device
+int xpool_noalloc(XBuf *xb, int32_t **flag);
+
 // AC-FGM state of a single-node solve (pr_variants.hip), device resident.
 struct AcState {
   double L1;         // first-step curvature estimate (line search)
@@ -223,6 +245,14 @@ hipError_t launch_node_init_x(const NodeParams *prm, NodeState *S, NodeBufs nb, 
                               XShape g, const XBuf &xb, hipStream_t s);
 hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B, const StepArgs &a,
                               XShape g, const XBuf &xb, hipStream_t s);
+// The standalone prox and regulariser over several workgroups, p <= reg_x_max();
+// kbar is counted from st.  *flag (optional): 0, 1 bad status code, 2 |J1| > k
+// (nothing else written then), 3 the workgroups lost each other.
+int64_t reg_x_max();
+hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
+                         int32_t *flag, const XBuf &xb, hipStream_t s);
+hipError_t launch_regularizer_x(const double *beta, const double *alpha, int64_t p, int32_t k, double M,
+                                const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s);
 hipError_t launch_batch_init(const NodeParams *prm, NodeState *S, BatchBufs bb, const double *B0, double L,
                              int64_t p, hipStream_t s);
 hipError_t launch_batch_step(const NodeParams *prm, NodeState *S, BatchBufs bb, int64_t p, hipStream_t s);

@@ -1,8 +1,10 @@
 // pr_prox_noalloc: the prox of g_N without any allocation, for callers that
 // cannot allocate device memory (code under stream capture, tight serving
-// loops, harnesses that forbid hipMalloc).  Its workspace is a file-scope
-// device array; every GPU the library runs on holds its own copy until the
-// process ends, and every call on that GPU shares it.
+// loops, harnesses that forbid hipMalloc).  Vectors up to reg_x_max() stay in
+// the registers of the workgroups that share them and need only the exchange
+// area this entry point owns; longer ones stage their magnitudes in a
+// file-scope device array.  Every GPU the library runs on holds its own copy of
+// both until the process ends, and every call on that GPU shares them.
 #include <math.h>
 
 #include <mutex>
@@ -49,17 +51,25 @@ int pr_prox_noalloc(void *stream, const double *v, int64_t p, double rho, int32_
                     const int8_t *status, double *out) {
   if (!v || !out || !status || p < 1 || !(rho > 0.0) || !isfinite(rho) || !(M > 0.0) || k < 1) return PR_EINVAL;
   if (p > kMaxP) return PR_EINVAL;
-  double *ws = nullptr;
-  const int rc = scratch_of_current_device(&ws);
-  if (rc != PR_OK) return rc;
-  int32_t *flag = reinterpret_cast<int32_t *>(ws + kMaxP);
   hipStream_t s = (hipStream_t)stream;
-  int32_t hflag = -1;
-  hipError_t e = launch_prox_counted(v, out, p, rho, k, M, status, ws, flag, s);
+  int32_t hflag = -1, *flag = nullptr;
+  hipError_t e;
+  if (p <= reg_x_max()) {
+    XBuf xb;
+    const int rc = xpool_noalloc(&xb, &flag);
+    if (rc != PR_OK) return rc;
+    e = launch_prox_x(v, out, p, rho, k, M, status, flag, xb, s);
+  } else {
+    double *ws = nullptr;
+    const int rc = scratch_of_current_device(&ws);
+    if (rc != PR_OK) return rc;
+    flag = reinterpret_cast<int32_t *>(ws + kMaxP);
+    e = launch_prox_counted(v, out, p, rho, k, M, status, ws, flag, s);
+  }
   if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(hflag), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return PR_EDEVICE;
-  return hflag == 0 ? PR_OK : PR_EINVAL;
+  return hflag == 0 ? PR_OK : (hflag == 1 || hflag == 2 ? PR_EINVAL : PR_EDEVICE);
 }
 
 }  // extern "C"

@@ -35,12 +35,15 @@ struct Codes {
     const int b = wg * EPT;
     w = stp[(b >> 4) * NT + (int)threadIdx.x] >> (2 * (b & 15));
   }
-  __device__ __forceinline__ void load(const int8_t *__restrict__ st, int64_t j0, int64_t p) {
+  // from the status vector; `bad` counts the codes outside {free, J0, J1}
+  __device__ __forceinline__ void load(const int8_t *__restrict__ st, int64_t j0, int64_t p, int &bad) {
     w = 0u;
 #pragma unroll
     for (int e = 0; e < EPT; e++) {
       const int64_t j = j0 + (int64_t)e * NT;
-      w |= (j < p ? (uint32_t)st[j] & 3u : 3u) << (2 * e);
+      const int c = j < p ? (int)st[j] : 3;
+      if (j < p && (c < 0 || c > 2)) bad++;
+      w |= ((uint32_t)c & 3u) << (2 * e);
     }
   }
 };
@@ -75,10 +78,13 @@ __device__ __forceinline__ void rank_window(NodeXLds &L, int cw, int mm, double 
 
 // Exact k-th largest of the entries aval(e) >= 0 over all workgroups, 1 <= k
 // <= their number.  A bracket of IEEE bit patterns (monotone for non-negative
-// doubles) that holds the value shrinks 16-fold per exchange by the counts at
-// 15 inner points, until it is a single pattern or holds at most 64 entries,
-// which every workgroup then gathers and ranks.  [lo, hi) with nlo entries
-// >= lo (at least k) and nhi >= hi (fewer than k) is the starting bracket.
+// doubles) that holds the value shrinks by the counts at 15 inner points per
+// exchange, until it is a single pattern or holds at most 64 entries, which
+// every workgroup then gathers and ranks.  [lo, hi) with nlo entries >= lo
+// (at least k) and nhi >= hi (fewer than k) is the starting bracket.  The k-th
+// of the largest values lies near the upper end, so the first points are a
+// quarter of a binary order apart below it, the second's four orders, and only
+// then do they divide the bracket evenly.
 template <int EPT, class F>
 __device__ double select_x(F aval, int k, uint64_t lo, uint64_t hi, double nlo, double nhi, NodeXLds &L, Group &X) {
   uint64_t key[EPT];
@@ -88,12 +94,16 @@ __device__ double select_x(F aval, int k, uint64_t lo, uint64_t hi, double nlo, 
     key[e] = a >= 0.0 ? (uint64_t)__double_as_longlong(a) + 1u : 0u;  // 0: ignored
   }
   const int lane = lane_id();
+  int width = 50;  // log2 of the spacing below hi
   while (hi - lo > 1 && nlo - nhi > (double)xwg::kGat) {
-    const uint64_t step = (hi - lo + 15u) >> 4;
+    uint64_t step = (hi - lo + 15u) >> 4;
+    if (width < 58 && step > (1ull << width)) step = 1ull << width;
+    width += 4;
+    const uint64_t first = hi - lo > 16 * step ? hi - 15 * step : lo + step;
     int c = 0;
 #pragma unroll 1
     for (int i = 0; i < 15; i++) {
-      const uint64_t pv = lo + step * (uint64_t)(i + 1);
+      const uint64_t pv = first + step * (uint64_t)i;
       int n = 0;
 #pragma unroll
       for (int e = 0; e < EPT; e++) n += __popcll(__ballot(key[e] > pv));  // entries whose pattern is >= pv
@@ -101,18 +111,17 @@ __device__ double select_x(F aval, int k, uint64_t lo, uint64_t hi, double nlo, 
     }
     const double tot = X.counts<15>((double)c);
     if (X.failed) return 0.0;
-    const uint64_t mine = lo + step * (uint64_t)(lane + 1);
+    const uint64_t mine = first + step * (uint64_t)lane;
     const bool in = lane < 15 && mine < hi;
     const unsigned long long up = __ballot(in && tot >= (double)k), dn = __ballot(in && !(tot >= (double)k));
-    const uint64_t lo0 = lo;
     if (up) {
       const int i = 63 - __clzll((long long)up);
-      lo = lo0 + step * (uint64_t)(i + 1);
+      lo = first + step * (uint64_t)i;
       nlo = __shfl(tot, i, 64);
     }
     if (dn) {
       const int i = __ffsll((long long)dn) - 1;
-      hi = lo0 + step * (uint64_t)(i + 1);
+      hi = first + step * (uint64_t)i;
       nhi = __shfl(tot, i, 64);
     }
   }
@@ -152,49 +161,33 @@ __device__ double select_x(F aval, int k, uint64_t lo, uint64_t hi, double nlo, 
   return L.bc[0];
 }
 
-// The prox threshold tau (the search of solve_tau, pr_regularizer.h) over the
-// register-resident magnitudes aval(e): the statistics of the first pass
-// travel with the evaluation at the previous tau, when there is one.
+// Per-thread part of one evaluation of the prox threshold's S(tau): {head
+// count, count, block sum} over the magnitudes aval(e).
 template <int EPT, class F>
-__device__ __forceinline__ double solve_tau_x(F aval, int kbar, double rho, double M, double warm, Group &X,
-                                              int *evals) {
-  const bool finM = isfinite(M);
-  auto Dof = [&](double t) { return finM ? fmin(t / rho, M) : t / rho; };
-  auto eval = [&](double tau, double (&v)[3]) {
-    const double top = tau + Dof(tau);
-    v[0] = v[1] = v[2] = 0.0;
-#pragma unroll
-    for (int e = 0; e < EPT; e++) {
-      const double x = aval(e);
-      if (x > tau) {
-        v[1] += 1.0;
-        if (x > top) v[0] += 1.0;
-        else v[2] += x;
-      }
-    }
-  };
-  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  double mx[1] = {0.0};
+__device__ __forceinline__ void tau_sums(F aval, double rho, double M, double tau, double *v) {
+  const double top = tau + (isfinite(M) ? fmin(tau / rho, M) : tau / rho);
+  v[0] = v[1] = v[2] = 0.0;
 #pragma unroll
   for (int e = 0; e < EPT; e++) {
     const double x = aval(e);
-    if (x > 0.0) {
-      s[3] += 1.0;
-      s[4] += x;
-      mx[0] = fmax(mx[0], x);
+    if (x > tau) {
+      v[1] += 1.0;
+      if (x > top) v[0] += 1.0;
+      else v[2] += x;
     }
   }
-  if (warm > 0.0) {
-    double v[3];
-    eval(warm, v);
-    s[0] = v[0];
-    s[1] = v[1];
-    s[2] = v[2];
-  }
-  X.summax(s, mx);
-  const double amax = mx[0];
+}
+
+// The prox threshold tau (the search of solve_tau, pr_regularizer.h) over the
+// register-resident magnitudes aval(e).  s: the totals {evaluation at warm
+// (used when warm lies inside the bracket), number and sum of the positive
+// magnitudes}, amax their largest.
+template <int EPT, class F>
+__device__ __forceinline__ double solve_tau_x(F aval, int kbar, double rho, double M, double warm, const double *s,
+                                              double amax, Group &X, int *evals) {
+  const bool finM = isfinite(M);
+  auto Dof = [&](double t) { return finM ? fmin(t / rho, M) : t / rho; };
   *evals = 0;
-  if (X.failed) return 0.0;
   if (kbar <= 0) return INFINITY;
   const double K = (double)kbar;
   if (s[3] <= K) return 0.0;
@@ -218,7 +211,7 @@ __device__ __forceinline__ double solve_tau_x(F aval, int kbar, double rho, doub
     const double D = Dof(tau);
     double v[3] = {s[0], s[1], s[2]};
     if (!have) {
-      eval(tau, v);
+      tau_sums<EPT>(aval, rho, M, tau, v);
       X.sum(v);
       if (X.failed) return 0.0;
     }
@@ -457,6 +450,7 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
   sv.load_packed(A.stp, X.w);
   double x[EPT], xk[EPT], xq[EPT], g2[EPT];
   double r1[4] = {0.0, 0.0, 0.0, 0.0};  // sum_{J1} H_M(w), #{w > wb}, #{w >= wa}, sum_{w > wb} H_M(w)
+  double wmax[1] = {0.0};               // the largest free |w|
 #pragma unroll
   for (int e = 0; e < EPT; e++) {
     const int64_t j = j0 + (int64_t)e * NT;
@@ -492,6 +486,7 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
     if (s == kOne) r1[0] += huber(w, M);
     if (s == kFree) {
       const double aw = fabs(w);
+      wmax[0] = fmax(wmax[0], aw);
       if (aw > wb) {
         r1[1] += 1.0;
         r1[3] += huber(aw, M);
@@ -523,7 +518,7 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
         }
       }
     };
-    X.run<4, 0, false>(r1, nullptr, nullptr, pub, take);
+    X.run<4, 1, false>(r1, wmax, nullptr, pub, take);
   }
   if (X.failed) {
     give_up(S, X, xb);
@@ -546,8 +541,8 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
     tkn = lds.bc[0];
     topsum = lds.bc[1];
   } else if (kbar > 0) {
-    // the bracket the window counts leave (all patterns up to infinity without)
-    uint64_t lo = 0ull, hi = 0x7ff0000000000001ull;
+    // the bracket the window counts leave (all patterns up to the largest without)
+    uint64_t lo = 0ull, hi = (uint64_t)__double_as_longlong(wmax[0]) + 1u;
     double nlo = (double)p, nhi = 0.0;
     if (wv) {
       const uint64_t ka = (uint64_t)__double_as_longlong(wa), kb = (uint64_t)__double_as_longlong(wb) + 1u;
@@ -670,7 +665,19 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
   const double rho = 2.0 * lam2 * invL;
   int evals = 0;
   auto vabs = [&](int e) { return sv(e) == kFree ? fabs(x[e]) : -1.0; };
-  const double tau = solve_tau_x<EPT>(vabs, kbar, rho, M, s0.tau, X, &evals);
+  double sv5[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, mx[1] = {0.0};
+#pragma unroll
+  for (int e = 0; e < EPT; e++) {
+    const double a = vabs(e);
+    if (a > 0.0) {
+      sv5[3] += 1.0;
+      sv5[4] += a;
+      mx[0] = fmax(mx[0], a);
+    }
+  }
+  if (s0.tau > 0.0) tau_sums<EPT>(vabs, rho, M, s0.tau, sv5);
+  X.summax(sv5, mx);
+  const double tau = solve_tau_x<EPT>(vabs, kbar, rho, M, s0.tau, sv5, mx[0], X, &evals);
   if (X.failed) {
     give_up(S, X, xb);
     return;
@@ -708,6 +715,138 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
     S->parity = parity ^ 1;
     S->iter = it + 1;
   }
+  X.finish(xb);
+}
+
+// Standalone prox_{rho g_N}(v) (Algorithm 2 + Moreau, pooled-threshold form).
+// |J1| and |J_f| are counted here, kbar = min(k - |J1|, |J_f|).  *flag: 0, 1
+// for a status code outside {free, J0, J1}, 2 for |J1| > k (out is not written
+// then), 3 when the workgroups lost each other.
+template <int EPT>
+__global__ __launch_bounds__(NT) void k_prox_x(const double *v, double *out, int64_t p, double rho, int k, double M,
+                                               const int8_t *__restrict__ st, int32_t *flag, XBuf xb) {
+  __shared__ xwg::Lds lds;
+  Group X;
+  X.init(xb, &lds);
+  const int64_t j0 = (int64_t)X.w * (EPT * NT) + threadIdx.x;
+  double x[EPT];
+  double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, mx[1] = {0.0};  // bad codes, |J1|, |J_f|, #, sum of a > 0
+  Codes<EPT> sv;
+  int bad = 0;
+  sv.load(st, j0, p, bad);
+#pragma unroll
+  for (int e = 0; e < EPT; e++) {
+    const int64_t j = j0 + (int64_t)e * NT;
+    x[e] = j < p ? v[j] : 0.0;
+    const int c = sv(e);
+    s[1] += c == kOne ? 1.0 : 0.0;
+    s[2] += c == kFree ? 1.0 : 0.0;
+    const double a = c == kFree ? fabs(x[e]) : 0.0;
+    if (a > 0.0) {
+      s[3] += 1.0;
+      s[4] += a;
+      mx[0] = fmax(mx[0], a);
+    }
+  }
+  s[0] = (double)bad;
+  X.summax(s, mx);
+  const bool lead = X.w == 0 && threadIdx.x == 0;
+  int err = X.failed ? 3 : (s[0] > 0.0 ? 1 : (s[1] > (double)k ? 2 : 0));
+  if (err == 0) {
+    const int kbar = (int)fmin((double)k - s[1], s[2]);
+    auto vabs = [&](int e) { return sv(e) == kFree ? fabs(x[e]) : -1.0; };
+    int evals;
+    const double tau = solve_tau_x<EPT>(vabs, kbar, rho, M, -1.0, s, mx[0], X, &evals);
+    const double inv1p = 1.0 / (1.0 + rho);
+    if (X.failed) {
+      err = 3;
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; e++) {
+        const int c = sv(e);
+        if (c == 3) continue;
+        double xv = 0.0;
+        if (c != kZero) {
+          const double av = fabs(x[e]);
+          double r = fmin(av * inv1p, M);
+          if (c == kFree) r = fmin(r, fmax(av - tau, 0.0));
+          xv = (r == 0.0) ? 0.0 : copysign(r, x[e]);
+        }
+        out[j0 + (int64_t)e * NT] = xv;
+      }
+    }
+  }
+  if (lead && flag) *flag = err;
+  X.finish(xb);
+}
+
+// g_N(beta) (Algorithm 1, +inf off its domain) into out[0], g_N*(alpha) into
+// out[1] (each if its input is given); counts and *flag as in k_prox_x.
+template <int EPT>
+__global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__ beta,
+                                                      const double *__restrict__ alpha, int64_t p, int k, double M,
+                                                      const int8_t *__restrict__ st, double *out, int32_t *flag,
+                                                      XBuf xb) {
+  __shared__ NodeXLds lds;
+  Group X;
+  X.init(xb, &lds.x);
+  const int64_t j0 = (int64_t)X.w * (EPT * NT) + threadIdx.x;
+  Codes<EPT> sv;
+  int bad = 0;
+  sv.load(st, j0, p, bad);
+  double x[EPT], a[EPT];
+  // bad codes, |J1|, |J_f|, theta, sum_{J1} beta^2, sum_{J1} H_M(alpha); maxima of |beta|, of free |alpha|
+  double s[6] = {(double)bad, 0.0, 0.0, 0.0, 0.0, 0.0}, m[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int e = 0; e < EPT; e++) {
+    const int64_t j = j0 + (int64_t)e * NT;
+    x[e] = (beta && j < p) ? beta[j] : 0.0;
+    a[e] = (alpha && j < p) ? alpha[j] : 0.0;
+    const int c = sv(e);
+    s[1] += c == kOne ? 1.0 : 0.0;
+    s[2] += c == kFree ? 1.0 : 0.0;
+    if (c == kOne) s[5] += huber(a[e], M);
+    if (c == kFree) m[3] = fmax(m[3], fabs(a[e]));
+  }
+  {
+    const XStats t = local_stats<EPT>(x, sv);
+    s[3] = t.theta;
+    s[4] = t.sq1;
+    m[0] = t.amax;
+    m[1] = t.j0max;
+    m[2] = t.boxmax;
+  }
+  X.summax(s, m);
+  const bool lead = X.w == 0 && threadIdx.x == 0;
+  int err = X.failed ? 3 : (s[0] > 0.0 ? 1 : (s[1] > (double)k ? 2 : 0));
+  if (err == 0) {
+    const int kbar = (int)fmin((double)k - s[1], s[2]);
+    if (beta) {
+      const XStats t{s[3], s[4], m[0], m[1], m[2]};
+      auto xabs = [&](int e) { return sv(e) == kFree ? fabs(x[e]) : -1.0; };
+      const double g = 0.5 * t.sq1 + alg1_x<EPT>(xabs, kbar, t.theta, X);
+      if (lead) out[0] = in_domain(t, kbar, M) ? g : INFINITY;
+    }
+    if (alpha) {
+      auto aabs = [&](int e) { return sv(e) == kFree ? fabs(a[e]) : -1.0; };
+      double top = 0.0;
+      if (kbar > 0) {
+        const double t = select_x<EPT>(aabs, kbar, 0ull, (uint64_t)__double_as_longlong(m[3]) + 1u, s[2], 0.0, lds, X);
+        const double Ht = huber(t, M);
+        double v[1] = {0.0};
+#pragma unroll
+        for (int e = 0; e < EPT; e++) {
+          const double w = aabs(e);
+          if (w >= 0.0) v[0] += fmax(huber(w, M) - Ht, 0.0);
+        }
+        X.sum(v);
+        top = (double)kbar * Ht + v[0];
+      }
+      if (lead) out[1] = s[5] + top;
+    }
+    if (X.failed) err = 3;
+  }
+  if (lead && flag) *flag = err;
   X.finish(xb);
 }
 
@@ -750,5 +889,47 @@ hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, 
   }
   return hipGetLastError();
 }
+
+// Shape of the standalone kernels: one workgroup up to kXOne entries (its
+// reductions stay in LDS), then few entries per thread as above.
+constexpr int64_t kXOne = 4096;
+static XShape reg_xshape(int64_t p) {
+  for (int e = 1; e <= 16; e *= 2) {
+    const int64_t w = (p + (int64_t)e * NT - 1) / ((int64_t)e * NT);
+    if (w == 1 && p <= kXOne) return XShape{1, e};
+    if (p > kXOne && e >= 4 && w <= kXwgMax) return XShape{(int)w, e};
+  }
+  return XShape{0, 0};
+}
+
+int64_t reg_x_max() { return (int64_t)kXwgMax * 16 * NT; }
+
+#define PR_REGX(CALL)        \
+  switch (g.ept) {           \
+    case 1: CALL(1); break;  \
+    case 2: CALL(2); break;  \
+    case 4: CALL(4); break;  \
+    case 8: CALL(8); break;  \
+    case 16: CALL(16); break; \
+    default: return hipErrorInvalidValue; \
+  }
+hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
+                         int32_t *flag, const XBuf &xb, hipStream_t s) {
+  const XShape g = reg_xshape(p);
+#define PR_CALL(E) k_prox_x<E><<<g.wgs, NT, 0, s>>>(v, out, p, rho, k, M, st, flag, xb)
+  PR_REGX(PR_CALL)
+#undef PR_CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_regularizer_x(const double *beta, const double *alpha, int64_t p, int32_t k, double M,
+                                const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s) {
+  const XShape g = reg_xshape(p);
+#define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, p, k, M, st, out2, flag, xb)
+  PR_REGX(PR_CALL)
+#undef PR_CALL
+  return hipGetLastError();
+}
+#undef PR_REGX
 
 }  // namespace pr

@@ -69,3 +69,69 @@ def test_wide_node_traces(dev, p, k, n0, n1, M, warm, loss):
     assert (again["lower_bound"], again["primal"]) == (r["lower_bound"], r["primal"])
     assert torch.equal(again["beta"], r["beta"])
     ctx.close()
+
+
+@pytest.mark.parametrize("p", [1, 512, 513, 4096, 4097, 131072, 131073, 524288, 524289])
+@pytest.mark.parametrize("ties", [False, True])
+def test_prox_and_regularizer_at_shape_edges(dev, p, ties):
+    """prox_{rho g_N}, g_N and g_N* where the number of workgroups and the
+    entries per thread change (524289: the kernels over global memory), with
+    many equal magnitudes and zeros and a cardinality past the gather's 64
+    entries: 1e-12 of Algorithms 1 and 2, the tolerance of the other prox tests."""
+    import torch
+    import paper_2603_01306_amd as pr
+    print(f"prox edges p={p} ties={ties}", flush=True)
+    rng = np.random.default_rng(p + ties)
+    v = rng.standard_normal(p)
+    if ties:
+        v = np.round(v, 1)  # about 80 magnitudes, exact zeros among them
+    st = np.zeros(p, dtype=np.int8)
+    if p > 100:
+        idx = rng.permutation(p)
+        st[idx[:20]] = oracle.ZERO
+        st[idx[20:23]] = oracle.ONE
+    k = min(300, max(4, p // 10))
+    dv, ds = torch.from_numpy(v).to(dev), torch.from_numpy(st).to(dev)
+    for rho, M in ((0.6, 2.0), (1.3, float("inf"))):
+        x = pr.prox(dv, rho, k, M, ds).cpu().numpy()
+        ref = oracle.prox_g(v, rho, k, M, st)
+        assert np.abs(x - ref).max() <= 1e-12 * max(1.0, np.abs(ref).max())
+        g, gs = pr.regularizer(torch.from_numpy(ref).to(dev), dv, k, M, ds)
+        go, gso = oracle.g(ref, k, st), oracle.gstar(v, k, M, st)
+        assert abs(g - go) <= 1e-12 * max(1.0, abs(go)) and abs(gs - gso) <= 1e-12 * max(1.0, abs(gso))
+        assert pr.regularizer(None, dv, k, M, ds)[1] == gs
+    bad = ds.clone()
+    bad[p - 1] = 3
+    out = torch.full_like(dv, 7.0)
+    for fn in (lambda: pr.prox(dv, 0.5, k, 2.0, bad), lambda: pr.regularizer(dv, None, k, 2.0, bad),
+               lambda: pr.prox_noalloc(dv, 0.5, k, 2.0, bad, out=out)):
+        with pytest.raises(pr.PrError):
+            fn()
+    assert torch.all(out == 7.0)
+
+
+def test_prox_from_many_threads_and_streams(dev):
+    """More concurrent calls than the library keeps exchange areas for, each on
+    a stream of its own: every result equals the serial one."""
+    import threading
+    import torch
+    import paper_2603_01306_amd as pr
+    gen = np.random.default_rng(3)
+    cases = [torch.from_numpy(gen.standard_normal(20000 + 1000 * i)).to(dev) for i in range(12)]
+    sts = [torch.zeros(v.numel(), dtype=torch.int8, device=dev) for v in cases]
+    serial = [(pr.prox(v, 0.7, 12, 2.0, s), pr.regularizer(v, v, 12, 2.0, s)) for v, s in zip(cases, sts)]
+    torch.cuda.synchronize()
+    got = [None] * len(cases)
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                got[i] = (pr.prox(cases[i], 0.7, 12, 2.0, sts[i]), pr.regularizer(cases[i], cases[i], 12, 2.0, sts[i]))
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for (x, g), (y, h) in zip(serial, got):
+        assert torch.equal(x, y) and g == h
