@@ -140,8 +140,7 @@ struct pr_ctx {
   // learned warm start (allocated on first use)
   uint16_t *mF = nullptr;  // [p][8] features of one node
   float *mout = nullptr;   // [p] network outputs
-  double *mnz = nullptr;   // [p] compacted nonzero magnitudes
-  double *mfs = nullptr;   // {max |w|, nnz}
+  FeatBufs fb{};           // feature scratch, fb.cap nodes (one, or max_batch on the batched path)
   double *mvhat = nullptr, *mx = nullptr;  // [p] proposal before / after the prox step
   // batched warm start: proposals, w = X^T zeta at the parents [max_batch padded][p],
   // feature rows [..][p][8], network outputs [..][p]
@@ -188,7 +187,7 @@ void free_ctx(pr_ctx *c) {
       if (b) (void)hipFree(b);
   }
   void *bb[] = {c->bstp, c->Xrow, c->Uprev, c->Ucur, c->Uy, c->bdsum, c->bybt, c->bgbt, c->d_rowmap2, c->Bx, c->Rd, c->CF, c->CT, c->fsum, c->bx0, c->bx1, c->bxbest, c->bhprev,
-                c->bsval, c->bsidx, c->bstatus, c->d_bprm, c->d_bstate, c->d_active, c->d_rowmap, c->d_split, c->d_ftab, c->mF, c->mout, c->mnz, c->mfs, c->mvhat, c->mx, c->G, c->gb, c->BG.part, c->nb.xlb, c->mVb, c->mWb, c->mFb, c->moutb, c->mPb};
+                c->bsval, c->bsidx, c->bstatus, c->d_bprm, c->d_bstate, c->d_active, c->d_rowmap, c->d_split, c->d_ftab, c->mF, c->mout, c->fb.nzv, c->fb.nzi, c->fb.rank, c->fb.fs, c->fb.sc, c->mvhat, c->mx, c->G, c->gb, c->BG.part, c->nb.xlb, c->mVb, c->mWb, c->mFb, c->moutb, c->mPb};
   for (void *b : bb)
     if (b) (void)hipFree(b);
   if (c->h_bstate) (void)hipHostFree(c->h_bstate);
@@ -222,23 +221,22 @@ int pr::build_status(const pr_node *node, int64_t p, std::vector<int8_t> &st, in
   if (node->n0 < 0 || node->n1 < 0 || (node->n0 > 0 && !node->J0) || (node->n1 > 0 && !node->J1))
     return PR_EINVAL;
   st.assign((size_t)p, (int8_t)kFree);
+  int64_t nzero = 0;  // an index may be listed twice
+  n1 = 0;
   for (int64_t i = 0; i < node->n0; i++) {
     int64_t j = node->J0[i];
     if (j < 0 || j >= p) return PR_EINVAL;
+    nzero += st[(size_t)j] != kZero;
     st[(size_t)j] = (int8_t)kZero;
   }
   for (int64_t i = 0; i < node->n1; i++) {
     int64_t j = node->J1[i];
     if (j < 0 || j >= p) return PR_EINVAL;
     if (st[(size_t)j] == kZero) return PR_EOVERLAP;
+    n1 += st[(size_t)j] != kOne;
     st[(size_t)j] = (int8_t)kOne;
   }
-  n1 = 0;
-  int64_t nf = 0;
-  for (int64_t j = 0; j < p; j++) {
-    if (st[(size_t)j] == kOne) n1++;
-    else if (st[(size_t)j] == kFree) nf++;
-  }
+  const int64_t nf = p - nzero - n1;
   pbar = nf;
   infeasible = n1 > (int64_t)node->k;
   int64_t kb = infeasible ? 0 : (int64_t)node->k - n1;
@@ -980,26 +978,18 @@ int build_union(pr_ctx *c, int32_t m, bool fresh, bool *changed) {
   return PR_OK;
 }
 
-// FP64 values of the m batched nodes at their stopping iterates (rows of
-// bxbest), over the stored X, for every node at once: the forward product
-// X_it X^T and the transposed product R X on the batch's FP64-accumulated
-// GEMMs (split as the iteration splits them), residual rows and loss sums,
-// then one workgroup per node for g_N(x) and g_N*(X^T zeta / (2 lambda2)).
-// lb[q] = Psi(zeta_q) with zeta_q = 2 (y - X x_q), ub[q] = Phi(x_q).
-int certify_batch(pr_ctx *c, int32_t m, std::vector<double> &lb, std::vector<double> &ub, int32_t *kst_out = nullptr) {
+// Loss rows and transposed products of the points in the rows 0 .. m-1 of Bx,
+// over the stored X: u = X x, zeta (least squares r) and the loss sums, X^T of
+// them in the split planes of CT (*kst of them), split as the iteration does.
+int batch_products(pr_ctx *c, int32_t m, int32_t *kst_out) {
   const int64_t n = c->P.n, p = c->P.p;
-  const int NrMax = nr_of(c->max_batch), Nr = nr_of(m), NrT = nr_of(c->rs * m);
+  const int Nr = nr_of(m), NrT = nr_of(c->rs * m);
   hipStream_t s = c->stream;
-  if (!c->cert_a) {
-    bool ok = dalloc(&c->cert_a, (size_t)NrMax * p) == hipSuccess && dalloc(&c->d_cert, 2 * (size_t)NrMax) == hipSuccess;
-    if (!ok) return PR_ENOMEM;
-  }
   int nta = Nr / 64;
   if (nta >= kTuneMax) nta = kTuneMax - 1;
   static_assert(kTuneTables >= 2, "forward and transpose split tables");
   const int32_t ksf = c->KSF * c->h_ftab[nta];
   const int32_t kst = kst_for(c, m);
-  PR_TRY(hipMemcpyAsync(c->Bx, c->bxbest, sizeof(double) * m * p, hipMemcpyDeviceToDevice, s));
   PR_TRY(hipMemcpyAsync(c->d_split + 6, &ksf, sizeof(int32_t), hipMemcpyHostToDevice, s));
   PR_TRY(launch_gemm_any(c->P.xdt, c->Xrow, p, kF64, c->Bx, p, c->CF, n, Nr, p, ksf, nullptr, nullptr, nullptr,
                          nullptr, ksf, nullptr, s));
@@ -1007,6 +997,28 @@ int certify_batch(pr_ctx *c, int32_t m, std::vector<double> &lb, std::vector<dou
                             s));
   PR_TRY(launch_gemm_any(c->P.xdt, c->P.X, n, kF64, c->Rd, n, c->CT, p, NrT, n, kst, nullptr, nullptr, nullptr,
                          nullptr, kst, nullptr, s));
+  *kst_out = kst;
+  return PR_OK;
+}
+
+// FP64 values of the m batched nodes at their stopping iterates (rows of
+// bxbest), over the stored X, for every node at once: the forward product
+// X_it X^T and the transposed product R X on the batch's FP64-accumulated
+// GEMMs (split as the iteration splits them), residual rows and loss sums,
+// then one workgroup per node for g_N(x) and g_N*(X^T zeta / (2 lambda2)).
+// lb[q] = Psi(zeta_q) with zeta_q = 2 (y - X x_q), ub[q] = Phi(x_q).
+int certify_batch(pr_ctx *c, int32_t m, std::vector<double> &lb, std::vector<double> &ub, int32_t *kst_out = nullptr) {
+  const int64_t p = c->P.p;
+  const int NrMax = nr_of(c->max_batch), NrT = nr_of(c->rs * m);
+  hipStream_t s = c->stream;
+  if (!c->cert_a) {
+    bool ok = dalloc(&c->cert_a, (size_t)NrMax * p) == hipSuccess && dalloc(&c->d_cert, 2 * (size_t)NrMax) == hipSuccess;
+    if (!ok) return PR_ENOMEM;
+  }
+  PR_TRY(hipMemcpyAsync(c->Bx, c->bxbest, sizeof(double) * m * p, hipMemcpyDeviceToDevice, s));
+  int32_t kst = 1;
+  const int rc = batch_products(c, m, &kst);
+  if (rc != PR_OK) return rc;
   PR_TRY(launch_cert_batch(c->d_bprm, c->bxbest, c->CT, kst, NrT, c->rs, c->fsum, c->nfb, p, c->cert_a, c->bsidx,
                            c->bsval, c->d_cert, m, s));
   if (kst_out) *kst_out = kst;
@@ -1787,20 +1799,22 @@ int ensure_mlp(pr_ctx *c) {
   if (c->mF) return PR_OK;
   const int64_t p = c->P.p;
   bool ok = dalloc(&c->mF, (size_t)p * 8) == hipSuccess && dalloc(&c->mout, (size_t)p) == hipSuccess;
-  ok = ok && dalloc(&c->mnz, (size_t)p) == hipSuccess && dalloc(&c->mfs, 2) == hipSuccess;
+  const int cap = c->batch_ok ? c->max_batch : 1;
+  FeatBufs &f = c->fb;
+  ok = ok && dalloc(&f.nzv, (size_t)cap * p) == hipSuccess && dalloc(&f.nzi, (size_t)cap * p) == hipSuccess;
+  ok = ok && dalloc(&f.rank, (size_t)cap * p) == hipSuccess && dalloc(&f.fs, 2 * (size_t)cap) == hipSuccess;
+  ok = ok && dalloc(&f.sc, (size_t)cap) == hipSuccess;
+  f.cap = cap;
   ok = ok && dalloc(&c->mvhat, (size_t)p) == hipSuccess && dalloc(&c->mx, (size_t)p) == hipSuccess;
   return ok ? PR_OK : PR_ENOMEM;
 }
 
-FeatScalars feat_scalars(const pr_node *node, const std::vector<int8_t> &st, int32_t kbar) {
+FeatScalars feat_scalars(const pr_node *node, int64_t p, int64_t n1, int64_t pbar, int32_t kbar) {
   FeatScalars sc;
   sc.lambda2 = node->lambda2;
   sc.k = node->k;
-  sc.n0 = sc.n1 = 0;
-  for (int8_t v : st) {
-    sc.n0 += v == kZero;
-    sc.n1 += v == kOne;
-  }
+  sc.n0 = (int32_t)(p - n1 - pbar);
+  sc.n1 = (int32_t)n1;
   sc.kbar = kbar;
   return sc;
 }
@@ -1819,17 +1833,41 @@ hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const d
   return launch_regularizer(beta, alpha, c->P.p, kbar, node.M, c->d_status, c->d_regscratch, out2, c->stream);
 }
 
-// Status of the node in c->d_status and w = X^T zeta, zeta = -grad F(X beta),
-// in c->d_w: the inputs of the feature kernel.
-int grad_image(pr_ctx *c, const std::vector<int8_t> &st, const double *beta) {
-  const int64_t n = c->P.n, p = c->P.p;
+// w = X^T zeta, zeta = -grad F(X beta), in c->d_w: an input of the features.
+int grad_image(pr_ctx *c, const double *beta) {
+  const int64_t n = c->P.n;
   hipStream_t s = c->stream;
-  PR_TRY(hipMemcpyAsync(c->d_status, st.data(), (size_t)p, hipMemcpyHostToDevice, s));
   if (launch_spfwd(c->P, c->B, c->iota, beta, c->d_np, kSpPlain, nullptr, c->d_u, s) != hipSuccess)
     return PR_EDEVICE;
   PR_TRY(launch_loss_terms(c->P.loss, c->d_u, c->P.y, n, c->B.gm, c->d_scal, s));
   PR_TRY(launch_gemv_t(c->P, c->B.gm, nullptr, c->d_w, nullptr, nullptr, s));
   return PR_OK;
+}
+
+// The same of m nodes (rows of Bp) in the rows of c->mWb, from one pass of the
+// batch's two FP64 GEMMs.
+int grad_images(pr_ctx *c, int32_t m, const double *Bp) {
+  const int64_t p = c->P.p;
+  hipStream_t s = c->stream;
+  if (!c->mWb && dalloc(&c->mWb, (size_t)nr_of(c->max_batch) * p) != hipSuccess) return PR_ENOMEM;
+  PR_TRY(hipMemcpyAsync(c->Bx, Bp, sizeof(double) * m * p, hipMemcpyDeviceToDevice, s));
+  int32_t kst = 1;
+  const int rc = batch_products(c, m, &kst);
+  if (rc != PR_OK) return rc;
+  // least squares: the planes hold X^T r, zeta = 2 r
+  PR_TRY(launch_sum_planes(c->CT, kst, nr_of(c->rs * m), c->rs, p, m, c->P.loss == kLsq ? 2.0 : 1.0, c->mWb, s));
+  return PR_OK;
+}
+
+// Whether m images go faster together: the tuned times of the two GEMMs at m
+// rows against two passes over X per node (a 64-row tile costs the same for
+// one node as for 64: 16384 x 8192 in BF16, 0.55 ms against 0.1 per node).
+bool images_pay(const pr_ctx *c, int32_t m) {
+  if (!c->batch_ok) return false;
+  int nta = nr_of(m) / 64, nta2 = nr_of(c->rs * m) / 64;
+  if (nta >= kTuneMax) nta = kTuneMax - 1;
+  if (nta2 >= kTuneMax) nta2 = kTuneMax - 1;
+  return 2.0 * m * c->t_gemv_ms >= c->h_tbest[nta] + c->h_tbest[kTuneMax + nta2];
 }
 
 }  // namespace
@@ -1838,26 +1876,38 @@ int pr_mlp_features(pr_ctx *c, const pr_node *nodes, int32_t m, const double *Bp
                     uint16_t *F, float *T) {
   if (!c || !nodes || m < 0 || !Bparent || !F || (Bchild && !T) || ((uintptr_t)F) % 16) return PR_EINVAL;
   const int64_t p = c->P.p;
-  std::vector<std::vector<int8_t>> sts((size_t)m);
-  std::vector<int32_t> kbars((size_t)m);
+  std::vector<int8_t> sts((size_t)m * p), st;
+  std::vector<FeatScalars> scs((size_t)m);
   for (int32_t i = 0; i < m; i++) {
     int64_t n1, pbar;
+    int32_t kbar;
     bool inf;
-    int rc = build_status(&nodes[i], p, sts[(size_t)i], n1, pbar, kbars[(size_t)i], inf);
+    int rc = build_status(&nodes[i], p, st, n1, pbar, kbar, inf);
     if (rc != PR_OK) return rc;
-    if (inf) kbars[(size_t)i] = 0;
+    std::copy(st.begin(), st.end(), sts.begin() + (size_t)i * p);
+    scs[(size_t)i] = feat_scalars(&nodes[i], p, n1, pbar, kbar);
   }
   int rc = ensure_mlp(c);
   if (rc != PR_OK) return rc;
   hipStream_t s = c->stream;
-  for (int32_t i = 0; i < m; i++) {
-    const double *bp = Bparent + (int64_t)i * p;
-    rc = grad_image(c, sts[(size_t)i], bp);
+  for (int32_t i = 0; i < m;) {
+    const int32_t mc = m - i < c->fb.cap ? m - i : c->fb.cap;
+    const bool batch = images_pay(c, mc);
+    const int32_t mq = batch ? mc : 1;
+    const double *bp = Bparent + (int64_t)i * p, *w = c->d_w;
+    int8_t *dst = batch ? c->bstatus : c->d_status;
+    PR_TRY(hipMemcpyAsync(dst, sts.data() + (size_t)i * p, (size_t)mq * p, hipMemcpyHostToDevice, s));
+    PR_TRY(hipMemcpyAsync(c->fb.sc, scs.data() + i, sizeof(FeatScalars) * mq, hipMemcpyHostToDevice, s));
+    if (batch) {
+      rc = grad_images(c, mq, bp);
+      w = c->mWb;
+    } else {
+      rc = grad_image(c, bp);
+    }
     if (rc != PR_OK) return rc;
-    PR_TRY(launch_features(bp, c->d_w, c->d_status, p, c->mnz, c->mfs,
-                           feat_scalars(&nodes[i], sts[(size_t)i], kbars[(size_t)i]),
-                           Bchild ? Bchild + (int64_t)i * p : nullptr, F + (int64_t)i * p * 8,
-                           T ? T + (int64_t)i * p : nullptr, s));
+    PR_TRY(launch_features(bp, w, dst, p, mq, c->fb, Bchild ? Bchild + (int64_t)i * p : nullptr,
+                           F + (int64_t)i * p * 8, T ? T + (int64_t)i * p : nullptr, s));
+    i += mq;
   }
   PR_TRY(hipStreamSynchronize(s));
   return PR_OK;
@@ -1907,8 +1957,9 @@ static int stage_batch_nodes(pr_ctx *c, const pr_node *nodes, const std::vector<
 // proposals in one launch and their certificates from a third pass.
 static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const float *params, const double *Bparent,
                               double *B0, const std::vector<std::vector<int8_t>> &sts,
-                              const std::vector<int32_t> &kbars, const std::vector<int64_t> &pbars,
-                              const std::vector<char> &infeas, int32_t *choice, double *gaps) {
+                              const std::vector<int32_t> &kbars, const std::vector<int64_t> &n1s,
+                              const std::vector<int64_t> &pbars, const std::vector<char> &infeas, int32_t *choice,
+                              double *gaps) {
   const int64_t p = c->P.p;
   hipStream_t s = c->stream;
   std::vector<int32_t> slot_of;
@@ -1928,7 +1979,8 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
   }
   const int NrMax = nr_of(c->max_batch);
   if (!c->mVb) {
-    bool ok = dalloc(&c->mVb, (size_t)NrMax * p) == hipSuccess && dalloc(&c->mWb, (size_t)NrMax * p) == hipSuccess;
+    bool ok = dalloc(&c->mVb, (size_t)NrMax * p) == hipSuccess;
+    ok = ok && (c->mWb || dalloc(&c->mWb, (size_t)NrMax * p) == hipSuccess);
     ok = ok && dalloc(&c->mFb, (size_t)NrMax * p * 8) == hipSuccess && dalloc(&c->moutb, (size_t)NrMax * p) == hipSuccess;
     ok = ok && dalloc(&c->mPb, (size_t)NrMax * p) == hipSuccess;
     if (!ok) return PR_ENOMEM;
@@ -1938,6 +1990,7 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
   int rc = stage_batch_nodes(c, nodes, slot_of, sts, kbars, pbars, o, Bparent);  // parents -> bxbest
   if (rc != PR_OK) return rc;
   std::vector<double> lbP, ubP, lbA, ubA, lbN, ubN;
+  std::vector<FeatScalars> fsc((size_t)mb);
   int32_t kst = 1;
   rc = certify_batch(c, mb, lbP, ubP, &kst);  // leaves X^T zeta (or X^T r) of every parent in CT's split planes
   if (rc != PR_OK) return rc;
@@ -1953,11 +2006,11 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
   PR_TRY(hipMemcpyAsync(c->mPb, c->bxbest, sizeof(double) * mb * p, hipMemcpyDeviceToDevice, s));
   if (params) {
     for (int32_t q = 0; q < mb; q++) {
-      const int32_t i = slot_of[(size_t)q];
-      PR_TRY(launch_features(c->mVb + (int64_t)q * p, c->mWb + (int64_t)q * p, c->bstatus + (int64_t)q * p, p,
-                             c->mnz, c->mfs, feat_scalars(&nodes[i], sts[(size_t)i], kbars[(size_t)i]), nullptr,
-                             c->mFb + (int64_t)q * p * 8, nullptr, s));
+      const size_t i = (size_t)slot_of[(size_t)q];
+      fsc[(size_t)q] = feat_scalars(&nodes[i], p, n1s[i], pbars[i], kbars[i]);
     }
+    PR_TRY(hipMemcpyAsync(c->fb.sc, fsc.data(), sizeof(FeatScalars) * mb, hipMemcpyHostToDevice, s));
+    PR_TRY(launch_features(c->mVb, c->mWb, c->bstatus, p, mb, c->fb, nullptr, c->mFb, nullptr, s));
     PR_TRY(launch_mlp_forward(params, c->mFb, (int64_t)mb * p, c->moutb, s));
     PR_TRY(launch_mlp_propose(c->mVb, c->moutb, (int64_t)mb * p, c->mVb, s));
     PR_TRY(launch_prox_batch(c->d_bprm, c->mVb, c->bxbest, c->cert_a, p, mb, 1.0 / L, s));
@@ -1995,12 +2048,11 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
   const int64_t p = c->P.p;
   std::vector<std::vector<int8_t>> sts((size_t)m);
   std::vector<int32_t> kbars((size_t)m);
-  std::vector<int64_t> pbars((size_t)m);
+  std::vector<int64_t> pbars((size_t)m), n1s((size_t)m);
   std::vector<char> infeas((size_t)m);
   for (int32_t i = 0; i < m; i++) {
-    int64_t n1;
     bool inf;
-    int rc = build_status(&nodes[i], p, sts[(size_t)i], n1, pbars[(size_t)i], kbars[(size_t)i], inf);
+    int rc = build_status(&nodes[i], p, sts[(size_t)i], n1s[(size_t)i], pbars[(size_t)i], kbars[(size_t)i], inf);
     if (rc != PR_OK) return rc;
     infeas[(size_t)i] = inf;
   }
@@ -2008,7 +2060,7 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
   if (rc != PR_OK) return rc;
   if (m == 0) return PR_OK;
   if (c->batch_ok && m <= c->max_batch)
-    return warm_start_batched(c, nodes, m, params, Bparent, B0, sts, kbars, pbars, infeas, choice, gaps);
+    return warm_start_batched(c, nodes, m, params, Bparent, B0, sts, kbars, n1s, pbars, infeas, choice, gaps);
   hipStream_t s = c->stream;
   const double L = 1.01 * curvature(c->P.loss) * c->norm2;
   for (int32_t i = 0; i < m; i++) {
@@ -2023,9 +2075,10 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
       gp = ub - lb;
       const double rho = 2.0 * nodes[i].lambda2 / L;
       if (params) {  // the network's proposal first: d_w still holds X^T zeta at the parent
-        PR_TRY(launch_features(bp, c->d_w, c->d_status, p, c->mnz, c->mfs,
-                               feat_scalars(&nodes[i], sts[(size_t)i], kbars[(size_t)i]), nullptr, c->mF, nullptr,
-                               s));
+        const FeatScalars sc =
+            feat_scalars(&nodes[i], p, n1s[(size_t)i], pbars[(size_t)i], kbars[(size_t)i]);
+        PR_TRY(hipMemcpyAsync(c->fb.sc, &sc, sizeof(sc), hipMemcpyHostToDevice, s));
+        PR_TRY(launch_features(bp, c->d_w, c->d_status, p, 1, c->fb, nullptr, c->mF, nullptr, s));
         PR_TRY(launch_mlp_forward(params, c->mF, p, c->mout, s));
         PR_TRY(launch_mlp_propose(bp, c->mout, p, c->mvhat, s));
         PR_TRY(ctx_prox(c, nodes[i], kbars[(size_t)i], rho, c->mvhat, c->mvhat));

@@ -316,9 +316,19 @@ hipError_t launch_mlp_grad(const float *P, const uint16_t *F, const float *T, in
                            float *grad, hipStream_t s);
 hipError_t launch_mlp_adam(float *P, const float *g, float *m1, float *m2, float lr, float beta1, float beta2,
                            float eps, float c1, float c2, hipStream_t s);
-hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, double *nzv,
-                           double *fs, FeatScalars sc, const double *beta_child, uint16_t *F, float *T,
-                           hipStream_t s);
+// Scratch of the feature kernels for up to `cap` nodes: nonzero magnitudes and
+// their coordinates, ranks [cap][p], {max |w|, nnz} and the scalars per node.
+struct FeatBufs {
+  double *nzv;
+  int32_t *nzi, *rank;
+  double *fs;
+  FeatScalars *sc;
+  int cap;
+};
+// feature rows (and with beta_child the targets) of m <= fb.cap nodes, vectors
+// node-major [m][p], fb.sc filled
+hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, int m,
+                           const FeatBufs &fb, const double *beta_child, uint16_t *F, float *T, hipStream_t s);
 hipError_t launch_mlp_propose(const double *beta, const float *out, int64_t p, double *vhat, hipStream_t s);
 hipError_t launch_zbest_final(const NodeState *S, const ProbBufs &B, int32_t loss, int64_t n,
                               hipStream_t s);
