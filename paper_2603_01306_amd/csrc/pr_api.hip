@@ -41,12 +41,17 @@ struct pr_ctx {
   Problem P{};
   double norm2 = 0.0;
   int32_t max_batch = 1;
+  // what a solve uploads, in one copy: NodeParams | packed status | status (the
+  // three pointers into it) from the pinned h_stage
+  char *d_stage = nullptr, *h_stage = nullptr;
+  char *h_pinned = nullptr;  // h_stage, h_state and h_scal
+  size_t stage_stp = 0, stage_st = 0;  // offsets of the two statuses
   NodeParams *d_prm = nullptr;
   NodeState *d_state = nullptr;
   NodeState *h_state = nullptr;  // pinned, 2 slots
   int8_t *d_status = nullptr;
   uint32_t *d_stp = nullptr;     // the status packed 2 bits per entry (NodeParams::stp)
-  std::vector<uint32_t> h_stp;
+  size_t stp_words = 0;
   NodeBufs nb{};
   ProbBufs B{};
   XBuf xb{};                     // exchange area of the steps over several workgroups
@@ -55,7 +60,8 @@ struct pr_ctx {
   double *d_u = nullptr;         // n
   double *d_v = nullptr;         // p
   double *d_w = nullptr;         // p
-  double *d_scal = nullptr;      // small scalars
+  double *d_scal = nullptr;      // small scalars, and the pinned copy the host reads
+  double *h_scal = nullptr;
   double *d_lam = nullptr;       // Lanczos coefficients: alpha [kLanczosMax], beta [kLanczosMax]
   double *d_vprev = nullptr;     // p: previous Lanczos vector
   double *d_regscratch = nullptr;  // 3p
@@ -152,10 +158,10 @@ struct pr_ctx {
 namespace {
 
 // Status in the packed layout of NodeParams::stp (3 = beyond p).
-void pack_status(const std::vector<int8_t> &st, std::vector<uint32_t> &w) {
+void pack_status(const std::vector<int8_t> &st, uint32_t *w, size_t words) {
   const int64_t p = (int64_t)st.size();
   const int64_t T = kNodeThreads;
-  for (size_t k = 0; k < w.size(); k++) {
+  for (size_t k = 0; k < words; k++) {
     const int64_t q = (int64_t)k / T, t = (int64_t)k % T;
     uint32_t v = 0u;
     for (int i = 0; i < 16; i++) {
@@ -197,15 +203,14 @@ void free_ctx(pr_ctx *c) {
     if (c->tev[i]) (void)hipEventDestroy(c->tev[i]);
   }
   if (c->cap) (void)hipStreamDestroy(c->cap);
-  void *bufs[] = {c->d_prm, c->d_state, c->d_status, c->d_stp, c->nb.x0, c->nb.x1, c->nb.xbest, c->nb.hprev, c->nb.vbuf,
+  void *bufs[] = {c->d_stage, c->d_state, c->nb.x0, c->nb.x1, c->nb.xbest, c->nb.hprev, c->nb.vbuf,
                   c->nb.abuf, c->nb.sidx, c->nb.sval, c->nb.ybt, c->nb.gbt, c->B.uy, c->B.dsum, c->B.r, c->B.gm,
                   c->B.ucur, c->B.uprev,
                   c->B.zbest, c->B.h1, c->B.h2, c->B.part, c->B.rbsum, c->iota,
-                  c->d_np, c->d_u, c->d_v, c->d_w, c->d_scal, c->d_lam, c->d_vprev, c->d_regscratch, c->xb.slots,
-                  c->xb.round};
+                  c->d_np, c->d_u, c->d_v, c->d_w, c->d_scal, c->d_lam, c->d_vprev, c->d_regscratch, c->xb.slots};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
-  if (c->h_state) (void)hipHostFree(c->h_state);
+  if (c->h_pinned) (void)hipHostFree(c->h_pinned);
   delete c;
 }
 
@@ -306,6 +311,7 @@ int capture_units(pr_ctx *c, int32_t units, hipGraphExec_t *out) {
   PR_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   for (int i = 0; i < units && e == hipSuccess; i++) e = enqueue_unit(c, c->cap, i);
+  if (e == hipSuccess) e = launch_publish(c->d_state, c->h_state, c->cap);
   hipError_t e2 = hipStreamEndCapture(c->cap, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
@@ -342,24 +348,28 @@ int ensure_graph(pr_ctx *c, int32_t units) {
 }
 
 // Launch a captured iteration graph of `units` iterations until the node state
-// reports done or `max_units` iterations have been launched.  Each launch is
-// followed by a copy of the node state into its own pinned slot and an event;
-// at most two launches are in flight.  Iterations launched after the stop
-// still cost their launches, so the host predicts the stop from the rate at
-// which the relative gap fell over the last `units` or more evaluations: no
-// further launch is queued behind launches that are predicted to reach it, and
-// the last iterations run as launches of the short graph `gs` (`sunits`
-// iterations) when there is one.  The prediction only decides how much is
-// queued; the iterates do not depend on it.
-hipError_t run_graph(pr_ctx *c, hipGraphExec_t g, int32_t units, int64_t max_units, double tol,
+// reports done or `max_units` iterations have been launched; *last receives the
+// state reached.  Each launch ends by writing the node state into its own pinned
+// slot and is followed by an event; at most two launches are in flight, and on
+// return one that found the node done may still be.  Iterations launched after
+// the stop still cost their launches, so the short graph `gs` (`sunits`
+// iterations), when there is one, runs a solve's first evaluations, among
+// which many warm-started nodes stop (a branch-and-bound node from the Gram
+// matrix, 2048 x 2048, takes 6 to 28 evaluations and ran 64; with 0, 8, 16, 24
+// and 32 of them in short graphs the tree takes 52, 50, 41.5, 37.1 and 37.1 ms,
+// and the 500 x 200 root 2.82 ms up to 24, 2.87 with 32), and its last ones:
+// from the rate at which the relative gap fell over the last
+// `units` or more evaluations the host predicts the stop, and queues no launch
+// behind launches that are predicted to reach it.  Neither changes the
+// iterates.
+hipError_t run_graph(pr_ctx *c, hipGraphExec_t g, int32_t units, int64_t max_units, const pr_opts &o, NodeState *last,
                      hipGraphExec_t gs = nullptr, int32_t sunits = 0) {
+  const double tol = o.rel_gap_tol;
   int slot = 0, head = 0, inflight = 0;
   int32_t qunits[2] = {0, 0};
   int64_t issued = 0;
   auto issue = [&](bool small) -> hipError_t {
     hipError_t e = hipGraphLaunch(small ? gs : g, c->stream);
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(&c->h_state[slot], c->d_state, sizeof(NodeState), hipMemcpyDeviceToHost, c->stream);
     if (e != hipSuccess) return e;
     e = hipEventRecord(c->ev[slot], c->stream);
     if (e != hipSuccess) return e;
@@ -369,10 +379,11 @@ hipError_t run_graph(pr_ctx *c, hipGraphExec_t g, int32_t units, int64_t max_uni
     inflight++;
     return hipSuccess;
   };
-  hipError_t e = issue(false);
+  const int64_t early = gs ? 3 * sunits : 0;  // evaluations of the short graph at the start
+  hipError_t e = issue(early > 0);
   if (e != hipSuccess) return e;
   if (issued < max_units) {
-    e = issue(false);
+    e = issue(early > 0);
     if (e != hipSuccess) return e;
   }
   // (evaluations, relative gap) at each observation with a finite gap
@@ -381,32 +392,33 @@ hipError_t run_graph(pr_ctx *c, hipGraphExec_t g, int32_t units, int64_t max_uni
     e = hipEventSynchronize(c->ev[head]);
     if (e != hipSuccess) return e;
     const NodeState h = c->h_state[head];
+    *last = h;
     head ^= 1;
     inflight--;
     if (h.done) break;
-    // evaluations predicted before the stop (infinite while the gap has not
-    // fallen over the window)
+    // evaluations predicted before the stop: those the iteration limit leaves,
+    // or fewer where the gap has fallen over the window
     const int64_t ev = (int64_t)h.iter + h.trials;
-    double rem = INFINITY;
+    double rem = (double)((int64_t)o.max_iter + 1 - h.iter);
     if (isfinite(h.rel_gap) && h.rel_gap > 0.0) {
       const std::pair<int64_t, double> *base = nullptr;
       for (const auto &o : hist)
         if (ev - o.first >= units || !base) base = &o;
       if (base && ev > base->first && h.rel_gap < base->second && tol > 0.0)
-        rem = log(h.rel_gap / tol) * (double)(ev - base->first) / log(base->second / h.rel_gap);
+        rem = fmin(rem, log(h.rel_gap / tol) * (double)(ev - base->first) / log(base->second / h.rel_gap));
       hist.emplace_back(ev, h.rel_gap);
     }
     double queued = inflight ? (double)qunits[head] : 0.0;
     while (inflight < 2 && issued < max_units) {
       const double need = rem - queued;
       if (inflight > 0 && need <= 0.0) break;
-      const bool small = gs && need < (double)units;
+      const bool small = gs && (need < (double)units || issued < early);
       e = issue(small);
       if (e != hipSuccess) return e;
       queued += small ? sunits : units;
     }
   }
-  return hipStreamSynchronize(c->stream);
+  return hipSuccess;
 }
 
 // Buffers of the iteration variants, allocated on first use.
@@ -457,6 +469,7 @@ int ensure_variant_graph(pr_ctx *c, int kind, const double *key, int32_t units) 
   PR_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   for (int i = 0; i < units && e == hipSuccess; i++) e = enqueue_variant_unit(c, c->cap, kind, key);
+  if (e == hipSuccess) e = launch_publish(c->d_state, c->h_state, c->cap);
   hipError_t e2 = hipStreamEndCapture(c->cap, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
@@ -716,7 +729,7 @@ int alloc_batch(pr_ctx *c) {
   ok = ok && dalloc(&c->bxbest, (size_t)cap * p) == hipSuccess && dalloc(&c->bhprev, (size_t)cap * p) == hipSuccess;
   ok = ok && dalloc(&c->bsval, (size_t)cap * p) == hipSuccess && dalloc(&c->bsidx, (size_t)cap * p) == hipSuccess;
   ok = ok && dalloc(&c->bstatus, (size_t)cap * p) == hipSuccess;
-  ok = ok && dalloc(&c->bstp, (size_t)cap * c->h_stp.size()) == hipSuccess;
+  ok = ok && dalloc(&c->bstp, (size_t)cap * c->stp_words) == hipSuccess;
   ok = ok && dalloc(&c->d_bprm, cap) == hipSuccess && dalloc(&c->d_bstate, cap) == hipSuccess;
   ok = ok && dalloc(&c->d_active, 2) == hipSuccess;
   // d_split: {rows iterating, forward split, second split, compacted split, tile counters x2,
@@ -827,7 +840,7 @@ BatchBufs batch_bufs(pr_ctx *c, int32_t m) {
   bb.gap_factor = 0.99;
   bb.p = c->P.p;
   bb.stp = c->bstp;
-  bb.stpw = (int64_t)c->h_stp.size();
+  bb.stpw = (int64_t)c->stp_words;
   bb.gb = c->gram ? c->gb : nullptr;
   bb.gyy = c->gyy;
   bb.ybt = c->bybt;
@@ -1001,6 +1014,50 @@ int batch_products(pr_ctx *c, int32_t m, int32_t *kst_out) {
   return PR_OK;
 }
 
+// The prox and the terms g_N(beta), g_N*(ascale alpha) of the feasible node whose
+// status is in c->d_status, on the context's stream.
+hipError_t ctx_prox(pr_ctx *c, const pr_node &node, int32_t kbar, double rho, const double *v, double *out) {
+  if (c->P.p <= reg_x_max())
+    return launch_prox_x(v, out, c->P.p, rho, node.k, node.M, c->d_status, nullptr, c->xb, c->stream);
+  return launch_prox(v, out, c->P.p, rho, kbar, node.M, c->d_status, c->d_regscratch, nullptr, c->stream);
+}
+hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const double *beta, const double *alpha,
+                           double ascale, double *out2) {
+  if (c->P.p <= reg_x_max())
+    return launch_regularizer_x(beta, alpha, ascale, c->P.p, node.k, node.M, c->d_status, out2, nullptr, c->xb,
+                                c->stream);
+  if (alpha) {
+    const hipError_t e = launch_scale_copy(alpha, c->d_v, ascale, c->P.p, c->stream);
+    if (e != hipSuccess) return e;
+    alpha = c->d_v;
+  }
+  return launch_regularizer(beta, alpha, c->P.p, kbar, node.M, c->d_status, c->d_regscratch, out2, c->stream);
+}
+
+// The terms of Psi(zeta) and Phi(beta) of the node whose status is in
+// c->d_status, over the stored X: scal = {F(X beta), -F*(-zeta), g_N(beta),
+// g_N*(X^T zeta / (2 lambda2))}.  Without zeta it is induced from beta and left
+// in B.gm; w = X^T zeta is left in d_w.
+int enqueue_dual(pr_ctx *c, const pr_node &node, int32_t kbar, const double *zeta, const double *beta, double *scal) {
+  const int64_t n = c->P.n;
+  hipStream_t s = c->stream;
+  const double *z = zeta;
+  if (beta) {
+    if (launch_spfwd(c->P, c->B, c->iota, beta, c->d_np, kSpPlain, nullptr, c->d_u, s) != hipSuccess)
+      return PR_EDEVICE;
+    PR_TRY(launch_loss_terms(c->P.loss, c->d_u, c->P.y, n, c->B.gm, scal, s));
+    if (!zeta) z = c->B.gm;
+  }
+  if (zeta) PR_TRY(launch_zeta_terms(c->P.loss, zeta, c->P.y, n, scal, s));
+  PR_TRY(launch_gemv_t(c->P, z, nullptr, c->d_w, nullptr, nullptr, s));
+  PR_TRY(ctx_regularizer(c, node, kbar, beta, c->d_w, 0.5 / node.lambda2, scal + 2));
+  return PR_OK;
+}
+void dual_values(const double *scal, double lam2, double *lb, double *ub) {
+  *lb = scal[1] - 2.0 * lam2 * scal[3];
+  *ub = scal[0] + 2.0 * lam2 * scal[2];
+}
+
 // FP64 values of the m batched nodes at their stopping iterates (rows of
 // bxbest), over the stored X, for every node at once: the forward product
 // X_it X^T and the transposed product R X on the batch's FP64-accumulated
@@ -1105,11 +1162,20 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   c->B.nfin = spfwd_final_blocks(n);
   bool ok = hipGetDevice(&c->device) == hipSuccess;
   ok = ok && hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) == hipSuccess;
-  ok = ok && dalloc(&c->d_prm, 1) == hipSuccess && dalloc(&c->d_state, 1) == hipSuccess;
-  ok = ok && hipHostMalloc((void **)&c->h_state, 2 * sizeof(NodeState), hipHostMallocDefault) == hipSuccess;
-  ok = ok && dalloc(&c->d_status, p) == hipSuccess;
-  c->h_stp.assign((size_t)kNodeThreads * (size_t)((p + 16 * kNodeThreads - 1) / (16 * kNodeThreads)), 0u);
-  ok = ok && dalloc(&c->d_stp, c->h_stp.size()) == hipSuccess;
+  c->stp_words = (size_t)kNodeThreads * (size_t)((p + 16 * kNodeThreads - 1) / (16 * kNodeThreads));
+  c->stage_stp = (sizeof(NodeParams) + 255) / 256 * 256;
+  c->stage_st = c->stage_stp + sizeof(uint32_t) * c->stp_words;
+  ok = ok && dalloc(&c->d_stage, c->stage_st + (size_t)p) == hipSuccess && dalloc(&c->d_state, 1) == hipSuccess;
+  const size_t pin_state = (c->stage_st + (size_t)p + 255) / 256 * 256, pin_scal = pin_state + 2 * sizeof(NodeState);
+  ok = ok && hipHostMalloc((void **)&c->h_pinned, pin_scal + 8 * sizeof(double), hipHostMallocDefault) == hipSuccess;
+  if (ok) {
+    c->h_stage = c->h_pinned;
+    c->h_state = reinterpret_cast<NodeState *>(c->h_pinned + pin_state);
+    c->h_scal = reinterpret_cast<double *>(c->h_pinned + pin_scal);
+    c->d_prm = reinterpret_cast<NodeParams *>(c->d_stage);
+    c->d_stp = reinterpret_cast<uint32_t *>(c->d_stage + c->stage_stp);
+    c->d_status = reinterpret_cast<int8_t *>(c->d_stage + c->stage_st);
+  }
   ok = ok && dalloc(&c->nb.x0, p) == hipSuccess && dalloc(&c->nb.x1, p) == hipSuccess;
   ok = ok && dalloc(&c->nb.xbest, p) == hipSuccess && dalloc(&c->nb.xlb, p) == hipSuccess;
   ok = ok && dalloc(&c->nb.hprev, p) == hipSuccess && dalloc(&c->nb.vbuf, p) == hipSuccess;
@@ -1128,7 +1194,8 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && dalloc(&c->d_w, p) == hipSuccess && dalloc(&c->d_scal, 8) == hipSuccess;
   ok = ok && dalloc(&c->d_lam, 2 * kLanczosMax) == hipSuccess && dalloc(&c->d_vprev, p) == hipSuccess;
   ok = ok && dalloc(&c->d_regscratch, 3 * (size_t)p) == hipSuccess;
-  ok = ok && dalloc(&c->xb.slots, kXwgWords) == hipSuccess && dalloc(&c->xb.round, 1) == hipSuccess;
+  ok = ok && dalloc(&c->xb.slots, kXwgWords + 1) == hipSuccess;
+  if (ok) c->xb.round = reinterpret_cast<uint32_t *>(c->xb.slots + kXwgWords);
   ok = ok && hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreate(&c->tev[0]) == hipSuccess && hipEventCreate(&c->tev[1]) == hipSuccess;
@@ -1142,8 +1209,7 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && hipMemsetAsync(c->B.r, 0, sizeof(double) * n, c->stream) == hipSuccess;
   ok = ok && hipMemsetAsync(c->B.gm, 0, sizeof(double) * n, c->stream) == hipSuccess;
   ok = ok && hipMemsetAsync(c->B.uy, 0, sizeof(double) * n, c->stream) == hipSuccess;
-  ok = ok && hipMemsetAsync(c->xb.slots, 0, sizeof(uint64_t) * kXwgWords, c->stream) == hipSuccess;
-  ok = ok && hipMemsetAsync(c->xb.round, 0, sizeof(uint32_t), c->stream) == hipSuccess;
+  ok = ok && hipMemsetAsync(c->xb.slots, 0, sizeof(uint64_t) * (kXwgWords + 1), c->stream) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->d_np, &pp, sizeof(int32_t), hipMemcpyHostToDevice, c->stream) == hipSuccess;
   ok = ok && launch_iota(c->iota, p, c->stream) == hipSuccess;
   ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
@@ -1194,16 +1260,22 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
 // iterate with the best Psi and of the iterate with the best Phi, and Phi at
 // the latter.  A decision (converged / prune / branch) these values do not
 // confirm is redone on the matrix-vector path from the best iterate.
-static int gram_certify(pr_ctx *c, const pr_node *node, const pr_opts *opts, const NodeState &hs, double *beta_out,
-                        double *zeta_out, pr_result *out) {
+static int gram_certify(pr_ctx *c, const pr_node *node, int32_t kbar, const pr_opts *opts, const NodeState &hs,
+                        double *beta_out, double *zeta_out, pr_result *out) {
   const int64_t n = c->P.n, p = c->P.p;
   hipStream_t s = c->stream;
-  double lb1 = -INFINITY, ub1 = INFINITY, lb2 = -INFINITY, ub2 = INFINITY;
-  int rc = pr_dual_bound(c, node, nullptr, c->nb.xlb, &lb1, &ub1);  // leaves zeta(x_lb) in B.gm
+  // the node's status is on the device; the two iterates are often the same one
+  const bool same = hs.lb_it == hs.ub_it;
+  int rc = enqueue_dual(c, *node, kbar, nullptr, c->nb.xlb, c->d_scal);  // leaves zeta(x_lb) in B.gm
   if (rc != PR_OK) return rc;
   if (zeta_out) PR_TRY(hipMemcpyAsync(zeta_out, c->B.gm, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  rc = pr_dual_bound(c, node, nullptr, c->nb.xbest, &lb2, &ub2);
+  if (!same) rc = enqueue_dual(c, *node, kbar, nullptr, c->nb.xbest, c->d_scal + 4);
   if (rc != PR_OK) return rc;
+  PR_TRY(hipMemcpyAsync(c->h_scal, c->d_scal, 8 * sizeof(double), hipMemcpyDeviceToHost, s));
+  PR_TRY(hipStreamSynchronize(s));
+  double lb1, ub1, lb2, ub2;
+  dual_values(c->h_scal, node->lambda2, &lb1, &ub1);
+  dual_values(c->h_scal + (same ? 0 : 4), node->lambda2, &lb2, &ub2);
   if (zeta_out && lb2 > lb1) PR_TRY(hipMemcpyAsync(zeta_out, c->B.gm, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
   const double lb = lb2 > lb1 ? lb2 : lb1, ub = ub2;
   const double rel = (ub - lb) / fmax(fabs(ub), 1e-300);
@@ -1253,12 +1325,11 @@ static int solve_acfgm(pr_ctx *c, const pr_opts *opts, double L, const double *b
   const double key[3] = {opts->acfgm_b, opts->acfgm_c, opts->method == kAcfgmGap ? 1.0 : 0.0};
   rc = ensure_variant_graph(c, 0, key, opts->check_every);
   if (rc != PR_OK) return rc;
-  PR_TRY(run_graph(c, c->vgexec, c->vgraph_units,
-                   ((int64_t)opts->max_iter / opts->check_every + 3) * c->vgraph_units, opts->rel_gap_tol));
-  PR_TRY(launch_zbest_final(c->d_state, c->B, c->P.loss, n, c->stream));
   NodeState hs;
+  PR_TRY(run_graph(c, c->vgexec, c->vgraph_units,
+                   ((int64_t)opts->max_iter / opts->check_every + 3) * c->vgraph_units, *opts, &hs));
+  PR_TRY(launch_zbest_final(c->d_state, c->B, c->P.loss, n, c->stream));
   AcState ha;
-  PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
   PR_TRY(hipMemcpyAsync(&ha, c->d_ac, sizeof(ha), hipMemcpyDeviceToHost, c->stream));
   if (beta_out)
     PR_TRY(hipMemcpyAsync(beta_out, c->nb.xbest, sizeof(double) * p, hipMemcpyDeviceToDevice, c->stream));
@@ -1306,12 +1377,11 @@ int pr_lasso_solve(pr_ctx *c, const pr_lasso *lp, const pr_opts *opts_in, const 
   const double key[3] = {lp->lam, 0.0, 0.0};
   rc = ensure_variant_graph(c, 1 + lp->kind, key, opts.check_every);
   if (rc != PR_OK) return rc;
-  PR_TRY(run_graph(c, c->vgexec, c->vgraph_units,
-                   ((int64_t)opts.max_iter / opts.check_every + 3) * c->vgraph_units, opts.rel_gap_tol));
-  PR_TRY(launch_zbest_final(c->d_state, c->B, kLsq, n, c->stream));
   NodeState hs;
+  PR_TRY(run_graph(c, c->vgexec, c->vgraph_units,
+                   ((int64_t)opts.max_iter / opts.check_every + 3) * c->vgraph_units, opts, &hs));
+  PR_TRY(launch_zbest_final(c->d_state, c->B, kLsq, n, c->stream));
   LassoState hl;
-  PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
   PR_TRY(hipMemcpyAsync(&hl, c->d_lx, sizeof(hl), hipMemcpyDeviceToHost, c->stream));
   PR_TRY(hipStreamSynchronize(c->stream));
   if (beta_out)
@@ -1432,11 +1502,10 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
     prm.ls_c = opts.acfgm_c;
     L_init = prm.L0;
   }
-  pack_status(st, c->h_stp);
-  PR_TRY(hipMemcpyAsync(c->d_status, st.data(), (size_t)p, hipMemcpyHostToDevice, c->stream));
-  PR_TRY(hipMemcpyAsync(c->d_stp, c->h_stp.data(), sizeof(uint32_t) * c->h_stp.size(), hipMemcpyHostToDevice,
-                        c->stream));
-  PR_TRY(hipMemcpyAsync(c->d_prm, &prm, sizeof(prm), hipMemcpyHostToDevice, c->stream));
+  memcpy(c->h_stage, &prm, sizeof(prm));
+  pack_status(st, reinterpret_cast<uint32_t *>(c->h_stage + c->stage_stp), c->stp_words);
+  memcpy(c->h_stage + c->stage_st, st.data(), (size_t)p);
+  PR_TRY(hipMemcpyAsync(c->d_stage, c->h_stage, c->stage_st + (size_t)p, hipMemcpyHostToDevice, c->stream));
   if (opts.method == kAcfgmGap || opts.method == kAcfgm)
     return solve_acfgm(c, &opts, L, beta0, beta_out, zeta_out, out);
   if (const XShape g = node_xshape(p); g.wgs)
@@ -1448,19 +1517,15 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
   if (rc != PR_OK) return rc;
   // backtracking: rejected trials take evaluations beyond the iteration budget
   const int64_t launches = (int64_t)opts.max_iter / opts.check_every + 3;
-  PR_TRY(run_graph(c, c->gexec, c->graph_units, (is_bt(opts.method) ? 2 * launches : launches) * c->graph_units,
-                   opts.rel_gap_tol, c->gtail, kTailUnits));
   NodeState hs;
-  if (c->gram) {
-    PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
+  PR_TRY(run_graph(c, c->gexec, c->graph_units, (is_bt(opts.method) ? 2 * launches : launches) * c->graph_units,
+                   opts, &hs, c->gtail, kTailUnits));
+  if (hs.status == kFailed) {
     PR_TRY(hipStreamSynchronize(c->stream));
-    if (hs.status == kFailed) return PR_EDEVICE;
-    return gram_certify(c, node, &opts, hs, beta_out, zeta_out, out);
+    return PR_EDEVICE;
   }
+  if (c->gram) return gram_certify(c, node, kbar, &opts, hs, beta_out, zeta_out, out);
   PR_TRY(launch_zbest_final(c->d_state, c->B, c->P.loss, n, c->stream));
-  PR_TRY(hipMemcpyAsync(&hs, c->d_state, sizeof(hs), hipMemcpyDeviceToHost, c->stream));
-  PR_TRY(hipStreamSynchronize(c->stream));
-  if (hs.status == kFailed) return PR_EDEVICE;
   if (beta_out)
     PR_TRY(hipMemcpyAsync(beta_out, c->nb.xbest, sizeof(double) * p, hipMemcpyDeviceToDevice, c->stream));
   if (zeta_out)
@@ -1562,7 +1627,7 @@ int pr_time_prox(void *stream, const double *v, int64_t p, double rho, int32_t k
                 : launch_prox(v, out, p, rho, (int32_t)kb, M, status, abuf, nullptr, s);
   };
   auto reg = [&] {
-    return wide ? launch_regularizer_x(out, nullptr, p, k, M, status, g2, nullptr, x.xb, s)
+    return wide ? launch_regularizer_x(out, nullptr, 1.0, p, k, M, status, g2, nullptr, x.xb, s)
                 : launch_regularizer(out, nullptr, p, (int32_t)kb, M, status, abuf, g2, s);
   };
   hipError_t e = hipEventCreate(&e0);
@@ -1601,7 +1666,7 @@ int pr_regularizer(void *stream, const double *beta, const double *alpha, int64_
     XLease x;
     const int rc = x.take(s);
     if (rc != PR_OK) return rc;
-    PR_TRY(launch_regularizer_x(beta, alpha, p, k, M, status, x.res->v, &x.res->flag, x.xb, s));
+    PR_TRY(launch_regularizer_x(beta, alpha, 1.0, p, k, M, status, x.res->v, &x.res->flag, x.xb, s));
     PR_TRY(hipStreamSynchronize(s));
     const XResult r = *x.res;
     if (r.flag == 1) return PR_EINVAL;
@@ -1817,20 +1882,6 @@ FeatScalars feat_scalars(const pr_node *node, int64_t p, int64_t n1, int64_t pba
   sc.n1 = (int32_t)n1;
   sc.kbar = kbar;
   return sc;
-}
-
-// prox_{rho g_N} and g_N / g_N* of the feasible node whose status is in
-// c->d_status, on the context's stream.
-hipError_t ctx_prox(pr_ctx *c, const pr_node &node, int32_t kbar, double rho, const double *v, double *out) {
-  if (c->P.p <= reg_x_max())
-    return launch_prox_x(v, out, c->P.p, rho, node.k, node.M, c->d_status, nullptr, c->xb, c->stream);
-  return launch_prox(v, out, c->P.p, rho, kbar, node.M, c->d_status, c->d_regscratch, nullptr, c->stream);
-}
-hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const double *beta, const double *alpha,
-                           double *out2) {
-  if (c->P.p <= reg_x_max())
-    return launch_regularizer_x(beta, alpha, c->P.p, node.k, node.M, c->d_status, out2, nullptr, c->xb, c->stream);
-  return launch_regularizer(beta, alpha, c->P.p, kbar, node.M, c->d_status, c->d_regscratch, out2, c->stream);
 }
 
 // w = X^T zeta, zeta = -grad F(X beta), in c->d_w: an input of the features.
@@ -2113,7 +2164,7 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
 int pr_dual_bound(pr_ctx *c, const pr_node *node, const double *zeta, const double *beta,
                   double *lb_out, double *primal_out) {
   if (!c || !lb_out || (!zeta && !beta)) return PR_EINVAL;
-  const int64_t n = c->P.n, p = c->P.p;
+  const int64_t p = c->P.p;
   std::vector<int8_t> st;
   int64_t n1, pbar;
   int32_t kbar;
@@ -2127,26 +2178,13 @@ int pr_dual_bound(pr_ctx *c, const pr_node *node, const double *zeta, const doub
   }
   hipStream_t s = c->stream;
   PR_TRY(hipMemcpyAsync(c->d_status, st.data(), (size_t)p, hipMemcpyHostToDevice, s));
-  const double lam2 = node->lambda2;
-  double *scal = c->d_scal;  // [0] F(X beta), [1] -F*(-zeta), [2] g(beta), [3] g*(w)
-  const double *z = zeta;
-  if (beta) {
-    if (launch_spfwd(c->P, c->B, c->iota, beta, c->d_np, kSpPlain, nullptr, c->d_u, s) != hipSuccess)
-      return PR_EDEVICE;
-    // zeta induced from beta goes to B.zbest's twin: reuse B.gm as scratch
-    PR_TRY(launch_loss_terms(c->P.loss, c->d_u, c->P.y, n, c->B.gm, scal, s));
-    if (!zeta) z = c->B.gm;
-    PR_TRY(ctx_regularizer(c, *node, kbar, beta, nullptr, scal + 2));
-  }
-  if (zeta) PR_TRY(launch_zeta_terms(c->P.loss, zeta, c->P.y, n, scal, s));
-  PR_TRY(launch_gemv_t(c->P, z, nullptr, c->d_w, nullptr, nullptr, s));
-  PR_TRY(launch_scale_copy(c->d_w, c->d_v, 0.5 / lam2, p, s));
-  PR_TRY(ctx_regularizer(c, *node, kbar, nullptr, c->d_v, scal + 2));
-  double hs[4];
-  PR_TRY(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
+  rc = enqueue_dual(c, *node, kbar, zeta, beta, c->d_scal);
+  if (rc != PR_OK) return rc;
+  PR_TRY(hipMemcpyAsync(c->h_scal, c->d_scal, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
   PR_TRY(hipStreamSynchronize(s));
-  *lb_out = hs[1] - 2.0 * lam2 * hs[3];
-  if (primal_out) *primal_out = beta ? hs[0] + 2.0 * lam2 * hs[2] : NAN;
+  double ub;
+  dual_values(c->h_scal, node->lambda2, lb_out, &ub);
+  if (primal_out) *primal_out = beta ? ub : NAN;
   return PR_OK;
 }
 
@@ -2190,13 +2228,10 @@ static int stage_batch_nodes(pr_ctx *c, const pr_node *nodes, const std::vector<
                                   hipMemcpyDeviceToDevice, s));
   }
   {
-    const size_t W = c->h_stp.size();
+    const size_t W = c->stp_words;
     c->h_bstp.assign((size_t)mb * W, 0u);
-    std::vector<uint32_t> w(W);
-    for (int32_t q = 0; q < mb; q++) {
-      pack_status(sts[(size_t)slot_of[(size_t)q]], w);
-      std::copy(w.begin(), w.end(), c->h_bstp.begin() + (size_t)q * W);
-    }
+    for (int32_t q = 0; q < mb; q++)
+      pack_status(sts[(size_t)slot_of[(size_t)q]], c->h_bstp.data() + (size_t)q * W, W);
     PR_TRY(hipMemcpyAsync(c->bstp, c->h_bstp.data(), sizeof(uint32_t) * c->h_bstp.size(), hipMemcpyHostToDevice,
                           s));
   }

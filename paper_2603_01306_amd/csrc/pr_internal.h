@@ -79,6 +79,8 @@ struct NodeState {
   double tkw;      // relative half-width of the selection window around tk
   double dxy;      // backtracking: ||x_trial - y||^2 of the pending trial
   double bt_A;     // backtracking, least squares: (x_trial - y)^T h(y), h(y) = -grad f(y) / 2
+  int32_t lb_it, ub_it;  // Gram mode: iterations whose iterates attain lb and ub
+  int32_t launches;      // captured graphs run since the start (the host's slot of the state is its parity)
 };
 
 // Node-local vectors.
@@ -234,6 +236,9 @@ struct StepArgs {
   int32_t parity;
   int32_t bt;  // the backtracking variant of the step (pr_opts.method PR_FISTA_BT*)
 };
+// The state to the host at the end of a captured graph: slot launches & 1 of the
+// pinned pair `host`, then launches + 1.
+hipError_t launch_publish(NodeState *S, NodeState *host, hipStream_t s);
 hipError_t launch_node_step(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B,
                             int64_t p, hipStream_t s, const StepArgs *a = nullptr);
 // the node step and its start over several workgroups (pr_nodex.hip)
@@ -251,8 +256,8 @@ hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, 
 int64_t reg_x_max();
 hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
                          int32_t *flag, const XBuf &xb, hipStream_t s);
-hipError_t launch_regularizer_x(const double *beta, const double *alpha, int64_t p, int32_t k, double M,
-                                const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s);
+hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,
+                                double M, const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s);
 hipError_t launch_batch_init(const NodeParams *prm, NodeState *S, BatchBufs bb, const double *B0, double L,
                              int64_t p, hipStream_t s);
 hipError_t launch_batch_step(const NodeParams *prm, NodeState *S, BatchBufs bb, int64_t p, hipStream_t s);

@@ -233,6 +233,19 @@ __global__ __launch_bounds__(NT) void k_node_step(const NodeParams *__restrict__
   }
 }
 
+// One wave copies the node state to pinned host memory: as the last kernel of a
+// captured graph it costs one dispatch, where a copy queued behind the graph
+// cost the stream about 20 us more per launch.
+__global__ __launch_bounds__(64) void k_publish(NodeState *S, NodeState *host) {
+  static_assert(sizeof(NodeState) % 4 == 0, "copied word by word");
+  const int n = S->launches;
+  const uint32_t *src = reinterpret_cast<const uint32_t *>(S);
+  uint32_t *dst = reinterpret_cast<uint32_t *>(host + (n & 1));
+  for (unsigned i = threadIdx.x; i < sizeof(NodeState) / 4; i += 64) dst[i] = src[i];
+  __syncthreads();
+  if (threadIdx.x == 0) S->launches = n + 1;
+}
+
 __global__ void k_zbest_final(const NodeState *S, const double *__restrict__ r, double *zbest,
                               double scale, int64_t n) {
   if (!S->improved) return;
@@ -1408,6 +1421,8 @@ __global__ __launch_bounds__(NT) void k_node_step_r(const NodeParams *__restrict
       S->psi = psi;
       S->lb = lb;
       S->ub = ub;
+      if (improved) S->lb_it = it;
+      if (ub_improved) S->ub_it = it;
       S->rel_gap = rel;
       S->improved = improved;
       S->status = status;
@@ -2021,6 +2036,11 @@ hipError_t launch_batch_step(const NodeParams *prm, NodeState *S, BatchBufs bb, 
     default: return hipErrorInvalidValue;
   }
 #undef PR_BSTEP_CASE
+  return hipGetLastError();
+}
+
+hipError_t launch_publish(NodeState *S, NodeState *host, hipStream_t s) {
+  k_publish<<<1, 64, 0, s>>>(S, host);
   return hipGetLastError();
 }
 

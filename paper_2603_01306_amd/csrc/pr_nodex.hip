@@ -780,13 +780,13 @@ __global__ __launch_bounds__(NT) void k_prox_x(const double *v, double *out, int
   X.finish(xb);
 }
 
-// g_N(beta) (Algorithm 1, +inf off its domain) into out[0], g_N*(alpha) into
-// out[1] (each if its input is given); counts and *flag as in k_prox_x.
+// g_N(beta) (Algorithm 1, +inf off its domain) into out[0], g_N*(ascale alpha)
+// into out[1] (each if its input is given); counts and *flag as in k_prox_x.
 template <int EPT>
 __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__ beta,
-                                                      const double *__restrict__ alpha, int64_t p, int k, double M,
-                                                      const int8_t *__restrict__ st, double *out, int32_t *flag,
-                                                      XBuf xb) {
+                                                      const double *__restrict__ alpha, double ascale, int64_t p,
+                                                      int k, double M, const int8_t *__restrict__ st, double *out,
+                                                      int32_t *flag, XBuf xb) {
   __shared__ NodeXLds lds;
   Group X;
   X.init(xb, &lds.x);
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__
   for (int e = 0; e < EPT; e++) {
     const int64_t j = j0 + (int64_t)e * NT;
     x[e] = (beta && j < p) ? beta[j] : 0.0;
-    a[e] = (alpha && j < p) ? alpha[j] : 0.0;
+    a[e] = (alpha && j < p) ? ascale * alpha[j] : 0.0;
     const int c = sv(e);
     s[1] += c == kOne ? 1.0 : 0.0;
     s[2] += c == kFree ? 1.0 : 0.0;
@@ -922,10 +922,10 @@ hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, in
   return hipGetLastError();
 }
 
-hipError_t launch_regularizer_x(const double *beta, const double *alpha, int64_t p, int32_t k, double M,
-                                const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s) {
+hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,
+                                double M, const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s) {
   const XShape g = reg_xshape(p);
-#define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, p, k, M, st, out2, flag, xb)
+#define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, ascale, p, k, M, st, out2, flag, xb)
   PR_REGX(PR_CALL)
 #undef PR_CALL
   return hipGetLastError();
