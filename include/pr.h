@@ -308,8 +308,8 @@ int pr_gemv_t2(pr_ctx *ctx, const double *r1, const double *r2, double *h1, doub
  * the pr_solve path.  Other contexts run pr_solve node by node, and so does a
  * round whose measured per-iteration cost is lower one node at a time (the
  * batch's GEMMs at m active rows, timed at context creation, against m
- * single-node iterations: a 64-row MFMA tile costs as much for one node as
- * for 64); by the same measure, once the nodes still iterating are that few,
+ * single-node iterations, the GEMMs rated by whole tiles of 64 rows); by the
+ * same measure, once the nodes still iterating are that few,
  * they leave the batch and finish on the single-node path from their current
  * iterates (their iters / restarts / trials count both parts).  Every
  * iteration variant but AC-FGM (which runs node by node) runs batched, the

@@ -664,7 +664,8 @@ int tune_batch(pr_ctx *c) {
 // times; Gram mode its one product) plus the node steps, the single-node path
 // m times one X^T pass plus the product over the support and the step
 // (Gram mode: the product over the support's Gram columns and the step).  A
-// 64-row MFMA tile costs the same for 1 node as for 64, so small rounds
+// batch costs more than a few single-node passes (the tables are indexed by
+// whole tiles of 64 rows; up to 48 rows the products take less), so small rounds
 // (typically the first levels of a branch-and-bound tree) run one at a time.
 bool batch_pays(const pr_ctx *c, int32_t m) {
   int nta = nr_of(m) / 64, nta2 = nr_of(c->rs * m) / 64;
@@ -1005,11 +1006,11 @@ int batch_products(pr_ctx *c, int32_t m, int32_t *kst_out) {
   const int32_t kst = kst_for(c, m);
   PR_TRY(hipMemcpyAsync(c->d_split + 6, &ksf, sizeof(int32_t), hipMemcpyHostToDevice, s));
   PR_TRY(launch_gemm_any(c->P.xdt, c->Xrow, p, kF64, c->Bx, p, c->CF, n, Nr, p, ksf, nullptr, nullptr, nullptr,
-                         nullptr, ksf, nullptr, s));
+                         nullptr, ksf, nullptr, s, m));
   PR_TRY(launch_batch_resid(c->CF, c->d_split + 6, n, m, Nr, c->P.y, c->Rd, c->fsum, nullptr, c->P.loss, nullptr,
                             s));
   PR_TRY(launch_gemm_any(c->P.xdt, c->P.X, n, kF64, c->Rd, n, c->CT, p, NrT, n, kst, nullptr, nullptr, nullptr,
-                         nullptr, kst, nullptr, s));
+                         nullptr, kst, nullptr, s, c->rs * m));
   *kst_out = kst;
   return PR_OK;
 }
@@ -1808,7 +1809,7 @@ int pr_time_gram_gemm(pr_ctx *c, int32_t m, int32_t reps, double *ms) {
     hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
     if (e != hipSuccess) return e;
     return launch_gemm_any(kF64, c->G, p, kF64, c->Bx, p, c->CG, p, Nr, p, ksg, nullptr, nullptr, nullptr, nullptr, 0,
-                           cnt, s);
+                           cnt, s, m);
   };
   PR_TRY(gemm());
   PR_TRY(hipEventRecord(c->tev[0], s));
@@ -1836,13 +1837,13 @@ int pr_time_batch_gemm(pr_ctx *c, int32_t m, int32_t reps, double *ms_fwd, doubl
     hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
     if (e != hipSuccess) return e;
     return launch_gemm_any(c->P.xdt, c->Xrow, p, kF64, c->Bx, p, c->CF, n, Nr, p, ksf, nullptr, nullptr, nullptr,
-                           nullptr, 0, cnt, s);
+                           nullptr, 0, cnt, s, m);
   };
   auto trn = [&]() {
     hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
     if (e != hipSuccess) return e;
     return launch_gemm_any(c->P.xdt, c->P.X, n, kF64, c->Rd, n, c->CT, p, NrT, n, kst, nullptr, nullptr, nullptr,
-                           nullptr, 0, cnt, s);
+                           nullptr, 0, cnt, s, c->rs * m);
   };
   double *outs[2] = {ms_fwd, ms_t};
   for (int w = 0; w < 2; w++) {
@@ -1910,15 +1911,17 @@ int grad_images(pr_ctx *c, int32_t m, const double *Bp) {
   return PR_OK;
 }
 
-// Whether m images go faster together: the tuned times of the two GEMMs at m
-// rows against two passes over X per node (a 64-row tile costs the same for
-// one node as for 64: 16384 x 8192 in BF16, 0.55 ms against 0.1 per node).
+// Whether m images go faster together: the two GEMMs at m rows (the tables hold
+// whole tiles of 64 rows; one tile of 16 / 32 / 48 rows takes 0.37 / 0.58 / 0.79
+// of one) against two passes over X per node (16384 x 8192 in BF16: 0.2 ms up
+// to 16 nodes and 0.55 at 64, against 0.1 per node).
 bool images_pay(const pr_ctx *c, int32_t m) {
   if (!c->batch_ok) return false;
-  int nta = nr_of(m) / 64, nta2 = nr_of(c->rs * m) / 64;
-  if (nta >= kTuneMax) nta = kTuneMax - 1;
-  if (nta2 >= kTuneMax) nta2 = kTuneMax - 1;
-  return 2.0 * m * c->t_gemv_ms >= c->h_tbest[nta] + c->h_tbest[kTuneMax + nta2];
+  auto cost = [&](int table, int rows) {
+    const int r16 = (rows + 15) / 16, nta = std::min(nr_of(rows) / 64, kTuneMax - 1);
+    return c->h_tbest[table * kTuneMax + nta] * (r16 < 4 ? 0.16 + 0.21 * r16 : 1.0);
+  };
+  return 2.0 * m * c->t_gemv_ms >= cost(0, m) + cost(1, c->rs * m);
 }
 
 }  // namespace

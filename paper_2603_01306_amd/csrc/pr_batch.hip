@@ -63,25 +63,30 @@ struct Lane8<double> {
 
 // C[z][r][c] = sum_{k in split z} A[c][k] * B[r][k] on FP64 MFMA, operands
 // BF16 / FP32 / FP64 (converted exactly).  Block = 4 waves, block tile 128 (c)
-// x 64 (r), wave tile 64 x 32 = 4 x 2 MFMA tiles of 16 x 16.  The reduction
-// runs in steps of 32: the lanes of quarter q own the 8 consecutive indices
-// 8q .. 8q+7 of a step (16-byte loads; a wave reads whole cache lines of each
-// row over consecutive steps); MFMA s of the step combines index 8q + s of
-// every quarter.  Operands are loaded PIPE - 1 steps ahead of the MFMAs.
-template <typename TA, typename TB, int PIPE>
+// x 16 R16 (r): with R16 = 4 the waves form a 2 x 2 grid of 64 x 32 tiles (4 x 2
+// MFMA tiles of 16 x 16), with fewer rows they stand side by side, 32 x 16 R16
+// each, so that a batch's last, partial tile of 64 rows costs only the sixteens
+// it has.  The reduction runs in steps of 32: the lanes of quarter q own the 8
+// consecutive indices 8q .. 8q+7 of a step (16-byte loads; a wave reads whole
+// cache lines of each row over consecutive steps); MFMA s of the step combines
+// index 8q + s of every quarter, whatever the tile, so an entry's sum does not
+// depend on it.  Operands are loaded PIPE - 1 steps ahead of the MFMAs.
+template <typename TA, typename TB, int PIPE, int R16>
 __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, int64_t lda, const TB *__restrict__ B,
                                           int64_t ldb, double *__restrict__ C, int64_t Mc, int64_t Nr, int64_t Kc,
-                                          int mt, int z, int nt, int nr, const int32_t *__restrict__ rowmap) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+                                          int mt, int z, int row0, int nr, const int32_t *__restrict__ rowmap) {
+  constexpr int CT = R16 == 4 ? 4 : 2, RT = R16 == 4 ? 2 : R16;  // MFMA tiles of a wave along c and r
+  constexpr int WC = 8 / CT;                                     // waves along c
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int q = lane >> 4, rr = lane & 15;
-  const int64_t c0 = (int64_t)mt * 128 + (w & 1) * 64;
-  const int64_t r0 = (int64_t)nt * 64 + (w >> 1) * 32;
+  const int64_t c0 = (int64_t)mt * 128 + (w % WC) * (16 * CT);
+  const int64_t r0 = row0 + (w / WC) * (16 * RT);
   const int64_t k0 = (int64_t)z * Kc + 8 * q;
-  // B row of each of the lane's two r positions, and the C row it is stored
-  // to (-1: past the compacted rows, read a valid row and store nothing)
-  int64_t brow[2], orow[2];
+  // B row of each of the lane's r positions, and the C row it is stored to
+  // (-1: past the compacted rows, read a valid row and store nothing)
+  int64_t brow[RT], orow[RT];
 #pragma unroll
-  for (int u = 0; u < 2; u++) {
+  for (int u = 0; u < RT; u++) {
     const int64_t l = r0 + 16 * u + rr;
     if (rowmap) {
       orow[u] = l < nr ? rowmap[l] : -1;
@@ -90,39 +95,40 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, int64_t lda,
       orow[u] = brow[u] = l;
     }
   }
-  const TA *pa[4];
-  const TB *pb[2];
+  // A: a lane offset within the wave's rows (they span at most 64 lda) from
+  // wave-uniform row bases; B rows may lie anywhere
+  const TA *abase = A + c0 * lda + (int64_t)z * Kc;
+  const int64_t alane = rr * lda + 8 * q;
+  const TB *pb[RT];
 #pragma unroll
-  for (int t = 0; t < 4; t++) pa[t] = A + (c0 + 16 * t + rr) * lda + k0;
+  for (int u = 0; u < RT; u++) pb[u] = B + brow[u] * ldb + k0;
+  d4v_t acc[CT][RT];
 #pragma unroll
-  for (int u = 0; u < 2; u++) pb[u] = B + brow[u] * ldb + k0;
-  d4v_t acc[4][2];
+  for (int t = 0; t < CT; t++)
 #pragma unroll
-  for (int t = 0; t < 4; t++)
-#pragma unroll
-    for (int u = 0; u < 2; u++) acc[t][u] = d4v_t{0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < RT; u++) acc[t][u] = d4v_t{0.0, 0.0, 0.0, 0.0};
   const int64_t nsteps = Kc / 32;
-  Lane8<TA> ar[PIPE][4];
-  Lane8<TB> br[PIPE][2];
-  auto load = [&](int64_t st, Lane8<TA>(&a)[4], Lane8<TB>(&bb)[2]) {
+  Lane8<TA> ar[PIPE][CT];
+  Lane8<TB> br[PIPE][RT];
+  auto load = [&](int64_t st, Lane8<TA>(&a)[CT], Lane8<TB>(&bb)[RT]) {
     const int64_t kk = st * 32;
 #pragma unroll
-    for (int t = 0; t < 4; t++) a[t].load(pa[t] + kk);
+    for (int t = 0; t < CT; t++) a[t].load(abase + (16 * t * lda + kk) + alane);
 #pragma unroll
-    for (int u = 0; u < 2; u++) bb[u].load(pb[u] + kk);
+    for (int u = 0; u < RT; u++) bb[u].load(pb[u] + kk);
   };
-  auto step = [&](const Lane8<TA>(&a)[4], const Lane8<TB>(&bb)[2]) {
+  auto step = [&](const Lane8<TA>(&a)[CT], const Lane8<TB>(&bb)[RT]) {
 #pragma unroll
     for (int s8 = 0; s8 < 8; s8++) {
-      double av[4], bv[2];
+      double av[CT], bv[RT];
 #pragma unroll
-      for (int t = 0; t < 4; t++) av[t] = a[t].get(s8);
+      for (int t = 0; t < CT; t++) av[t] = a[t].get(s8);
 #pragma unroll
-      for (int u = 0; u < 2; u++) bv[u] = bb[u].get(s8);
+      for (int u = 0; u < RT; u++) bv[u] = bb[u].get(s8);
 #pragma unroll
-      for (int t = 0; t < 4; t++)
+      for (int t = 0; t < CT; t++)
 #pragma unroll
-        for (int u = 0; u < 2; u++) acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], bv[u], acc[t][u], 0, 0, 0);
+        for (int u = 0; u < RT; u++) acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t], bv[u], acc[t][u], 0, 0, 0);
     }
   };
 #pragma unroll
@@ -142,10 +148,10 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, int64_t lda,
   // MFMA output: register v of lane l is (c = 4v + l/16, r = l%16)
   double *Cz = C + (int64_t)z * Nr * Mc;
 #pragma unroll
-  for (int u = 0; u < 2; u++) {
+  for (int u = 0; u < RT; u++) {
     if (orow[u] < 0) continue;
 #pragma unroll
-    for (int t = 0; t < 4; t++)
+    for (int t = 0; t < CT; t++)
 #pragma unroll
       for (int v = 0; v < 4; v++) Cz[orow[u] * Mc + c0 + 16 * t + 4 * v + q] = acc[t][u][v];
   }
@@ -162,86 +168,89 @@ __device__ __forceinline__ void gemm_tile(const TA *__restrict__ A, int64_t lda,
 constexpr int kLdsRow = 18;
 constexpr int kLdsStage = (128 + 64) * kLdsRow;  // doubles per buffer
 
+template <int R16>
 __device__ __forceinline__ void gemm_tile_f64_lds(const double *__restrict__ A, int64_t lda,
                                                   const double *__restrict__ B, int64_t ldb, double *__restrict__ C,
-                                                  int64_t Mc, int64_t Nr, int64_t Kc, int mt, int z, int nt, int nr,
+                                                  int64_t Mc, int64_t Nr, int64_t Kc, int mt, int z, int row0, int nr,
                                                   const int32_t *__restrict__ rowmap, double *lds) {
+  constexpr int CT = R16 == 4 ? 4 : 2, RT = R16 == 4 ? 2 : R16, WC = 8 / CT;  // as in gemm_tile
+  constexpr int BL = (R16 + 1) / 2;                                             // rounds of B loads, 32 rows each
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int q = lane >> 4, rr = lane & 15;
-  // cooperative loads: A chunk id = tid + 256 i (i < 4), B chunk id = tid + 256 i (i < 2);
+  // cooperative loads: A chunk id = tid + 256 i (i < 4), B chunk id = tid + 256 i (i < BL);
   // row = id / 8, 16-byte part = id % 8
   const int part = tid & 7;
   const double *ga[4];
-  const double *gbp[2];
+  const double *gbp[BL];
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int row = (tid >> 3) + 32 * i;
     ga[i] = A + ((int64_t)mt * 128 + row) * lda + (int64_t)z * Kc + 2 * part;
   }
 #pragma unroll
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < BL; i++) {
     const int row = (tid >> 3) + 32 * i;
-    const int l = nt * 64 + row;
+    const int l = row0 + (row < 16 * R16 ? row : 0);
     const int64_t br = rowmap ? (l < nr ? rowmap[l] : rowmap[0]) : l;
     gbp[i] = B + br * ldb + (int64_t)z * Kc + 2 * part;
   }
-  // C rows of the lane's two r positions (-1: past the compacted rows)
-  const int64_t c0 = (int64_t)mt * 128 + (w & 1) * 64;
-  const int lr0 = nt * 64 + (w >> 1) * 32;
-  int64_t orow[2];
+  // C rows of the lane's r positions (-1: past the compacted rows)
+  const int64_t c0 = (int64_t)mt * 128 + (w % WC) * (16 * CT);
+  const int lr0 = row0 + (w / WC) * (16 * RT);
+  int64_t orow[RT];
 #pragma unroll
-  for (int u = 0; u < 2; u++) {
+  for (int u = 0; u < RT; u++) {
     const int l = lr0 + 16 * u + rr;
     orow[u] = rowmap ? (l < nr ? rowmap[l] : -1) : l;
   }
-  d4v_t acc[4][2];
+  d4v_t acc[CT][RT];
 #pragma unroll
-  for (int t = 0; t < 4; t++)
+  for (int t = 0; t < CT; t++)
 #pragma unroll
-    for (int u = 0; u < 2; u++) acc[t][u] = d4v_t{0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < RT; u++) acc[t][u] = d4v_t{0.0, 0.0, 0.0, 0.0};
   const int64_t nsteps = Kc / 16;
-  d2v_t ra[4], rb[2];
+  d2v_t ra[4], rb[BL];
   auto gload = [&](int64_t st) {
 #pragma unroll
     for (int i = 0; i < 4; i++) ra[i] = *reinterpret_cast<const d2v_t *>(ga[i] + st * 16);
 #pragma unroll
-    for (int i = 0; i < 2; i++) rb[i] = *reinterpret_cast<const d2v_t *>(gbp[i] + st * 16);
+    for (int i = 0; i < BL; i++) rb[i] = *reinterpret_cast<const d2v_t *>(gbp[i] + st * 16);
   };
   auto lstore = [&](double *buf) {
 #pragma unroll
     for (int i = 0; i < 4; i++) *reinterpret_cast<d2v_t *>(buf + ((tid >> 3) + 32 * i) * kLdsRow + 2 * part) = ra[i];
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+    for (int i = 0; i < BL; i++)
       *reinterpret_cast<d2v_t *>(buf + (128 + (tid >> 3) + 32 * i) * kLdsRow + 2 * part) = rb[i];
   };
   gload(0);
   lstore(lds);
   __syncthreads();
-  const int arow = (w & 1) * 64 + rr, brow = 128 + (w >> 1) * 32 + rr;
+  const int arow = (w % WC) * (16 * CT) + rr, brow = 128 + (w / WC) * (16 * RT) + rr;
   for (int64_t st = 0; st < nsteps; st++) {
     double *cur = lds + (st & 1) * kLdsStage;
     if (st + 1 < nsteps) gload(st + 1);
-    d4v_t fa[4], fb[2];
+    d4v_t fa[CT], fb[RT];
 #pragma unroll
-    for (int t = 0; t < 4; t++) fa[t] = *reinterpret_cast<const d4v_t *>(cur + (arow + 16 * t) * kLdsRow + 4 * q);
+    for (int t = 0; t < CT; t++) fa[t] = *reinterpret_cast<const d4v_t *>(cur + (arow + 16 * t) * kLdsRow + 4 * q);
 #pragma unroll
-    for (int u = 0; u < 2; u++) fb[u] = *reinterpret_cast<const d4v_t *>(cur + (brow + 16 * u) * kLdsRow + 4 * q);
+    for (int u = 0; u < RT; u++) fb[u] = *reinterpret_cast<const d4v_t *>(cur + (brow + 16 * u) * kLdsRow + 4 * q);
 #pragma unroll
     for (int j = 0; j < 4; j++)
 #pragma unroll
-      for (int t = 0; t < 4; t++)
+      for (int t = 0; t < CT; t++)
 #pragma unroll
-        for (int u = 0; u < 2; u++)
+        for (int u = 0; u < RT; u++)
           acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[t][j], fb[u][j], acc[t][u], 0, 0, 0);
     if (st + 1 < nsteps) lstore(lds + ((st + 1) & 1) * kLdsStage);
     __syncthreads();
   }
   double *Cz = C + (int64_t)z * Nr * Mc;
 #pragma unroll
-  for (int u = 0; u < 2; u++) {
+  for (int u = 0; u < RT; u++) {
     if (orow[u] < 0) continue;
 #pragma unroll
-    for (int t = 0; t < 4; t++)
+    for (int t = 0; t < CT; t++)
 #pragma unroll
       for (int v = 0; v < 4; v++) Cz[orow[u] * Mc + c0 + 16 * t + 4 * v + q] = acc[t][u][v];
   }
@@ -273,15 +282,24 @@ __global__ void k_sum_planes(const double *__restrict__ C, int KS, int Nr, int r
 template <typename TA, typename TB, int PIPE>
 __global__ __launch_bounds__(256, 2) void k_gemm_f64(const TA *__restrict__ A, int64_t lda, const TB *__restrict__ B,
                                                      int64_t ldb, double *__restrict__ C, int64_t Mc, int64_t Nr,
-                                                     int64_t K, int MT, int NT, int KS,
+                                                     int64_t K, int MT, int KS,
                                                      const int32_t *__restrict__ active,
                                                      const int32_t *__restrict__ rowmap,
                                                      const int32_t *__restrict__ nrow,
-                                                     const int32_t *__restrict__ ksp, int32_t *__restrict__ counter) {
+                                                     const int32_t *__restrict__ ksp, int32_t *__restrict__ counter,
+                                                     int rows) {
   if (active && *active == 0) return;
   if (ksp) KS = *ksp;
-  const int nr = rowmap ? *nrow : (int)Nr;
-  const int nta = rowmap ? (nr + 63) / 64 : NT;
+  const int nr = rowmap ? *nrow : rows;
+  // Rows in sixteens over the fewest tiles of at most four.  Where tiles of up
+  // to three hold them (1-3, 5, 6 and 9 sixteens) they are spread evenly: 16 /
+  // 32 / 48 rows of 16384 x 8192 in BF16 take 0.103 / 0.163 / 0.223 ms where
+  // every count took the 0.281 of 64, and 80 / 96 / 144 rows 0.46 / 0.51 / 0.62
+  // where they took 0.54 / 0.54 / 0.80.  Other counts keep whole tiles: a mix
+  // of four and three was slower than padding (208 rows: 1.12 against 1.05).
+  const int r16 = (nr + 15) / 16, nta = (r16 + 3) / 4;
+  const bool even = r16 <= 3 * nta;
+  const int rbase = even ? r16 / nta : 4, rmore = even ? r16 - rbase * nta : 0;
   const int groups = MT * KS;
   const int nitems = ((groups + 7) / 8) * 8 * nta;
   const int64_t Kc = K / KS;
@@ -296,16 +314,24 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(const TA *__restrict__ A, i
     const int g = qq / nta, nt = qq - g * nta;
     const int G = g * 8 + x;
     if (G < groups) {
-      if constexpr (std::is_same<TA, double>::value && std::is_same<TB, double>::value)
-        gemm_tile_f64_lds(A, lda, B, ldb, C, Mc, Nr, Kc, G % MT, G / MT, nt, nr, rowmap, stage);
-      else
-        gemm_tile<TA, TB, PIPE>(A, lda, B, ldb, C, Mc, Nr, Kc, G % MT, G / MT, nt, nr, rowmap);
+      const int n16 = rbase + (nt < rmore ? 1 : 0), row0 = 16 * (nt * rbase + (nt < rmore ? nt : rmore));
+      auto tile = [&](auto r) {
+        constexpr int R16 = decltype(r)::value;
+        if constexpr (kLds)
+          gemm_tile_f64_lds<R16>(A, lda, B, ldb, C, Mc, Nr, Kc, G % MT, G / MT, row0, nr, rowmap, stage);
+        else
+          gemm_tile<TA, TB, PIPE, R16>(A, lda, B, ldb, C, Mc, Nr, Kc, G % MT, G / MT, row0, nr, rowmap);
+      };
+      if (n16 == 4) tile(std::integral_constant<int, 4>{});
+      else if (n16 == 3) tile(std::integral_constant<int, 3>{});
+      else if (n16 == 2) tile(std::integral_constant<int, 2>{});
+      else tile(std::integral_constant<int, 1>{});
     }
     if (counter) {
       __syncthreads();
       if (threadIdx.x == 0) next = (int)gridDim.x + atomicAdd(counter, 1);
       __syncthreads();
-      item = next;
+      item = __builtin_amdgcn_readfirstlane(next);
     } else {
       item += gridDim.x;
     }
@@ -647,13 +673,14 @@ __global__ __launch_bounds__(256) void k_union_fix(const T *__restrict__ Mat, in
 template <typename TA, typename TB, int PIPE>
 hipError_t launch_gemm_t(const TA *A, int64_t lda, const TB *B, int64_t ldb, double *C, int64_t Mc, int64_t Nr,
                          int64_t K, int KS, const int32_t *active, const int32_t *rowmap, const int32_t *nrow,
-                         const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s) {
+                         const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s, int rows) {
+  if (rows <= 0 || rows > Nr) rows = (int)Nr;
   const int MT = (int)(Mc / 128), NT = (int)(Nr / 64);
   const int groups = MT * (ksp ? ks_max : KS);
   const int items = (groups + 7) / 8 * 8 * NT;
   const int grid = items < kGemmGrid ? (items + 7) / 8 * 8 : kGemmGrid;
-  k_gemm_f64<TA, TB, PIPE><<<(unsigned)grid, 256, 0, s>>>(A, lda, B, ldb, C, Mc, Nr, K, MT, NT, KS, active, rowmap,
-                                                          nrow, ksp, counter);
+  k_gemm_f64<TA, TB, PIPE><<<(unsigned)grid, 256, 0, s>>>(A, lda, B, ldb, C, Mc, Nr, K, MT, KS, active, rowmap, nrow,
+                                                          ksp, counter, rows);
   return hipGetLastError();
 }
 
@@ -661,15 +688,16 @@ hipError_t launch_gemm_f64(const uint16_t *A, int64_t lda, const double *B, int6
                            int64_t Nr, int64_t K, int KS, const int32_t *active, const int32_t *rowmap,
                            const int32_t *nrow, const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s) {
   return launch_gemm_t<uint16_t, double, kPipe>(A, lda, B, ldb, C, Mc, Nr, K, KS, active, rowmap, nrow, ksp, ks_max,
-                                                counter, s);
+                                                counter, s, (int)Nr);
 }
 
 hipError_t launch_gemm_any(int adt, const void *A, int64_t lda, int bdt, const void *B, int64_t ldb, double *C,
                            int64_t Mc, int64_t Nr, int64_t K, int KS, const int32_t *active, const int32_t *rowmap,
-                           const int32_t *nrow, const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s) {
+                           const int32_t *nrow, const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s,
+                           int rows) {
 #define PR_GEMM_CASE(A_T, B_T, PIPE_)                                                                              \
   return launch_gemm_t<A_T, B_T, PIPE_>((const A_T *)A, lda, (const B_T *)B, ldb, C, Mc, Nr, K, KS, active, rowmap, \
-                                        nrow, ksp, ks_max, counter, s)
+                                        nrow, ksp, ks_max, counter, s, rows)
   if (adt == kBF16 && bdt == kF64) PR_GEMM_CASE(uint16_t, double, kPipe);
   if (adt == kF32 && bdt == kF64) PR_GEMM_CASE(float, double, kPipe);
   if (adt == kBF16 && bdt == kBF16) PR_GEMM_CASE(uint16_t, uint16_t, kPipe);
