@@ -249,7 +249,7 @@ def mlp_kernel_bench(rows=1 << 20, reps=10):
     ms = e0.elapsed_time(e1) / reps
     flop = 6 * (8 * 64 + 64 * 64 + 64) * rows
     tfs = flop / (ms * 1e-3) / 1e12
-    return {"kernel": "pr_mlp_grad (k_mlp<true> + partial-gradient reduction)", "rows": rows, "ms_per_launch": round(ms, 4),
+    return {"kernel": "pr_mlp_grad (k_mlp_grad + partial-gradient reduction)", "rows": rows, "ms_per_launch": round(ms, 4),
             "rows_per_s": round(rows / ms * 1e3), "epoch_s_409.6M_rows": round(409.6e6 / (rows / ms * 1e3), 3),
             "roofline": {"bound": "mfma", "achieved": round(tfs, 2), "peak": 2500.0, "unit": "TFLOP/s",
                          "frac": round(tfs / 2500.0, 4), "traffic": None,

@@ -5,14 +5,15 @@
 //
 // Layout.  A wave takes 32 rows (coordinates) at a time and keeps every layer
 // transposed, units x rows: Z1^T = W1 F^T, Z2^T = W2 A1^T, so the weights are
-// the A operands (loaded once per wave) and the activations stay in the MFMA
+// the A operands (converted once per block) and the activations stay in the MFMA
 // C layout, where register v of lane l holds unit 8(v/4) + 4(l/32) + v%4 of row
 // l%32.  Turning a C tile into the B operand of the next product (lane l needs
 // 8 consecutive units of row l%32) takes one exchange of 4 values between
 // lanes l and l^32 per 16-unit step.  The weight gradients are products over
-// rows (dW2 = dZ2^T A1, dW1 = dZ1^T F); their operands are transposed through
-// LDS tiles of 64 units x 32 rows.  The bias gradient of layer 1 rides on a
-// column of ones next to the 8 features in the dW1 product.
+// rows (dW2 = dZ2^T A1, dW1 = dZ1^T F); their operands go through LDS tiles of
+// the block's 128 rows and come back by transposing reads.  The bias gradient
+// of layer 1 rides on a column of ones next to the 8 features in the dW1
+// product.
 #include "pr_device.h"
 #include "pr_internal.h"
 
@@ -27,6 +28,10 @@ constexpr int kWaves = 4;
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // FP32 -> BF16, round to nearest even (one v_cvt_pk_bf16_f32 on gfx950)
 __device__ __forceinline__ unsigned short f2bf(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
@@ -41,248 +46,345 @@ __device__ __forceinline__ int crow(int v, int hh) { return 8 * (v >> 2) + 4 * h
 // of the tile as the reduction index, the lane's row as the column.  Lane
 // l < 32 holds units 16S + 0..3 (registers 8S + i) and 16S + 8..11 (8S + 4 + i)
 // and needs 16S + 0..7; lane l + 32 holds 16S + 4..7 and 16S + 12..15 and
-// needs 16S + 8..15.  One v_permlane32_swap per register pair exchanges the
-// upper half of the first register with the lower half of the second.
+// needs 16S + 8..15.  After the conversion a register holds two units, so two
+// v_permlane32_swap exchange the upper half of the wave in one register with
+// the lower half in the other.
 template <int S>
 __device__ __forceinline__ bf16x8_t b_from_c(const f32x16_t &c) {
-  bf16x8_t r;
+  u32x4_t r;
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(c[8 * S + i]),
-                                                     __float_as_uint(c[8 * S + 4 + i]), false, false);
-    r[i] = (__bf16)__uint_as_float(sw[0]);
-    r[4 + i] = (__bf16)__uint_as_float(sw[1]);
+  for (int i = 0; i < 2; i++) {
+    const bf16x2_t lo = {(__bf16)c[8 * S + 2 * i], (__bf16)c[8 * S + 2 * i + 1]};
+    const bf16x2_t up = {(__bf16)c[8 * S + 4 + 2 * i], (__bf16)c[8 * S + 5 + 2 * i]};
+    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, lo),
+                                                     __builtin_bit_cast(unsigned, up), false, false);
+    r[i] = sw[0];
+    r[2 + i] = sw[1];
   }
-  return r;
+  return __builtin_bit_cast(bf16x8_t, r);
 }
 
 __device__ __forceinline__ bf16x8_t lds8(const unsigned short *p) {
   return as_bf(*reinterpret_cast<const u16x8_t *>(p));
 }
 
-// Forward (TRAIN = false: out[row] = network output) or forward + backward
-// (TRAIN = true: block partial sums of the gradient of
-// inv_n * sum_rows (out - T)^2 and of sum_rows (out - T)^2 into part[block]).
-// Block = 4 waves; block b takes row chunks (b * cpb + it) * 4 + wave.
-template <bool TRAIN>
-__global__ __launch_bounds__(256) void k_mlp(const float *__restrict__ P, const uint16_t *__restrict__ F,
-                                             const float *__restrict__ T, int64_t rows, int cpb, float inv_n,
-                                             float *__restrict__ out, float *__restrict__ part) {
-  __shared__ float sp[kNP];
-  __shared__ __align__(16) unsigned short t_dz2[TRAIN ? kWaves : 1][kH * 32];
-  __shared__ __align__(16) unsigned short t_a1[TRAIN ? kWaves : 1][kH * 32];
-  __shared__ __align__(16) unsigned short t_dz1[TRAIN ? kWaves : 1][kH * 32];
-  __shared__ __align__(16) unsigned short t_f[TRAIN ? kWaves : 1][16 * 32];
-  for (int i = threadIdx.x; i < kNP; i += blockDim.x) sp[i] = P[i];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hh = lane >> 5, lr = lane & 31;
+// Values of one 32-unit tile in the C layout's order, from LDS (broadcast reads)
+__device__ __forceinline__ f32x16_t units(const float *sp, int hh) {
+  f32x16_t r;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const f32x4_t t = *reinterpret_cast<const f32x4_t *>(sp + 8 * g + 4 * hh);
+#pragma unroll
+    for (int e = 0; e < 4; e++) r[4 * g + e] = t[e];
+  }
+  return r;
+}
 
-  bf16x8_t aw1[2], aw2[2][4], aw2t[2][4];
+// Weights as MFMA operands (lane: unit, eight consecutive reduction indices),
+// BF16.  Layer 1 has 8 inputs and the product 16 reduction indices: the upper
+// eight are zero.
+__device__ __forceinline__ void load_w1(const float *sp, int lr, int hh, bf16x8_t (&w1)[2]) {
 #pragma unroll
   for (int u = 0; u < 2; u++) {
     u16x8_t t;
 #pragma unroll
     for (int e = 0; e < 8; e++) t[e] = hh ? (unsigned short)0 : f2bf(sp[OW1 + (32 * u + lr) * kNF + e]);
-    aw1[u] = as_bf(t);
+    w1[u] = as_bf(t);
   }
+}
+// Layer 2: units 32o .., reduction indices 16s ..; of W2, or of W2^T
+__device__ __forceinline__ bf16x8_t load_w2(const float *sp, int lr, int hh, int o, int s, bool transposed) {
+  const int k = 16 * s + 8 * hh, u = 32 * o + lr;
+  u16x8_t t;
+#pragma unroll
+  for (int e = 0; e < 8; e++) t[e] = f2bf(sp[OW2 + (transposed ? (k + e) * kH + u : u * kH + k + e)]);
+  return as_bf(t);
+}
+
+// Forward of the wave's 32 rows (feature operand fb): the activations of layer
+// 1 as operands b (lane: row, eight consecutive units), layer 2 after its ReLU
+// in a2 (units x rows), and the row's output in every lane.  Starting the
+// products from the bias saves nothing: the maximum of an MFMA result with zero
+// costs a second instruction, that of a sum does not.  w2(o, s): operand of
+// layer 2.
+template <class W2>
+__device__ __forceinline__ float forward_rows(const bf16x8_t (&w1)[2], const W2 &w2, const float *b1, const float *b2, const float *w3, float b3,
+                                              bf16x8_t fb, int hh, bf16x8_t (&b)[4], f32x16_t (&a2)[2]) {
+  const f32x16_t zero = {};
+#pragma unroll
+  for (int u = 0; u < 2; u++) {
+    const f32x16_t bias = units(b1 + 32 * u, hh);
+    f32x16_t a1 = mma(w1[u], fb, zero);
+#pragma unroll
+    for (int v = 0; v < 16; v++) a1[v] = fmaxf(a1[v] + bias[v], 0.f);
+    b[2 * u] = b_from_c<0>(a1);
+    b[2 * u + 1] = b_from_c<1>(a1);
+  }
+  float po = 0.f;
+#pragma unroll
+  for (int o = 0; o < 2; o++) {
+    const f32x16_t bias = units(b2 + 32 * o, hh), wo = units(w3 + 32 * o, hh);
+    a2[o] = zero;
+#pragma unroll
+    for (int s = 0; s < 4; s++) a2[o] = mma(w2(o, s), b[s], a2[o]);
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      a2[o][v] = fmaxf(a2[o][v] + bias[v], 0.f);
+      po += wo[v] * a2[o][v];
+    }
+  }
+  return po + __shfl_xor(po, 32) + b3;
+}
+
+// out[row] = network output.  Block = 4 waves; block b takes row chunks
+// (b * cpb + it) * 4 + wave.
+__global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ P, const uint16_t *__restrict__ F,
+                                                     int64_t rows, int cpb, float *__restrict__ out) {
+  __shared__ __align__(16) float sp[kNP];
+  for (int i = threadIdx.x; i < kNP; i += blockDim.x) sp[i] = P[i];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hh = lane >> 5, lr = lane & 31;
+  bf16x8_t w1[2], w2[2][4];
+  load_w1(sp, lr, hh, w1);
 #pragma unroll
   for (int o = 0; o < 2; o++)
 #pragma unroll
-    for (int s = 0; s < 4; s++) {
-      u16x8_t t, tt;
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        t[e] = f2bf(sp[OW2 + (32 * o + lr) * kH + 16 * s + 8 * hh + e]);
-        tt[e] = f2bf(sp[OW2 + (16 * s + 8 * hh + e) * kH + 32 * o + lr]);
-      }
-      aw2[o][s] = as_bf(t);
-      aw2t[o][s] = as_bf(tt);  // A operand of W2^T (tile o of its rows = input units)
-    }
-  const float b3 = sp[OB3];
-  const f32x16_t zero = {};
+    for (int s = 0; s < 4; s++) w2[o][s] = load_w2(sp, lr, hh, o, s, false);
+  for (int it = 0; it < cpb; it++) {
+    const int64_t row = (((int64_t)blockIdx.x * cpb + it) * kWaves + w) * 32 + lr;
+    const bool valid = row < rows;
+    u16x8_t fu = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (valid && hh == 0) fu = *reinterpret_cast<const u16x8_t *>(F + row * kNF);
+    bf16x8_t b[4];
+    f32x16_t a2[2];
+    const float orow = forward_rows(w1, [&](int o, int s) { return w2[o][s]; }, sp + OB1, sp + OB2, sp + OW3, sp[OB3],
+                                    as_bf(fu), hh, b, a2);
+    if (valid && hh == 0) out[row] = orow;
+  }
+}
 
-  f32x16_t gW2[2][2] = {{zero, zero}, {zero, zero}}, gW1[2] = {zero, zero};
+// LDS tiles of the training kernel: kRows rows x 32 units, BF16, rows of 64 B
+// whose four 16 B chunks are permuted by bits 2-3 of the row, so that the eight
+// rows of a 16 B store and the four rows of a transposing read each cover all
+// banks once.
+constexpr int kRows = 32 * kWaves;
+struct Tile {
+  unsigned short v[kRows * 32];
+  // units 8c .. 8c+7 of one row
+  __device__ __forceinline__ void put(int row, int c, bf16x8_t x) {
+    *reinterpret_cast<bf16x8_t *>(&v[row * 32 + ((c ^ ((row >> 2) & 3)) << 3)]) = x;
+  }
+};
+// MFMA operand over rows: lane = unit, rows 16ks + 8hh .. + 7.  A transposing
+// read hands lane i of 16 the i-th of 16 units over four rows; the lane's own
+// address is that of four units in row i / 4 of them.
+__device__ __forceinline__ bf16x8_t rows8(const unsigned short *lo, const unsigned short *up) {
+  typedef __attribute__((address_space(3))) s16x4_t lds_t;
+  const s16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t *)lo);
+  const s16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t *)up);
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// x where the packed activation a (>= 0) is not zero, else 0: two packed 16-bit
+// instructions per pair.  (With a constant one the compiler takes the product
+// apart into compares and selects of single halves, five per pair.)
+__device__ __forceinline__ bf16x8_t relu_mask(bf16x8_t x, bf16x8_t a, unsigned one) {
+  const u32x4_t ones = {one, one, one, one};
+  return as_bf(__builtin_bit_cast(u16x8_t, x) *
+               __builtin_elementwise_min(__builtin_bit_cast(u16x8_t, a), __builtin_bit_cast(u16x8_t, ones)));
+}
+
+// Sum of x[v] over the 32 rows of each half of the wave, for all 16 registers
+// in 16 exchanges: every step halves the registers a lane is responsible for.
+// The lane ends with the sum for register (lane & 15), lane bit 4 apart.
+__device__ __forceinline__ float sum_rows(const float (&x)[16], int lane) {
+  float t[8];
+#pragma unroll
+  for (int s = 3; s >= 0; s--) {
+    const bool upper = (lane >> s) & 1;
+#pragma unroll
+    for (int v = 0; v < (1 << s); v++) {
+      const float a = s == 3 ? x[v] : t[v], c = s == 3 ? x[v + 8] : t[v + (1 << s)];
+      t[v] = (upper ? c : a) + __shfl_xor(upper ? a : c, 1 << s);
+    }
+  }
+  return t[0] + __shfl_xor(t[0], 16);
+}
+
+// Forward + backward: block partial sums of the gradient of
+// inv_n * sum_rows (out - T)^2 and of sum_rows (out - T)^2 into part[block].
+//
+// Bound by LDS and vector instructions together: per 128 rows the four waves
+// issue about 2600 cycles of LDS accesses and 2000 of vector instructions per
+// SIMD beside 960 of MFMA.  The weight gradients are products over rows, so
+// their operands are needed transposed: the packed operands of the forward and
+// backward products go to LDS as they are (16 B stores) and come back through
+// transposing reads.  The waves share the tiles, and each accumulates one
+// 32 x 32 quarter of dW2 and, over half the rows, one 32 x 9 half of dW1: 32
+// accumulator registers instead of 96, which with layer 2's operands in LDS
+// leaves room for two waves per SIMD, and dW2 needs no sum over waves.
+// 1M rows 171 -> 71 us, one row 25 -> 13 us, both with the reduction kernel
+// (before: 2-byte transposing stores, one wave per SIMD, all accumulators in
+// every wave).  Recomputing the transposed operands by MFMAs with their factors
+// swapped, without LDS tiles, took 120 us.
+__global__ __launch_bounds__(256, 2) void k_mlp_grad(const float *__restrict__ P, const uint16_t *__restrict__ F,
+                                                     const float *__restrict__ T, int64_t rows, int cpb, float inv_n,
+                                                     float *__restrict__ part) {
+  struct Tiles {
+    Tile z2[2], a1[2], z1[2];
+  };
+  __shared__ __align__(16) union {
+    Tiles t;
+    float sp[kNP];
+  } u;
+  __shared__ __align__(16) unsigned short t_f[kRows * 16];      // 8 features, a one (bias of layer 1), zeros
+  __shared__ __align__(16) unsigned short w2f[16][64 * 8];   // operands of W2, then of W2^T
+  __shared__ __align__(16) float s_b1[kH], s_b2[kH], s_w3[kH];
+  __shared__ float red[2][kWaves][kH];
+  __shared__ float lred[2][kWaves];
+  for (int i = threadIdx.x; i < kNP; i += blockDim.x) u.sp[i] = P[i];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hh = lane >> 5, lr = lane & 31;
+  bf16x8_t w1[2];
+  load_w1(u.sp, lr, hh, w1);
+  for (int f = w; f < 16; f += kWaves)
+    *reinterpret_cast<bf16x8_t *>(&w2f[f][8 * lane]) = load_w2(u.sp, lr, hh, (f >> 2) & 1, f & 3, f >= 8);
+  if (threadIdx.x < kH) {
+    s_b1[threadIdx.x] = u.sp[OB1 + threadIdx.x];
+    s_b2[threadIdx.x] = u.sp[OB2 + threadIdx.x];
+    s_w3[threadIdx.x] = u.sp[OW3 + threadIdx.x];
+  }
+  const float b3 = u.sp[OB3];
+  const int lrow = 32 * w + lr;  // the lane's row of the block's 128
+  if (hh) *reinterpret_cast<u16x8_t *>(&t_f[lrow * 16 + 8]) = u16x8_t{0x3f80, 0, 0, 0, 0, 0, 0, 0};
+  __syncthreads();
+
+  // the lane's addresses in transposing reads, rows 8hh + (0..3) and + 4
+  const int i16 = lane & 15, tr = 8 * hh + (i16 >> 2), tc = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
+  const int off0 = tr * 32 + ((tc ^ (2 * hh)) << 3) + 4 * (i16 & 1);
+  const int off1 = (tr + 4) * 32 + ((tc ^ (2 * hh + 1)) << 3) + 4 * (i16 & 1);
+  const int offf = tr * 16 + 4 * (i16 & 3);  // features: both groups of 16 lanes read the 16 columns
+
+  const int qo = w & 1, qi = w >> 1;  // the wave's quarter of dW2; for dW1: half qo of the units, rows 64 qi ..
+  unsigned one = 0x00010001u;
+  __asm__("" : "+v"(one));
+  const f32x16_t zero = {};
+  f32x16_t gW2 = zero, gW1 = zero;
   float gb2[2][16], gw3[2][16], gb3 = 0.f, lsum = 0.f;
 #pragma unroll
   for (int o = 0; o < 2; o++)
 #pragma unroll
     for (int v = 0; v < 16; v++) gb2[o][v] = gw3[o][v] = 0.f;
 
-  if (TRAIN && hh == 0) {
-    // rows 8..15 of the transposed feature tile: a row of ones (bias of layer 1), zeros
-#pragma unroll
-    for (int e = 8; e < 16; e++) t_f[w][e * 32 + lr] = (e == 8) ? (unsigned short)0x3f80 : (unsigned short)0;
-  }
-
+  const int64_t row0 = (int64_t)blockIdx.x * cpb * kRows + lrow;
+  u16x8_t fu = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (row0 < rows && hh == 0) fu = *reinterpret_cast<const u16x8_t *>(F + row0 * kNF);
+  float tv = row0 < rows ? T[row0] : 0.f;
   for (int it = 0; it < cpb; it++) {
-    const int64_t row = (((int64_t)blockIdx.x * cpb + it) * kWaves + w) * 32 + lr;
+    const int64_t row = row0 + (int64_t)it * kRows, next = row + kRows;
     const bool valid = row < rows;
-    u16x8_t fu = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (valid && hh == 0) fu = *reinterpret_cast<const u16x8_t *>(F + row * kNF);
-    const bf16x8_t fb = as_bf(fu);
-    f32x16_t a1[2];
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-      a1[u] = mma(aw1[u], fb, zero);
-#pragma unroll
-      for (int v = 0; v < 16; v++) a1[u][v] = fmaxf(a1[u][v] + sp[OB1 + 32 * u + crow(v, hh)], 0.f);
+    // the next rows' inputs are on their way during this iteration
+    u16x8_t fn = {0, 0, 0, 0, 0, 0, 0, 0};
+    float tn = 0.f;
+    if (it + 1 < cpb && next < rows) {
+      if (hh == 0) fn = *reinterpret_cast<const u16x8_t *>(F + next * kNF);
+      tn = T[next];
     }
-    f32x16_t a2[2] = {zero, zero};
-    {
-      const bf16x8_t b0 = b_from_c<0>(a1[0]), b1 = b_from_c<1>(a1[0]);
-      const bf16x8_t b2 = b_from_c<0>(a1[1]), b3v = b_from_c<1>(a1[1]);
+
+    bf16x8_t b[4], bd[4];
+    f32x16_t a2[2];
+    const float orow = forward_rows(w1, [&](int o, int s) { return lds8(&w2f[4 * o + s][8 * lane]); }, s_b1,
+                                    s_b2, s_w3, b3, as_bf(fu), hh, b, a2);
 #pragma unroll
-      for (int o = 0; o < 2; o++) {
-        a2[o] = mma(aw2[o][0], b0, a2[o]);
-        a2[o] = mma(aw2[o][1], b1, a2[o]);
-        a2[o] = mma(aw2[o][2], b2, a2[o]);
-        a2[o] = mma(aw2[o][3], b3v, a2[o]);
-      }
-    }
-    float po = 0.f;
-#pragma unroll
-    for (int o = 0; o < 2; o++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const int u = 32 * o + crow(v, hh);
-        a2[o][v] = fmaxf(a2[o][v] + sp[OB2 + u], 0.f);
-        po += sp[OW3 + u] * a2[o][v];
-      }
-    const float orow = po + __shfl_xor(po, 32) + b3;
-    if (!TRAIN) {
-      if (valid && hh == 0) out[row] = orow;
-      continue;
-    }
-    const float d = valid ? orow - T[row] : 0.f;
+    for (int s = 0; s < 4; s++) u.t.a1[s >> 1].put(lrow, 2 * (s & 1) + hh, b[s]);
+    const float d = valid ? orow - tv : 0.f;
+    const float dout = 2.f * d * inv_n;
     if (hh == 0) {
       lsum += d * d;
+      gb3 += dout;
+      *reinterpret_cast<u16x8_t *>(&t_f[lrow * 16]) = fu;
     }
-    const float dout = 2.f * d * inv_n;
-    if (hh == 0) gb3 += dout;
-    f32x16_t dz2[2];
 #pragma unroll
-    for (int o = 0; o < 2; o++)
+    for (int o = 0; o < 2; o++) {
+      const f32x16_t wo = units(s_w3 + 32 * o, hh);
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        const int u = 32 * o + crow(v, hh);
         gw3[o][v] += a2[o][v] * dout;
-        const float g = a2[o][v] > 0.f ? sp[OW3 + u] * dout : 0.f;
-        dz2[o][v] = g;
-        gb2[o][v] += g;
+        const float g = wo[v] * dout;
+        a2[o][v] = a2[o][v] > 0.f ? g : 0.f;
+        gb2[o][v] += a2[o][v];
       }
-    // dA1^T = W2^T dZ2^T, then the ReLU mask of layer 1
-    f32x16_t dz1[2] = {zero, zero};
-    {
-      const bf16x8_t b0 = b_from_c<0>(dz2[0]), b1 = b_from_c<1>(dz2[0]);
-      const bf16x8_t b2 = b_from_c<0>(dz2[1]), b3v = b_from_c<1>(dz2[1]);
+      bd[2 * o] = b_from_c<0>(a2[o]);
+      bd[2 * o + 1] = b_from_c<1>(a2[o]);
+    }
 #pragma unroll
-      for (int i = 0; i < 2; i++) {
-        dz1[i] = mma(aw2t[i][0], b0, dz1[i]);
-        dz1[i] = mma(aw2t[i][1], b1, dz1[i]);
-        dz1[i] = mma(aw2t[i][2], b2, dz1[i]);
-        dz1[i] = mma(aw2t[i][3], b3v, dz1[i]);
+    for (int s = 0; s < 4; s++) u.t.z2[s >> 1].put(lrow, 2 * (s & 1) + hh, bd[s]);
+    // dA1^T = W2^T dZ2^T, then the ReLU mask of layer 1: where its packed activation is not zero
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      f32x16_t z = zero;
+#pragma unroll
+      for (int s = 0; s < 4; s++) z = mma(lds8(&w2f[8 + 4 * i + s][8 * lane]), bd[s], z);
+      u.t.z1[i].put(lrow, hh, relu_mask(b_from_c<0>(z), b[2 * i], one));
+      u.t.z1[i].put(lrow, 2 + hh, relu_mask(b_from_c<1>(z), b[2 * i + 1], one));
+    }
+    dev::lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < kRows / 16; ks++) {
+      const unsigned short *zp = u.t.z2[qo].v + 512 * ks, *ap = u.t.a1[qi].v + 512 * ks;
+      gW2 = mma(rows8(zp + off0, zp + off1), rows8(ap + off0, ap + off1), gW2);
+      if (ks & 1) {
+        const int kf = 4 * qi + (ks >> 1);
+        const unsigned short *yp = u.t.z1[qo].v + 512 * kf, *fp = t_f + 256 * kf + offf;
+        gW1 = mma(rows8(yp + off0, yp + off1), rows8(fp, fp + 64), gW1);
       }
     }
-    // transposed tiles for the products over rows
-#pragma unroll
-    for (int o = 0; o < 2; o++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const int u = 32 * o + crow(v, hh);
-        t_dz2[w][u * 32 + lr] = f2bf(dz2[o][v]);
-        t_a1[w][u * 32 + lr] = f2bf(a1[o][v]);
-        t_dz1[w][u * 32 + lr] = f2bf(a1[o][v] > 0.f ? dz1[o][v] : 0.f);
-      }
-    if (hh == 0) {
-#pragma unroll
-      for (int e = 0; e < 8; e++) t_f[w][e * 32 + lr] = fu[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int s2 = 0; s2 < 2; s2++) {
-      const int kofs = 16 * s2 + 8 * hh;
-      bf16x8_t ad[2], ba[2], a1t[2];
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        ad[q] = lds8(&t_dz2[w][(32 * q + lr) * 32 + kofs]);
-        ba[q] = lds8(&t_a1[w][(32 * q + lr) * 32 + kofs]);
-        a1t[q] = lds8(&t_dz1[w][(32 * q + lr) * 32 + kofs]);
-      }
-      u16x8_t zf = {0, 0, 0, 0, 0, 0, 0, 0};
-      const bf16x8_t bf = lr < 16 ? lds8(&t_f[w][lr * 32 + kofs]) : as_bf(zf);
-#pragma unroll
-      for (int o = 0; o < 2; o++)
-#pragma unroll
-        for (int i = 0; i < 2; i++) gW2[o][i] = mma(ad[o], ba[i], gW2[o][i]);
-#pragma unroll
-      for (int i = 0; i < 2; i++) gW1[i] = mma(a1t[i], bf, gW1[i]);
-    }
-    __syncthreads();
+    dev::lds_barrier();
+    fu = fn;
+    tv = tn;
   }
-  if (!TRAIN) return;
 
-  // block reduction, wave by wave in a fixed order, into LDS (reusing sp)
-  __syncthreads();
-  for (int i = threadIdx.x; i < kNP; i += blockDim.x) sp[i] = 0.f;
-  __syncthreads();
-  float lsw = lsum, gb3w = gb3;
+  // sums over the block's waves, each in a fixed order
+  float *dst = part + (int64_t)blockIdx.x * kMlpPartStride;
 #pragma unroll
-  for (int o = 0; o < 2; o++)
+  for (int v = 0; v < 16; v++) dst[OW2 + (32 * qo + crow(v, hh)) * kH + 32 * qi + lr] = gW2[v];
+#pragma unroll
+  for (int o = 0; o < 2; o++) {
+    const float x = sum_rows(gb2[o], lane), y = sum_rows(gw3[o], lane);
+    if ((lane & 16) == 0) {
+      red[0][w][32 * o + crow(lane & 15, hh)] = x;
+      red[1][w][32 * o + crow(lane & 15, hh)] = y;
+    }
+  }
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) {
+    lsum += __shfl_xor(lsum, m);
+    gb3 += __shfl_xor(gb3, m);
+  }
+  if (lane == 0) {
+    lred[0][w] = lsum;
+    lred[1][w] = gb3;
+  }
+  if (qi == 1 && lr <= kNF) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) u.sp[(32 * qo + crow(v, hh)) * (kNF + 1) + lr] = gW1[v];
+  }
+  __syncthreads();
+  if (qi == 0 && lr <= kNF) {
 #pragma unroll
     for (int v = 0; v < 16; v++) {
-      float x = gb2[o][v], y = gw3[o][v];
-#pragma unroll
-      for (int m = 1; m < 32; m <<= 1) {
-        x += __shfl_xor(x, m);
-        y += __shfl_xor(y, m);
-      }
-      gb2[o][v] = x;
-      gw3[o][v] = y;
+      const int un = 32 * qo + crow(v, hh);
+      dst[lr < kNF ? OW1 + un * kNF + lr : OB1 + un] = gW1[v] + u.sp[un * (kNF + 1) + lr];
     }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    lsw += __shfl_xor(lsw, m);
-    gb3w += __shfl_xor(gb3w, m);
   }
-  __shared__ float lred[kWaves];
-  for (int cur = 0; cur < kWaves; cur++) {
-    if (w == cur) {
-#pragma unroll
-      for (int o = 0; o < 2; o++)
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) sp[OW2 + (32 * o + crow(v, hh)) * kH + 32 * i + lr] += gW2[o][i][v];
-      if (lr < kNF) {
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) sp[OW1 + (32 * i + crow(v, hh)) * kNF + lr] += gW1[i][v];
-      } else if (lr == kNF) {
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) sp[OB1 + 32 * i + crow(v, hh)] += gW1[i][v];
-      }
-      if (lr == 0) {
-#pragma unroll
-        for (int o = 0; o < 2; o++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) {
-            sp[OB2 + 32 * o + crow(v, hh)] += gb2[o][v];
-            sp[OW3 + 32 * o + crow(v, hh)] += gw3[o][v];
-          }
-      }
-      if (lane == 0) {
-        sp[OB3] += gb3w;
-        lred[w] = lsw;
-      }
-    }
-    __syncthreads();
+  if (threadIdx.x < 2 * kH) {
+    const int q = threadIdx.x / kH, un = threadIdx.x % kH;
+    dst[(q ? OW3 : OB2) + un] = ((red[q][0][un] + red[q][1][un]) + red[q][2][un]) + red[q][3][un];
   }
-  float *dst = part + (int64_t)blockIdx.x * kMlpPartStride;
-  for (int i = threadIdx.x; i < kNP; i += blockDim.x) dst[i] = sp[i];
-  if (threadIdx.x == 0) dst[kNP] = ((lred[0] + lred[1]) + lred[2]) + lred[3];
+  if (threadIdx.x < 2) {
+    const float *l = lred[threadIdx.x];
+    dst[threadIdx.x ? OB3 : kNP] = ((l[0] + l[1]) + l[2]) + l[3];
+  }
 }
 
 // grad[i] = sum over blocks of part[b][i]; grad[kNP] = loss.  A workgroup
@@ -456,7 +558,7 @@ int mlp_grid(int64_t rows, int *cpb) {
 hipError_t launch_mlp_forward(const float *P, const uint16_t *F, int64_t rows, float *out, hipStream_t s) {
   int cpb;
   const int blocks = mlp_grid(rows, &cpb);
-  k_mlp<false><<<blocks, 256, 0, s>>>(P, F, nullptr, rows, cpb, 0.f, out, nullptr);
+  k_mlp_forward<<<blocks, 256, 0, s>>>(P, F, rows, cpb, out);
   return hipGetLastError();
 }
 
@@ -465,7 +567,7 @@ hipError_t launch_mlp_grad(const float *P, const uint16_t *F, const float *T, in
   int cpb;
   const int blocks = mlp_grid(rows, &cpb);
   const float inv_n = 1.0f / (float)rows;
-  k_mlp<true><<<blocks, 256, 0, s>>>(P, F, T, rows, cpb, inv_n, nullptr, part);
+  k_mlp_grad<<<blocks, 256, 0, s>>>(P, F, T, rows, cpb, inv_n, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_mlp_reduce<<<(kNP + 1 + 63) / 64, 64 * kRedWaves, 0, s>>>(part, blocks, inv_n, grad);
