@@ -84,9 +84,11 @@ __global__ __launch_bounds__(kSpThreads) void k_spfwd_part(const T *__restrict__
                                                            const int32_t *__restrict__ nlist,
                                                            const NodeState *S) {
   constexpr int VEC = XRaw<T>::VEC;
-  if (S && S->done) return;
-  const int rb = blockIdx.x, ch = blockIdx.y;
+  // both loads issued before the stop test waits
+  const int done = S ? S->done : 0;
   const int ns = *nlist;
+  if (done) return;
+  const int rb = blockIdx.x, ch = blockIdx.y;
   const int cs = (ns + B.nch - 1) / B.nch;
   const int t0 = ch * cs;
   const int t1 = (t0 + cs < ns) ? t0 + cs : ns;
@@ -133,35 +135,76 @@ __global__ __launch_bounds__(kSpThreads) void k_spfwd_part(const T *__restrict__
   for (int e = 0; e < VEC; e += 2) *reinterpret_cast<d2_t *>(part + e) = d2_t{acc[e], acc[e + 1]};
 }
 
+// U planes from c0 on of two rows, every load in flight together; those past
+// the end re-read the last plane (add_planes leaves them out).
+template <int U>
+__device__ __forceinline__ void load_planes(d2_t (&pv)[U], const double *__restrict__ part, int c0, int nch, int64_t n) {
+  static_assert(kFinRows == 2, "one 16-byte load per plane");
+#pragma unroll
+  for (int q = 0; q < U; q++) {
+    const int c = c0 + q < nch ? c0 + q : nch - 1;
+    pv[q] = *reinterpret_cast<const d2_t *>(part + (int64_t)c * n);
+  }
+}
+template <int U>
+__device__ __forceinline__ void add_planes(const d2_t (&pv)[U], int c0, int nch, double (&u)[kFinRows]) {
+#pragma unroll
+  for (int q = 0; q < U; q++) {
+    if (c0 + q < nch) {
+      u[0] += pv[q].x;
+      u[1] += pv[q].y;
+    }
+  }
+}
+
+// Bound by latency (a few dozen workgroups, one dependent chain each): the
+// node state, the first PL planes and the rows' vectors are loaded together
+// before the stop test is waited for, and the planes are added in chunk order.
+// PL = 32 where there are more than 16 chunks.  (Loads behind the stop test and
+// the state, 8 planes at a time and the remainder one by one took 6.6 us on the
+// 52 planes of a 4460 x 4735 design, this 5.6; 16 planes 5.75.)
+template <int PL>
 __global__ __launch_bounds__(kFinThreads) void k_spfwd_final(int64_t n, const double *__restrict__ y, ProbBufs B,
                                                              int32_t mode, const NodeState *S, double *u_out) {
   constexpr int VEC = kFinRows;
   __shared__ double red[(kFinThreads / 64) * 4];
-  if (S && S->done) return;
   const int fb = blockIdx.x;
   const int64_t row0 = ((int64_t)fb * kFinThreads + threadIdx.x) * VEC;
   const bool active = row0 < n;
+  const int64_t rowc = active ? row0 : 0;
+  int done = 0, improved = 0, bt = 0, acc = 0;
+  double mp = 0.0, t = 1.0;
+  if (S) {
+    done = S->done;
+    improved = S->improved;
+    bt = S->bt;
+    acc = S->bt_acc;
+    mp = S->mom;
+    t = S->t;
+  }
+  const double *part = B.part + rowc;
+  const int nch = B.nch;
+  d2_t pv[PL];
+  load_planes<PL>(pv, part, 0, nch, n);
+  const bool loss = mode == kSpLogistic || mode == kSpLsq;
+  double yv[VEC], ro[VEC], uo[VEC], up[VEC], uyo[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; e++) {
+    yv[e] = mode != kSpPlain ? y[rowc + e] : 0.0;
+    ro[e] = loss ? B.r[rowc + e] : 0.0;
+    uo[e] = loss ? B.ucur[rowc + e] : 0.0;
+    up[e] = loss ? B.uprev[rowc + e] : 0.0;
+    uyo[e] = loss ? B.uy[rowc + e] : 0.0;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (done) return;
   double u[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; e++) u[e] = 0.0;
-  if (active) {
-    const int nch = B.nch;
-    int c = 0;
-    for (; c + 8 <= nch; c += 8) {
-      d2_t pv[8];
-#pragma unroll
-      for (int q = 0; q < 8; q++) pv[q] = *reinterpret_cast<const d2_t *>(B.part + (int64_t)(c + q) * n + row0);
-#pragma unroll
-      for (int q = 0; q < 8; q++) {
-        u[0] += pv[q].x;
-        u[1] += pv[q].y;
-      }
-    }
-    for (; c < nch; c++) {
-      const d2_t pv = *reinterpret_cast<const d2_t *>(B.part + (int64_t)c * n + row0);
-      u[0] += pv.x;
-      u[1] += pv.y;
-    }
+  add_planes<PL>(pv, 0, nch, u);
+  for (int c = PL; c < nch; c += PL) {
+    load_planes<PL>(pv, part, c, nch, n);
+    add_planes<PL>(pv, c, nch, u);
   }
   double sums[3] = {0.0, 0.0, 0.0};
   if (mode == kSpPlain) {
@@ -174,34 +217,28 @@ __global__ __launch_bounds__(kFinThreads) void k_spfwd_final(int64_t n, const do
     // the product is G x over the Gram matrix and y holds b = X^T y: h = b - G x
     if (active)
 #pragma unroll
-      for (int e = 0; e < VEC; e++) B.h1[row0 + e] = y[row0 + e] - u[e];
+      for (int e = 0; e < VEC; e++) B.h1[row0 + e] = yv[e] - u[e];
     return;
   }
-  const int improved = S->improved;
   if (mode == kSpLsq) {
     // backtracking: X y of the pending trial as in the logistic branch below,
     // and its model-test remainder ||X x - X y||^2 row by row
-    const int bt = S->bt, acc = S->bt_acc;
-    const double mp = S->mom;
     if (active) {
 #pragma unroll
       for (int e = 0; e < VEC; e++) {
         const int64_t i = row0 + e;
-        if (improved) B.zbest[i] = 2.0 * B.r[i];
-        const double yi = y[i];
+        if (improved) B.zbest[i] = 2.0 * ro[e];
+        const double yi = yv[e];
         const double ri = yi - u[e];
         B.r[i] = ri;
         sums[0] += ri * ri;
         sums[1] += 2.0 * ri * yi - ri * ri;
         if (bt) {
-          const double uo = B.ucur[i];
-          double uyv;
+          double uyv = uyo[e];
           if (acc) {
-            uyv = (1.0 + mp) * uo - mp * B.uprev[i];
+            uyv = (1.0 + mp) * uo[e] - mp * up[e];
             B.uy[i] = uyv;
-            B.uprev[i] = uo;
-          } else {
-            uyv = B.uy[i];
+            B.uprev[i] = uo[e];
           }
           B.ucur[i] = u[e];
           const double du = u[e] - uyv;
@@ -210,34 +247,30 @@ __global__ __launch_bounds__(kFinThreads) void k_spfwd_final(int64_t n, const do
       }
     }
   } else {
-    const double t = S->t;
     const double mt = (t - 1.0) / fista_next_t(t);
     // backtracking: uprev holds X x of the last accepted iterate; when the
     // previous evaluation was accepted it moves there and the momentum point
     // y of the pending trial, X y = (1 + m) X x_k - m X x_{k-1} (m the step's
     // momentum, 0 after a restart), is kept in uy until the trial is decided
-    const int bt = S->bt, acc = S->bt_acc;
-    const double mp = S->mom;
     if (active) {
 #pragma unroll
       for (int e = 0; e < VEC; e++) {
         const int64_t i = row0 + e;
-        const double uo = B.ucur[i];
-        double up = uo;
+        double upv = uo[e], uyv = uyo[e];
         if (bt) {
-          up = B.uprev[i];
+          upv = up[e];
           if (acc) {
-            const double uyv = (1.0 + mp) * uo - mp * up;
+            uyv = (1.0 + mp) * uo[e] - mp * upv;
             B.uy[i] = uyv;
-            up = uo;
-            B.uprev[i] = up;
+            upv = uo[e];
+            B.uprev[i] = upv;
           }
         } else {
-          B.uprev[i] = uo;
+          B.uprev[i] = uo[e];
         }
         B.ucur[i] = u[e];
-        if (improved) B.zbest[i] = B.r[i];
-        const double yi = y[i];
+        if (improved) B.zbest[i] = ro[e];
+        const double yi = yv[e];
         const double z = yi * u[e];
         const double a = 1.0 / (1.0 + exp(z));
         B.r[i] = yi * a;
@@ -247,12 +280,11 @@ __global__ __launch_bounds__(kFinThreads) void k_spfwd_final(int64_t n, const do
           // F(X x) - F(X y) - <grad F(X y), X x - X y> of this row, with
           // a = -y_i (X y)_i and d = -y_i (X x - X y)_i: log1p(s expm1(d)) - s d,
           // s = 1 / (1 + exp(-a))
-          const double uyv = B.uy[i];
           const double aa = -yi * uyv, dd = -yi * (u[e] - uyv);
           const double sg = 1.0 / (1.0 + exp(-aa));
           sums[2] += log1p(sg * expm1(dd)) - sg * dd;
         }
-        const double sm = (1.0 + mt) * u[e] - mt * up;
+        const double sm = (1.0 + mt) * u[e] - mt * upv;
         B.gm[i] = -yi / (1.0 + exp(yi * sm));
       }
     }
@@ -285,7 +317,8 @@ hipError_t launch_spfwd(const Problem &P, const ProbBufs &B, const int32_t *idx,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_spfwd_final<<<(unsigned)B.nfin, kFinThreads, 0, s>>>(P.n, P.y, B, mode, S, u_out);
+  if (B.nch <= 16) k_spfwd_final<16><<<(unsigned)B.nfin, kFinThreads, 0, s>>>(P.n, P.y, B, mode, S, u_out);
+  else k_spfwd_final<32><<<(unsigned)B.nfin, kFinThreads, 0, s>>>(P.n, P.y, B, mode, S, u_out);
   return hipGetLastError();
 }
 
