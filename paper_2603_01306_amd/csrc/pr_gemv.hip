@@ -21,6 +21,19 @@
 // row steps in flight stayed slower than C = 8, one step (345 / 325 vs 313
 // us), and staging both right-hand sides in LDS per workgroup (one barrier
 // per 1024-row tile) cost 380-440 us.
+//
+// Designs with more columns than that (p > 10240 with one right-hand side, 4096
+// with two) whose right-hand sides fit half of a compute unit's LDS
+// run k_gemv_l instead: 512 workgroups of 8 waves, all resident, each with its
+// own LDS copy of the right-hand sides, whose waves walk the columns two at a
+// time.  The right-hand sides cost no L2 traffic, so two columns per wave
+// suffice; a wave's start is paid once and not per eight columns, and the last
+// round of workgroups, partly empty before, is gone.  A column's sum is formed in
+// the same order, whatever C.  FP32, two right-hand sides: 2300 x 89989 134 ->
+// 127 us (6.5 TB/s), 3000 x 20000 44.8 -> 38.4, 2000 x 8192 11.0 -> 9.9, 4460 x
+// 4735 21.2 -> 19.0; one: 2300 x 89989 130 -> 124, BF16 10000 x 40000 148 -> 123.
+// With C = 2 waves enough for one round (1000 x 4000) it is slower, 4.8 -> 5.2 us,
+// and so it is with one right-hand side at p = 4735 (15.0 -> 16.4).
 // Algorithmic bytes per launch: n*p*sizeof(X) + 8n per right-hand side + 8p
 // per output.
 #include "pr_device.h"
@@ -78,7 +91,8 @@ __device__ __forceinline__ double reduce_cols(double (&v)[C]) {
 // sums).  Each pass loads eight entries per thread before using them.
 // Writes S->gval and S->indom.  Runs as one extra workgroup of the X^T r
 // product, which follows the column-list product of the same iterate and
-// outlasts this evaluation.
+// outlasts this evaluation.  The workgroup may have more threads than NTH: they
+// take part in the barriers only, so the sums do not depend on its size.
 template <int NTH>
 __device__ void list_values(const NodeParams *__restrict__ P, const int32_t *__restrict__ idx,
                             const double *__restrict__ val, int ns, NodeState *S) {
@@ -87,8 +101,10 @@ __device__ void list_values(const NodeParams *__restrict__ P, const int32_t *__r
   __shared__ double red[NWS * 4];
   const int kbar = P->kbar;
   const double M = P->M;
+  const bool on = threadIdx.x < NTH;
+  const int first = on ? (int)threadIdx.x : ns;
   double v[4] = {0.0, 0.0, 0.0, 0.0};  // theta, sum_{J1} x^2, max |x| off J0, max |x| on J0
-  for (int t0 = threadIdx.x; t0 < ns; t0 += U * NTH) {
+  for (int t0 = first; t0 < ns; t0 += U * NTH) {
     int32_t it[U];
     double xv[U];
 #pragma unroll
@@ -113,7 +129,7 @@ __device__ void list_values(const NodeParams *__restrict__ P, const int32_t *__r
   v[1] = wave_sum(v[1]);
   v[2] = wave_max(v[2]);
   v[3] = wave_max(v[3]);
-  if (lane_id() == 0) {
+  if (on && lane_id() == 0) {
 #pragma unroll
     for (int k = 0; k < 4; k++) red[wave_id() * 4 + k] = v[k];
   }
@@ -140,7 +156,7 @@ __device__ void list_values(const NodeParams *__restrict__ P, const int32_t *__r
     a1 = NAN;
     for (int round = 0; round <= kbar + 1; round++) {
       double r[3] = {0.0, 0.0, 0.0};  // #{q > s}, sum of q <= s, sum of q^2 over q > s
-      for (int t0 = threadIdx.x; t0 < ns; t0 += U * NTH) {
+      for (int t0 = first; t0 < ns; t0 += U * NTH) {
         int32_t it[U];
         double xv[U];
 #pragma unroll
@@ -161,7 +177,20 @@ __device__ void list_values(const NodeParams *__restrict__ P, const int32_t *__r
           }
         }
       }
-      block_sum<NTH, 3>(r, red);
+#pragma unroll
+      for (int k = 0; k < 3; k++) r[k] = wave_sum(r[k]);
+      __syncthreads();
+      if (on && lane_id() == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) red[wave_id() * 3 + k] = r[k];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 3; k++) {
+        double t = 0.0;
+        for (int w = 0; w < NWS; w++) t += red[w * 3 + k];
+        r[k] = t;
+      }
       if (r[0] == prevK || r[0] >= K) {
         a1 = 0.5 * (r[2] + (K - r[0]) * sv * sv);
         break;
@@ -204,10 +233,6 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_t(const T *__restrict__ X
     bx--;
   }
   constexpr int VEC = XLoad<T>::VEC;
-#ifndef PR_GEMVT_STEPS
-#define PR_GEMVT_STEPS 1
-#endif
-  constexpr int U = PR_GEMVT_STEPS;  // row steps in flight
   const int lane = lane_id();
   const int64_t col0 = ((int64_t)bx * (kGemvThreads / 64) + wave_id()) * C;
   if (col0 >= p) return;
@@ -232,29 +257,6 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_t(const T *__restrict__ X
   // then the right-hand side once the first column has arrived) measured
   // faster: 316 vs 340 us on a 32768 x 16384 FP32 design, 89.8 vs 94.0 on
   // 16000 x 16000 BF16, equal on 16384 x 8192.
-  for (; i + (U - 1) * step + VEC <= n; i += U * step) {
-    typename XLoad<T>::raw_t xr[U][C];
-    double rv[U][NRHS][VEC];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-#pragma unroll
-      for (int q = 0; q < C; q++) xr[u][q] = XLoad<T>::raw(c[q] + i + u * step);
-      load_rhs<VEC>(r1, i + u * step, rv[u][0]);
-      if (NRHS > 1) load_rhs<VEC>(r2, i + u * step, rv[u][NRHS - 1]);
-    }
-    if constexpr (NRHS > 1) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < U; u++)
-#pragma unroll
-      for (int q = 0; q < C; q++) {
-        double xv[VEC];
-        XLoad<T>::cvt(xr[u][q], xv);
-#pragma unroll
-        for (int h = 0; h < NRHS; h++)
-#pragma unroll
-          for (int e = 0; e < VEC; e++) acc[h][q] = fma(xv[e], rv[u][h][e], acc[h][q]);
-      }
-  }
   for (; i + VEC <= n; i += step) {
     typename XLoad<T>::raw_t xr[C];
     double rv[NRHS][VEC];
@@ -286,6 +288,83 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_t(const T *__restrict__ X
   }
 }
 
+// The same product for many columns and right-hand sides of at most
+// kGemvLdsRows entries together (see the head of this file).
+constexpr int kGemvLThreads = 512;
+constexpr int kGemvLBlocks = 512;   // two workgroups per compute unit
+constexpr int kGemvLdsRows = 10176; // 79.5 KB: two workgroups with list_values' sums share 160 KB
+
+template <typename T, int NRHS>
+__global__ __launch_bounds__(kGemvLThreads) void k_gemv_l(const T *__restrict__ X, int64_t n, int64_t p,
+                                                          const double *__restrict__ r1,
+                                                          const double *__restrict__ r2,
+                                                          double *__restrict__ h1,
+                                                          double *__restrict__ h2,
+                                                          const int32_t *__restrict__ done,
+                                                          const NodeParams *__restrict__ node, NodeState *S,
+                                                          const int32_t *__restrict__ sidx,
+                                                          const double *__restrict__ sval,
+                                                          const int32_t *__restrict__ nlist,
+                                                          const double *__restrict__ dsum, int nfin) {
+  constexpr int VEC = XLoad<T>::VEC, C = 2, NWG = kGemvLThreads / 64;
+  __shared__ __align__(16) double rl[kGemvLdsRows];
+  if (done && *done) return;
+  if (dsum && S->bt && S->iter > 0 && !bt_accept(bt_remainder(dsum, nfin), S->L, S->dxy, node->Lmax)) return;
+  int bx = (int)blockIdx.x, nb = (int)gridDim.x;
+  if (node) {
+    if (bx == 0) {
+      list_values<kGemvThreads>(node, sidx, sval, *nlist, S);
+      return;
+    }
+    bx--;
+    nb--;
+  }
+  for (int i = 2 * (int)threadIdx.x; i < (int)n; i += 2 * kGemvLThreads) {
+    *reinterpret_cast<d2_t *>(rl + i) = *reinterpret_cast<const d2_t *>(r1 + i);
+    if (NRHS > 1) *reinterpret_cast<d2_t *>(rl + n + i) = *reinterpret_cast<const d2_t *>(r2 + i);
+  }
+  __syncthreads();
+  const int lane = lane_id();
+  const int64_t step = 64 * VEC;
+  for (int64_t col0 = ((int64_t)bx * NWG + wave_id()) * C; col0 < p; col0 += (int64_t)nb * NWG * C) {
+    const T *c[C];
+#pragma unroll
+    for (int q = 0; q < C; q++) c[q] = X + ((col0 + q < p) ? col0 + q : p - 1) * n;
+    double acc[NRHS][C];
+#pragma unroll
+    for (int h = 0; h < NRHS; h++)
+#pragma unroll
+      for (int q = 0; q < C; q++) acc[h][q] = 0.0;
+    for (int64_t i = (int64_t)lane * VEC; i + VEC <= n; i += step) {
+      typename XLoad<T>::raw_t xr[C];
+      double rv[NRHS][VEC];
+#pragma unroll
+      for (int q = 0; q < C; q++) xr[q] = XLoad<T>::raw(c[q] + i);
+      load_rhs<VEC>(rl, i, rv[0]);
+      if (NRHS > 1) load_rhs<VEC>(rl + n, i, rv[NRHS - 1]);
+#pragma unroll
+      for (int q = 0; q < C; q++) {
+        double xv[VEC];
+        XLoad<T>::cvt(xr[q], xv);
+#pragma unroll
+        for (int h = 0; h < NRHS; h++)
+#pragma unroll
+          for (int e = 0; e < VEC; e++) acc[h][q] = fma(xv[e], rv[h][e], acc[h][q]);
+      }
+    }
+    const int64_t col = col0 + (lane >> 5);
+    const bool writer = (lane & 31) == 0 && col < p;
+    {
+      const double t = reduce_cols(acc[0]);
+      if (writer) h1[col] = t;
+    }
+    if (NRHS > 1) {
+      const double t = reduce_cols(acc[NRHS - 1]);
+      if (writer) h2[col] = t;
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_gemv_t(const Problem &P, const double *r1, const double *r2, double *h1, double *h2,
@@ -296,6 +375,32 @@ hipError_t launch_gemv_t(const Problem &P, const double *r1, const double *r2, d
   if (dsum && !node) return hipErrorInvalidValue;
   const bool two = (r2 != nullptr);
   const int cols = gemv_cols(two ? 2 : 1, P.p);
+  if (cols > 2 && P.n * (two ? 2 : 1) <= kGemvLdsRows) {
+    // as many workgroups as are resident at once, the list's one included, and
+    // every wave with the same number of column pairs or one less
+    const int64_t cap = kGemvLBlocks - (node ? 1 : 0), need = (P.p + 15) / 16;
+    const int64_t rounds = (need + cap - 1) / cap;
+    const unsigned lgrid = (unsigned)((need + rounds - 1) / rounds) + (node ? 1u : 0u);
+#define PR_GEMVL(T, R)                                                                                              \
+  k_gemv_l<T, R><<<lgrid, kGemvLThreads, 0, s>>>((const T *)P.X, P.n, P.p, r1, r2, h1, h2, done, node, S, sidx, sval, \
+                                                 nlist, dsum, nfin)
+    switch (P.xdt) {
+      case kF32:
+        if (two) PR_GEMVL(float, 2);
+        else PR_GEMVL(float, 1);
+        break;
+      case kF64:
+        if (two) PR_GEMVL(double, 2);
+        else PR_GEMVL(double, 1);
+        break;
+      default:
+        if (two) PR_GEMVL(uint16_t, 2);
+        else PR_GEMVL(uint16_t, 1);
+        break;
+    }
+#undef PR_GEMVL
+    return hipGetLastError();
+  }
   const int cols_per_block = (kGemvThreads / 64) * cols;
   dim3 grid((unsigned)((P.p + cols_per_block - 1) / cols_per_block) + (node ? 1u : 0u));
   dim3 block(kGemvThreads);
