@@ -109,10 +109,14 @@ struct pr_ctx {
   bool cg_own = false, gram_batch_ok = false;
   uint32_t *bstp = nullptr;        // [cap][stpw] packed node status of the batch
   std::vector<uint32_t> h_bstp;
-  int32_t *h_active = nullptr;    // pinned, 2 slots
-  hipGraphExec_t bgexec = nullptr;
-  int32_t bgraph_units = 0, bgraph_m = 0;
-  int64_t bgraph_kp = 0, bgraph_ku = 0;
+  std::vector<int8_t> h_bst;       // [m][p] node statuses of the batch
+  int32_t *h_active = nullptr;    // pinned
+  // batch iteration graphs: [0] over all columns, [1] over a support union
+  struct BatchGraph {
+    hipGraphExec_t exec = nullptr;
+    int32_t units = 0, m = 0;
+    int64_t kp = 0, ku = 0;
+  } bgraph[2];
   // support-union compaction of the batched product with the iterates (built per pr_solve_batch)
   bool union_on = false;
   int64_t ku = 0, kp = 0;           // union size, padded to the GEMM's reduction granule
@@ -161,15 +165,17 @@ namespace {
 void pack_status(const std::vector<int8_t> &st, uint32_t *w, size_t words) {
   const int64_t p = (int64_t)st.size();
   const int64_t T = kNodeThreads;
-  for (size_t k = 0; k < words; k++) {
-    const int64_t q = (int64_t)k / T, t = (int64_t)k % T;
-    uint32_t v = 0u;
+  // by runs of T coordinates, which share their bits' place and have a word each
+  for (int64_t q = 0; q * T < (int64_t)words; q++) {
+    uint32_t *wq = w + q * T;
+    for (int64_t t = 0; t < T; t++) wq[t] = 0u;
     for (int i = 0; i < 16; i++) {
-      const int64_t j = t + (16 * q + i) * T;
-      const uint32_t code = (j < p) ? (uint32_t)st[(size_t)j] : 3u;
-      v |= code << (2 * i);
+      const int64_t j0 = (16 * q + i) * T;
+      const int64_t in = p - j0 < 0 ? 0 : (p - j0 < T ? p - j0 : T);
+      const int8_t *s = st.data() + (in ? j0 : 0);
+      for (int64_t t = 0; t < in; t++) wq[t] |= (uint32_t)s[t] << (2 * i);
+      for (int64_t t = in; t < T; t++) wq[t] |= 3u << (2 * i);
     }
-    w[k] = v;
   }
 }
 
@@ -177,7 +183,8 @@ void free_ctx(pr_ctx *c) {
   if (!c) return;
   if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
   if (c->gtail) (void)hipGraphExecDestroy(c->gtail);
-  if (c->bgexec) (void)hipGraphExecDestroy(c->bgexec);
+  for (auto &b : c->bgraph)
+    if (b.exec) (void)hipGraphExecDestroy(b.exec);
   if (c->vgexec) (void)hipGraphExecDestroy(c->vgexec);
   {
     void *vb[] = {c->d_ac, c->d_lx, c->ab.xb, c->ab.gb, c->ab.yb, c->ab.xc, c->ab.yc, c->ab.z, c->ab.sidx2,
@@ -738,7 +745,7 @@ int alloc_batch(pr_ctx *c) {
   ok = ok && dalloc(&c->d_rowmap, NrMax) == hipSuccess && dalloc(&c->d_split, 12) == hipSuccess;
   ok = ok && dalloc(&c->d_ftab, kTuneTables * kTuneMax) == hipSuccess;
   ok = ok && hipHostMalloc((void **)&c->h_bstate, sizeof(NodeState) * cap, hipHostMallocDefault) == hipSuccess;
-  ok = ok && hipHostMalloc((void **)&c->h_active, 2 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
+  ok = ok && hipHostMalloc((void **)&c->h_active, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
   if (!ok) return PR_ENOMEM;
   ok = hipMemsetAsync(c->Bx, 0, sizeof(double) * NrMax * p, c->stream) == hipSuccess;
   ok = ok && hipMemsetAsync(c->Rd, 0, sizeof(double) * NrMaxT * n, c->stream) == hipSuccess;
@@ -905,14 +912,18 @@ hipError_t enqueue_batch_unit(pr_ctx *c, int32_t m, hipStream_t s) {
   return launch_batch_step(c->d_bprm, c->d_bstate, batch_bufs(c, m), p, s);
 }
 
-int ensure_batch_graph(pr_ctx *c, int32_t m, int32_t units) {
+// The captured iterations of a batch of m nodes: the graph over all columns is
+// kept beside the one over the current union, so that the next solve's first
+// launch finds it (a capture of 32 units takes 0.65 ms).
+int ensure_batch_graph(pr_ctx *c, int32_t m, int32_t units, hipGraphExec_t *out) {
   // the union sizes are kernel arguments of the captured launches
   const int64_t kp = c->union_on ? c->kp : 0, ku = c->union_on ? c->ku : 0;
-  if (c->bgexec && c->bgraph_units == units && c->bgraph_m == m && c->bgraph_kp == kp && c->bgraph_ku == ku)
-    return PR_OK;
-  if (c->bgexec) {
-    (void)hipGraphExecDestroy(c->bgexec);
-    c->bgexec = nullptr;
+  pr_ctx::BatchGraph &b = c->bgraph[c->union_on ? 1 : 0];
+  *out = b.exec;
+  if (b.exec && b.units == units && b.m == m && b.kp == kp && b.ku == ku) return PR_OK;
+  if (b.exec) {
+    (void)hipGraphExecDestroy(b.exec);
+    b.exec = *out = nullptr;
   }
   hipGraph_t g = nullptr;
   PR_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
@@ -923,16 +934,17 @@ int ensure_batch_graph(pr_ctx *c, int32_t m, int32_t units) {
     if (g) (void)hipGraphDestroy(g);
     return PR_EDEVICE;
   }
-  e = hipGraphInstantiate(&c->bgexec, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&b.exec, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) {
-    c->bgexec = nullptr;
+    b.exec = nullptr;
     return PR_EDEVICE;
   }
-  c->bgraph_units = units;
-  c->bgraph_m = m;
-  c->bgraph_kp = kp;
-  c->bgraph_ku = ku;
+  b.units = units;
+  b.m = m;
+  b.kp = kp;
+  b.ku = ku;
+  *out = b.exec;
   return PR_OK;
 }
 
@@ -1444,11 +1456,11 @@ int pr_ctx_enable_gram(pr_ctx *c) {
       *ge = nullptr;
     }
   c->graph_units = 0;
-  if (c->bgexec) {
-    (void)hipGraphExecDestroy(c->bgexec);
-    c->bgexec = nullptr;
-    c->bgraph_units = 0;
-  }
+  for (auto &b : c->bgraph)
+    if (b.exec) {
+      (void)hipGraphExecDestroy(b.exec);
+      b.exec = nullptr;
+    }
   return PR_OK;
 }
 
@@ -2226,9 +2238,20 @@ static int stage_batch_nodes(pr_ctx *c, const pr_node *nodes, const std::vector<
       pp.L0 = opts.L0 > 0.0 ? fmin(opts.L0, Lcap) : Lcap / 16.0;
       pp.ls_c = opts.acfgm_c;
     }
-    PR_TRY(hipMemcpyAsync(c->bstatus + (int64_t)q * p, sts[(size_t)i].data(), (size_t)p, hipMemcpyHostToDevice, s));
-    if (B0) PR_TRY(hipMemcpyAsync(c->bxbest + (int64_t)q * p, B0 + (int64_t)i * p, sizeof(double) * p,
-                                  hipMemcpyDeviceToDevice, s));
+  }
+  // one upload for all statuses, and the starting points by runs of neighbouring
+  // nodes: a copy per node and kind cost 13 us each
+  c->h_bst.resize((size_t)mb * (size_t)p);
+  for (int32_t q = 0; q < mb; q++)
+    memcpy(c->h_bst.data() + (size_t)q * p, sts[(size_t)slot_of[(size_t)q]].data(), (size_t)p);
+  PR_TRY(hipMemcpyAsync(c->bstatus, c->h_bst.data(), c->h_bst.size(), hipMemcpyHostToDevice, s));
+  for (int32_t q = 0; B0 && q < mb;) {
+    const int32_t i = slot_of[(size_t)q];
+    int32_t cnt = 1;
+    while (q + cnt < mb && slot_of[(size_t)(q + cnt)] == i + cnt) cnt++;
+    PR_TRY(hipMemcpyAsync(c->bxbest + (int64_t)q * p, B0 + (int64_t)i * p, sizeof(double) * cnt * p,
+                          hipMemcpyDeviceToDevice, s));
+    q += cnt;
   }
   {
     const size_t W = c->stp_words;
@@ -2303,56 +2326,67 @@ int pr_solve_batch(pr_ctx *c, const pr_node *nodes, int32_t m, const pr_opts *op
   const double L_init = bt ? (opts.L0 > 0.0 ? fmin(opts.L0, L) : L / 16.0) : L;
   PR_TRY(launch_batch_init(c->d_bprm, c->d_bstate, bb, B0 ? c->bxbest : nullptr, L_init, p, s));
   c->union_on = false;
-  int rc = ensure_batch_graph(c, mb, opts.check_every);
-  if (rc != PR_OK) return rc;
-  auto issue = [&](int slot) -> hipError_t {
-    hipError_t e = hipGraphLaunch(c->bgexec, s);
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(&c->h_active[slot], c->d_active, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return e;
-    return hipEventRecord(c->ev[slot], s);
+  // Evaluations the batch can still use: without backtracking the iteration
+  // budget bounds them (the evaluation of iterate max_iter stops every node), so
+  // no launch goes past it and the last, shorter one is enqueued as it is; with
+  // it, rejected trials take evaluations beyond the budget.
+  const int64_t budget =
+      bt ? 2 * ((int64_t)opts.max_iter / opts.check_every + 3) * opts.check_every : (int64_t)opts.max_iter + 1;
+  int64_t issued = 0;
+  // the graph of the next launch, when that is a full one
+  hipGraphExec_t graph = nullptr;
+  auto ready = [&]() -> int {
+    return budget - issued >= opts.check_every ? ensure_batch_graph(c, mb, opts.check_every, &graph) : PR_OK;
   };
-  // backtracking: rejected trials take evaluations beyond the iteration budget
-  const int64_t max_launches = ((int64_t)opts.max_iter / opts.check_every + 3) * (bt ? 2 : 1);
-  int64_t launched = 0;
-  PR_TRY(issue(0));
-  launched++;
-  if (launched < max_launches) {
+  int rc = ready();
+  if (rc != PR_OK) return rc;
+  // One launch at a time: the host's look at the number of active nodes between
+  // two of them leaves the device idle for 31 us, while every unit launched after
+  // the last node stopped costs 27 us (48 logistic nodes of 8192 x 4096 that
+  // stop after 50 units ran 96 with a second launch queued behind: 15.7 -> 15.0 ms).
+  int32_t active = mb;
+  auto launch = [&]() -> hipError_t {
+    hipError_t e = hipSuccess;
+    const int64_t left = budget - issued;
+    if (left >= opts.check_every) {
+      e = hipGraphLaunch(graph, s);
+      issued += opts.check_every;
+    } else {
+      for (int64_t i = 0; i < left && e == hipSuccess; i++) e = enqueue_batch_unit(c, mb, s);
+      issued += left;
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(c->h_active, c->d_active, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    active = *c->h_active;
+    return e;
+  };
+  PR_TRY(launch());
+  if (active > 0 && issued < budget) {
     // after the first launch the supports have settled: compact the product
     // with the iterates to their union for the remaining launches
-    PR_TRY(hipEventSynchronize(c->ev[0]));
-    if (c->h_active[0] > 0) {
-      bool changed = false;
-      rc = build_union(c, mb, true, &changed);
-      if (rc != PR_OK) return rc;
-      if (changed) {
-        rc = ensure_batch_graph(c, mb, opts.check_every);
-        if (rc != PR_OK) return rc;
-      }
-    }
+    bool changed = false;
+    rc = build_union(c, mb, true, &changed);
+    if (rc == PR_OK && changed) rc = ready();
+    if (rc != PR_OK) return rc;
   }
-  PR_TRY(issue(1));
-  launched++;
   int rebuilds = 0;
   // tail handoff: once the nodes still iterating are so few that one node at a
-  // time is cheaper per iteration (batch_pays), the batch stops and they
-  // continue on the single-node path from their current iterates
+  // time is cheaper per iteration (batch_pays), the batch stops after one more
+  // launch and they continue on the single-node path from their current iterates
   bool handoff = false;
   const bool may_hand_off = !(c->debug & PR_DEBUG_FORCE_BATCH);
-  for (int64_t k = 0;; k++) {
-    const int slot = (int)(k & 1);
-    PR_TRY(hipEventSynchronize(c->ev[slot]));
-    if (c->h_active[slot] <= 0) break;
-    if (launched >= max_launches) break;
-    if (may_hand_off && !batch_pays(c, c->h_active[slot])) {
+  while (active > 0 && issued < budget) {
+    const int32_t before = active;
+    PR_TRY(launch());
+    if (active <= 0 || issued >= budget) break;
+    if (may_hand_off && !batch_pays(c, before)) {
       handoff = true;
       break;
     }
     if (c->union_on && rebuilds < kUnionRebuilds) {
-      // supports still move in the first launches: once the other launch is
-      // done, join the coordinates that left the union when there are more
-      // than one per four nodes (each costs one matrix column per iteration)
-      PR_TRY(hipStreamSynchronize(s));
+      // supports still move in the first launches: join the coordinates that
+      // left the union when there are more than one per four nodes (each costs
+      // one matrix column per iteration)
       std::vector<int32_t> oc((size_t)mb);
       PR_TRY(hipMemcpy(oc.data(), c->d_ocnt, sizeof(int32_t) * mb, hipMemcpyDeviceToHost));
       int64_t nout = 0;
@@ -2361,17 +2395,11 @@ int pr_solve_batch(pr_ctx *c, const pr_node *nodes, int32_t m, const pr_opts *op
       if (4 * nout > mb) {
         bool changed = false;
         rc = build_union(c, mb, false, &changed);
+        if (rc == PR_OK && changed) rc = ready();
         if (rc != PR_OK) return rc;
-        if (changed) {
-          rc = ensure_batch_graph(c, mb, opts.check_every);
-          if (rc != PR_OK) return rc;
-        } else {
-          rebuilds = kUnionRebuilds;  // nothing new fits: keep this union
-        }
+        if (!changed) rebuilds = kUnionRebuilds;  // nothing new fits: keep this union
       }
     }
-    PR_TRY(issue(slot));
-    launched++;
   }
   PR_TRY(hipStreamSynchronize(s));
   PR_TRY(hipMemcpy(c->h_bstate, c->d_bstate, sizeof(NodeState) * mb, hipMemcpyDeviceToHost));
@@ -2397,6 +2425,16 @@ int pr_solve_batch(pr_ctx *c, const pr_node *nodes, int32_t m, const pr_opts *op
   std::vector<double> lbs, ubs;
   rc = certify_batch(c, mb, lbs, ubs);
   if (rc != PR_OK) return rc;
+  // iterates of confirmed nodes go out in runs of neighbours, one copy each (256
+  // copies one by one: 3 ms of a 119 ms batch)
+  int32_t run_q = 0, run_i = 0, run_n = 0;
+  auto flush = [&]() -> hipError_t {
+    const int32_t cnt = run_n;
+    run_n = 0;
+    if (cnt == 0) return hipSuccess;
+    return hipMemcpyAsync(B_out + (int64_t)run_i * p, c->bxbest + (int64_t)run_q * p, sizeof(double) * cnt * p,
+                          hipMemcpyDeviceToDevice, s);
+  };
   for (int32_t q = 0; q < mb; q++) {
     const int32_t i = slot_of[(size_t)q];
     const NodeState &hs = c->h_bstate[q];
@@ -2419,7 +2457,14 @@ int pr_solve_batch(pr_ctx *c, const pr_node *nodes, int32_t m, const pr_opts *op
       r.restarts = hs.restarts;
       r.trials = hs.trials;
       r.status = st;
-      if (B_out) PR_TRY(hipMemcpyAsync(B_out + (int64_t)i * p, xq, sizeof(double) * p, hipMemcpyDeviceToDevice, s));
+      if (B_out) {
+        if (run_n > 0 && (q != run_q + run_n || i != run_i + run_n)) PR_TRY(flush());
+        if (run_n == 0) {
+          run_q = q;
+          run_i = i;
+        }
+        run_n++;
+      }
     } else {
       // the single-node FP64 path from the node's iterate: a fresh budget after
       // an unconfirmed decision, the rest of the budget after a handoff
@@ -2434,6 +2479,7 @@ int pr_solve_batch(pr_ctx *c, const pr_node *nodes, int32_t m, const pr_opts *op
       r.trials += hs.trials;
     }
   }
+  PR_TRY(flush());
   PR_TRY(hipStreamSynchronize(s));
   return PR_OK;
 }
