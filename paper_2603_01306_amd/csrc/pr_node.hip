@@ -1587,6 +1587,38 @@ __global__ __launch_bounds__(NT) void k_batch_init(const NodeParams *__restrict_
   }
 }
 
+// v[i] += the split planes 1 .. KS - 1 of entry tid + (E0 + i) NT, in plane
+// order.  The planes were written on other XCDs, so each is a round trip past the
+// L2; U of them are in flight together.  One plane at a time the step of 48
+// logistic nodes (p = 4096, 8 planes, two rows each) took 76 us, so 53.  (The
+// second row's planes summed at the start as well, to arrive during the dual
+// evaluation: no faster.)
+template <int EPT, int E0, int N>
+__device__ __forceinline__ void add_planes(double (&v)[N], const double *__restrict__ H, int KS, int64_t stride,
+                                           int64_t p) {
+  constexpr int U = EPT >= 32 ? 1 : 32 / EPT;
+  const int tid = threadIdx.x;
+  for (int z = 1; z < KS; z += U) {
+    double t[U][N];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int zc = z + u < KS ? z + u : KS - 1;
+#pragma unroll
+      for (int i = 0; i < N; i++) {
+        const uint32_t j = (uint32_t)(tid + (E0 + i) * NT);
+        t[u][i] = j < (uint32_t)p ? H[zc * stride + j] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      if (z + u < KS) {
+#pragma unroll
+        for (int i = 0; i < N; i++) v[i] += t[u][i];
+      }
+    }
+  }
+}
+
 // GRAM: the batch runs in Gram mode (bb.gb set); a compile-time variant, so
 // that the other batches carry none of its loads in registers.
 template <int EPT, bool GRAM>
@@ -1642,13 +1674,7 @@ __global__ __launch_bounds__(NT) void k_batch_step(const NodeParams *__restrict_
       return j < (uint32_t)p ? xc[j] : 0.0;
     }
   };
-  for (int z = 1; z < KS; z++) {
-#pragma unroll
-    for (int e = 0; e < EPT; e++) {
-      const uint32_t j = (uint32_t)(tid + e * NT);
-      if (j < (uint32_t)p) h[e] += Hn[z * stride + j];
-    }
-  }
+  add_planes<EPT, 0, EPT>(h, Hn, KS, stride, p);
   // loss sums of the residual blocks: lane-parallel loads, fixed-order wave sums
   double Fk = 0.0, negconj = 0.0;
   if (!gb) {
@@ -1932,15 +1958,7 @@ __global__ __launch_bounds__(NT) void k_batch_step(const NodeParams *__restrict_
       xq[i] = in ? xn[j] : 0.0;
       hq[i] = in ? (lsq ? hp[j] : H2[j]) : 0.0;
     }
-    if (!lsq) {
-      for (int z = 1; z < KS; z++) {
-#pragma unroll
-        for (int i = 0; i < HE; i++) {
-          const uint32_t j = (uint32_t)(tid + (E0 + i) * NT);
-          if (j < (uint32_t)p) hq[i] += H2[z * stride + j];
-        }
-      }
-    }
+    if (!lsq) add_planes<EPT, E0, HE>(hq, H2, KS, stride, p);
 #pragma unroll
     for (int i = 0; i < HE; i++) {
       const int e = E0 + i;
