@@ -7,7 +7,7 @@
 //               registers and every lane keeps 16 independent 16-byte
 //               non-temporal loads in flight (2 to 8 rows per lane),
 //               converted to FP64 at the FMA; the chunk's last columns form
-//               one masked round of 16.  Writes its partial sums to
+//               one masked round of 4, 8 or 16.  Writes its partial sums to
 //               part[chunk][n].
 // k_spfwd_final grid over rows: sums the chunk partials in chunk order (so the
 //               result does not depend on scheduling) and runs the epilogue:
@@ -52,26 +52,36 @@ struct XRaw<uint16_t> {
   }
 };
 
-// The chunk's last, partial round of kSpInFlight column loads (16 bytes per
-// lane each) for list entries t .. t1 - 1: the slots at or past t1 re-read
-// the chunk's last column, which sp_use_r then weights by zero.
-template <typename T>
-__device__ __forceinline__ void sp_issue_tail(u4_t (&raw)[kSpInFlight], const T *__restrict__ X, int64_t n,
-                                              int64_t row0, const int32_t *__restrict__ idx, int t, int t1) {
+// The chunk's last, partial round: list entries t .. t1 - 1, at most U columns
+// (16 bytes per lane each) loaded together; the slots at or past t1 re-read the
+// chunk's last column and are weighted by zero.  A sparse iterate leaves few
+// columns per chunk, so the rounds come in three sizes (16 slots for one column:
+// 1% slower on a 4460 x 4735 child and on the 500 x 200 root; 24 or 32 columns in
+// flight 1-3% slower on both and on the 16384 x 8192 root).
+template <typename T, int U>
+__device__ __forceinline__ void sp_tail(double (&acc)[XRaw<T>::VEC], const T *__restrict__ X, int64_t n, int64_t row0,
+                                        const int32_t *__restrict__ idx, const double *__restrict__ val, int t, int t1) {
+  u4_t raw[U];
 #pragma unroll
-  for (int c = 0; c < kSpInFlight; c++) {
+  for (int c = 0; c < U; c++) {
     const int tc = (t + c < t1) ? t + c : t1 - 1;
     const T *col = X + (int64_t)(idx[tc] & kIdxMask) * n;   // wave-uniform column base
     raw[c] = __builtin_nontemporal_load(reinterpret_cast<const u4_t *>(col + row0));
   }
+#pragma unroll
+  for (int c = 0; c < U; c++) {
+    const double w = (t + c < t1) ? val[t + c < t1 ? t + c : t1 - 1] : 0.0;
+#pragma unroll
+    for (int e = 0; e < XRaw<T>::VEC; e++) acc[e] = fma(XRaw<T>::at(raw[c], e), w, acc[e]);
+  }
 }
 
-template <typename T, bool FULL>
+template <typename T>
 __device__ __forceinline__ void sp_use_r(const u4_t (&raw)[kSpInFlight], double (&acc)[XRaw<T>::VEC],
-                                         const double *__restrict__ val, int t, int t1) {
+                                         const double *__restrict__ val, int t) {
 #pragma unroll
   for (int c = 0; c < kSpInFlight; c++) {
-    const double w = FULL ? val[t + c] : ((t + c < t1) ? val[t + c < t1 ? t + c : t1 - 1] : 0.0);
+    const double w = val[t + c];
 #pragma unroll
     for (int e = 0; e < XRaw<T>::VEC; e++) acc[e] = fma(XRaw<T>::at(raw[c], e), w, acc[e]);
   }
@@ -120,16 +130,14 @@ __global__ __launch_bounds__(kSpThreads) void k_spfwd_part(const T *__restrict__
 #pragma unroll
         for (int c = 0; c < kSpInFlight; c++) ci[c] = idx[tn + c];
       }
-      sp_use_r<T, true>(raw, acc, val, t, t1);
+      sp_use_r<T>(raw, acc, val, t);
       t = tn;
       if (!more) break;
     }
   }
-  if (t < t1) {
-    u4_t raw[kSpInFlight];
-    sp_issue_tail<T>(raw, X, n, row0, idx, t, t1);
-    sp_use_r<T, false>(raw, acc, val, t, t1);
-  }
+  if (t1 - t > 8) sp_tail<T, kSpInFlight>(acc, X, n, row0, idx, val, t, t1);
+  else if (t1 - t > 4) sp_tail<T, 8>(acc, X, n, row0, idx, val, t, t1);
+  else if (t < t1) sp_tail<T, 4>(acc, X, n, row0, idx, val, t, t1);
   double *part = B.part + (int64_t)ch * n + row0;
 #pragma unroll
   for (int e = 0; e < VEC; e += 2) *reinterpret_cast<d2_t *>(part + e) = d2_t{acc[e], acc[e + 1]};

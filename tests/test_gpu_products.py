@@ -18,7 +18,10 @@ def _design(dev, storage, n, p, seed):
 # per chunk at least as many as give every compute unit a workgroup, 64 at most
 @pytest.mark.parametrize("storage,n,p,planes", [("f64", 2, 1, 1), ("f32", 64, 15, 15), ("f32", 1024, 4095, 16),
                                                 ("bf16", 16384, 2047, 16), ("f64", 4608, 1920, 29),
-                                                ("f32", 4460, 3328, 52), ("f32", 2300, 5001, 64)])
+                                                ("f32", 4460, 3328, 52), ("f32", 2300, 5001, 64),
+                                                # 1, 7, 13 and 16 + 8 columns per chunk: each size of the last round
+                                                ("f32", 512, 16, 16), ("f32", 512, 100, 16), ("f64", 512, 200, 16),
+                                                ("bf16", 512, 384, 16)])
 def test_column_list_product_at_plane_counts(dev, storage, n, p, planes):
     import torch
     import paper_2603_01306_amd as pr
