@@ -132,9 +132,10 @@ typedef struct {
   double L;           /* step 1/L; 0 = 1.01 * loss curvature * ||X||^2 estimate */
   int32_t max_iter;   /* default 100000 */
   int32_t check_every; /* iterations per captured graph launch (rounded up to even); default 32.
-                        * pr_solve runs the iterations it predicts to be a solve's last ones
-                        * as launches of an 8-iteration graph; the iterates do not depend on
-                        * either length */
+                        * pr_solve runs a solve's first 24 evaluations and those it predicts
+                        * to be its last ones as launches of an 8-iteration graph;
+                        * pr_solve_batch runs the rest of an iteration budget that fills no
+                        * graph without one.  The iterates do not depend on any of it */
   int32_t method;      /* iteration variant, PR_FISTA_GAP (default) .. PR_FISTA_BT */
   int32_t pad0;
   double *trace;       /* pr_solve / pr_lasso_solve only, optional device array of
@@ -252,9 +253,11 @@ int pr_prox(void *stream, const double *v, int64_t p, double rho, int32_t k, dou
  * output), for callers that cannot allocate: code under stream capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Nothing is allocated, on
  * the device or the host: the workspace is a fixed device array of the
- * library, one copy per GPU, held until the process ends (8 bytes per
- * coordinate of PR_PROX_NOALLOC_MAX_P plus 256 bytes, 8 MiB).  |J1| and |J_f|
- * are counted on the device from `status`, so the host never reads it.
+ * library, one copy per GPU, held until the process ends (for p <= 524288 the
+ * 160 KiB through which the workgroups sharing the vector exchange partial
+ * sums, above that 8 bytes per coordinate of PR_PROX_NOALLOC_MAX_P plus 256
+ * bytes, 8 MiB).  |J1| and |J_f| are counted on the device from `status`, so the
+ * host never reads it.
  *   Arguments as pr_prox; additionally p <= PR_PROX_NOALLOC_MAX_P.
  *   Returns PR_EINVAL for a bad argument, p > PR_PROX_NOALLOC_MAX_P, a status
  *   code outside {PR_FREE, PR_ZERO, PR_ONE} or |J1| > k (then `out` is not

@@ -9,7 +9,8 @@
 //   k_prox, k_regularizer, k_loss_terms, ...: entry points of the C ABI.
 //
 // Two variants: register-resident (p <= 16384, coordinates j = tid + e*512
-// held in registers across all passes) and a global-memory one for larger p.
+// held in registers across all passes) and a global-memory one, for vectors
+// beyond the reach of the kernels that share a node among workgroups (p > 524288).
 #include "pr_device.h"
 
 #include "pr_regularizer.h"

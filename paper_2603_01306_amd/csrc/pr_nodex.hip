@@ -9,8 +9,8 @@
 // does not fit its registers: 512 us per step on average at p = 89989 (n =
 // 2300, logistic), up to 1.18 ms while the iterates are dense.  W workgroups
 // pay a W-th of it, and each reduction becomes an exchange between them
-// (pr_xwg.h, 1.2-2 us): 300 such iterations took 225 ms before and 56 now, the
-// X^T pass 116 us of the 190 us that remain.  The chain is kept short: the
+// (pr_xwg.h, 1.2-2 us): 300 such iterations took 228 ms before and 53 now, of
+// which the X^T pass takes 38.  The chain is kept short: the
 // top-kbar window's candidates travel with the dual sums, the prox statistics
 // with the first threshold evaluation at the previous tau, the sums of the
 // dom test with the support counts, and every workgroup takes the scalar
