@@ -479,34 +479,42 @@ __global__ __launch_bounds__(dev::NT) void k_feat_prep(const double *__restrict_
   }
 }
 
-// rank[q][j] = #{i : |beta_i| > |beta_j|} of every nonzero beta_j: a workgroup
-// takes 256 entries of the node's compacted list, one per thread, and walks the
-// list in LDS tiles that all its threads compare against.  The list is as long
-// as the support, so only its entries pay for it: with the loop in the kernel
-// that writes the rows, the few lanes with a nonzero coordinate kept their
-// whole wave for nnz dependent loads (87 us per node at p = 8192, nnz = 1200;
-// 32 such nodes take 29 us together here).
+// rank[q][j] = #{i : |beta_i| > |beta_j|} of every nonzero beta_j.  Bound by the
+// compares of one wave after another: a workgroup takes 64 entries of the node's
+// compacted list, one per lane, its four waves each compare them with a quarter
+// of every LDS tile of the list, and the counts are added.  The list is as long as
+// the support, so only its entries pay for it (with the loop in the kernel that
+// writes the rows, the few lanes with a nonzero coordinate kept their whole wave
+// for nnz dependent loads: 87 us per node at p = 8192, nnz = 1200; 32 such nodes
+// took 28.5 us with 256 entries per workgroup and the whole list per wave, 11.4 so).
 constexpr int kRankTile = 1024;
 __global__ __launch_bounds__(256) void k_feat_rank(const double *__restrict__ nzv, const int32_t *__restrict__ nzi,
                                                    const double *__restrict__ fs, int64_t p,
                                                    int32_t *__restrict__ rank) {
   __shared__ __align__(16) double tile[kRankTile];
+  __shared__ int cnt[kWaves][64];
   const int64_t o = (int64_t)blockIdx.y * p;
   const int nnz = (int)fs[2 * blockIdx.y + 1];
-  const int i0 = (int)blockIdx.x * 256;
-  if (i0 >= nnz) return;
-  const int i = i0 + (int)threadIdx.x;
-  const double a = i < nnz ? nzv[o + i] : INFINITY;
-  int r = 0;
-  for (int t0 = 0; t0 < nnz; t0 += kRankTile) {
-    __syncthreads();
-    for (int t = threadIdx.x; t < kRankTile; t += 256) tile[t] = t0 + t < nnz ? nzv[o + t0 + t] : 0.0;
-    __syncthreads();
-    const int n = nnz - t0 < kRankTile ? (nnz - t0 + 7) & ~7 : kRankTile;  // zeros pad the last tile
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int i0 = (int)blockIdx.x * 64; i0 < nnz; i0 += (int)gridDim.x * 64) {
+    const int i = i0 + lane;
+    const double a = i < nnz ? nzv[o + i] : INFINITY;
+    int r = 0;
+    for (int t0 = 0; t0 < nnz; t0 += kRankTile) {
+      __syncthreads();
+      for (int t = threadIdx.x; t < kRankTile; t += 256) tile[t] = t0 + t < nnz ? nzv[o + t0 + t] : 0.0;
+      __syncthreads();
+      // a quarter of the entries left, in eights (zeros pad the last tile)
+      const int left = nnz - t0 < kRankTile ? nnz - t0 : kRankTile;
+      const int q = ((left + kWaves - 1) / kWaves + 7) & ~7;
+      const int e = (w + 1) * q < kRankTile ? (w + 1) * q : kRankTile;
 #pragma unroll 8
-    for (int t = 0; t < n; t++) r += tile[t] > a;
+      for (int t = w * q; t < e; t++) r += tile[t] > a;
+    }
+    cnt[w][lane] = r;
+    __syncthreads();
+    if (w == 0 && i < nnz) rank[o + nzi[o + i]] = ((cnt[0][lane] + cnt[1][lane]) + cnt[2][lane]) + cnt[3][lane];
   }
-  if (i < nnz) rank[o + nzi[o + i]] = r;
 }
 
 __global__ __launch_bounds__(256) void k_feat_rows(const double *__restrict__ beta, const double *__restrict__ w,
