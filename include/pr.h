@@ -40,7 +40,8 @@ extern "C" {
 #define PR_OK 0
 #define PR_EINVAL (-1)   /* bad size, parameter, dtype or index */
 #define PR_EOVERLAP (-2) /* J0 and J1 share an index */
-#define PR_EDEVICE (-3)  /* a HIP runtime call failed */
+#define PR_EDEVICE (-3)  /* a HIP runtime call failed, or workgroups that share one long
+                          * vector waited 20 s for one another */
 #define PR_ENOMEM (-4)   /* device or host allocation failed */
 
 /* per-node status codes (positive, in pr_result.status) */
@@ -180,6 +181,10 @@ int pr_ctx_destroy(pr_ctx *ctx);
  * always iterates the nodes together to the end, also where its cost estimate
  * would run a small round, or the last nodes of a round, one at a time. */
 #define PR_DEBUG_FORCE_BATCH 2
+/* PR_DEBUG_LOSE_EXCHANGE: in every launch whose workgroups share one vector (p >
+ * 4096, or 16384 for the node step), the last workgroup gives up its first wait
+ * for the others, and they give up after 2 ms: the call returns PR_EDEVICE. */
+#define PR_DEBUG_LOSE_EXCHANGE 4
 int pr_ctx_set_debug(pr_ctx *ctx, int32_t flags);
 /* Cached estimate of ||X||_2^2 (largest eigenvalue of X^T X). */
 int pr_ctx_norm2(pr_ctx *ctx, double *norm2_out);

@@ -44,7 +44,7 @@ struct pr_ctx {
   // what a solve uploads, in one copy: NodeParams | packed status | status (the
   // three pointers into it) from the pinned h_stage
   char *d_stage = nullptr, *h_stage = nullptr;
-  char *h_pinned = nullptr;  // h_stage, h_state and h_scal
+  char *h_pinned = nullptr;  // h_stage, h_state, h_scal and *xb.lost
   size_t stage_stp = 0, stage_st = 0;  // offsets of the two statuses
   NodeParams *d_prm = nullptr;
   NodeState *d_state = nullptr;
@@ -1047,6 +1047,14 @@ hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const d
   return launch_regularizer(beta, alpha, c->P.p, kbar, node.M, c->d_status, c->d_regscratch, out2, c->stream);
 }
 
+// Whether workgroups of a launch since the last look lost each other (pr_xwg.h),
+// once the stream has been waited for: nothing such a launch wrote is valid.
+bool take_lost(pr_ctx *c) {
+  const bool lost = *c->xb.lost != 0;
+  *c->xb.lost = 0;
+  return lost;
+}
+
 // The terms of Psi(zeta) and Phi(beta) of the node whose status is in
 // c->d_status, over the stored X: scal = {F(X beta), -F*(-zeta), g_N(beta),
 // g_N*(X^T zeta / (2 lambda2))}.  Without zeta it is induced from beta and left
@@ -1180,11 +1188,13 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   c->stage_st = c->stage_stp + sizeof(uint32_t) * c->stp_words;
   ok = ok && dalloc(&c->d_stage, c->stage_st + (size_t)p) == hipSuccess && dalloc(&c->d_state, 1) == hipSuccess;
   const size_t pin_state = (c->stage_st + (size_t)p + 255) / 256 * 256, pin_scal = pin_state + 2 * sizeof(NodeState);
-  ok = ok && hipHostMalloc((void **)&c->h_pinned, pin_scal + 8 * sizeof(double), hipHostMallocDefault) == hipSuccess;
+  ok = ok && hipHostMalloc((void **)&c->h_pinned, pin_scal + 9 * sizeof(double), hipHostMallocDefault) == hipSuccess;
   if (ok) {
     c->h_stage = c->h_pinned;
     c->h_state = reinterpret_cast<NodeState *>(c->h_pinned + pin_state);
     c->h_scal = reinterpret_cast<double *>(c->h_pinned + pin_scal);
+    c->xb.lost = reinterpret_cast<uint64_t *>(c->h_scal + 8);
+    *c->xb.lost = 0;
     c->d_prm = reinterpret_cast<NodeParams *>(c->d_stage);
     c->d_stp = reinterpret_cast<uint32_t *>(c->d_stage + c->stage_stp);
     c->d_status = reinterpret_cast<int8_t *>(c->d_stage + c->stage_st);
@@ -1208,7 +1218,7 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && dalloc(&c->d_lam, 2 * kLanczosMax) == hipSuccess && dalloc(&c->d_vprev, p) == hipSuccess;
   ok = ok && dalloc(&c->d_regscratch, 3 * (size_t)p) == hipSuccess;
   ok = ok && dalloc(&c->xb.slots, kXwgWords + 1) == hipSuccess;
-  if (ok) c->xb.round = reinterpret_cast<uint32_t *>(c->xb.slots + kXwgWords);
+  if (ok) c->xb.head = reinterpret_cast<uint32_t *>(c->xb.slots + kXwgWords);
   ok = ok && hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreate(&c->tev[0]) == hipSuccess && hipEventCreate(&c->tev[1]) == hipSuccess;
@@ -1254,7 +1264,12 @@ int pr_ctx_destroy(pr_ctx *c) {
 }
 
 int pr_ctx_set_debug(pr_ctx *c, int32_t flags) {
-  if (!c || (flags & ~(PR_DEBUG_GRAM_RECHECK | PR_DEBUG_FORCE_BATCH))) return PR_EINVAL;
+  if (!c || (flags & ~(PR_DEBUG_GRAM_RECHECK | PR_DEBUG_FORCE_BATCH | PR_DEBUG_LOSE_EXCHANGE))) return PR_EINVAL;
+  if ((flags ^ c->debug) & PR_DEBUG_LOSE_EXCHANGE) {
+    const uint32_t lose = (flags & PR_DEBUG_LOSE_EXCHANGE) ? 1u : 0u;
+    PR_TRY(hipMemcpyAsync(c->xb.head + 1, &lose, sizeof(lose), hipMemcpyHostToDevice, c->stream));
+    PR_TRY(hipStreamSynchronize(c->stream));
+  }
   c->debug = flags;
   return PR_OK;
 }
@@ -1281,15 +1296,19 @@ static int gram_certify(pr_ctx *c, const pr_node *node, int32_t kbar, const pr_o
   const bool same = hs.lb_it == hs.ub_it;
   int rc = enqueue_dual(c, *node, kbar, nullptr, c->nb.xlb, c->d_scal);  // leaves zeta(x_lb) in B.gm
   if (rc != PR_OK) return rc;
-  if (zeta_out) PR_TRY(hipMemcpyAsync(zeta_out, c->B.gm, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+  if (zeta_out && !same)
+    PR_TRY(hipMemcpyAsync(c->B.zbest, c->B.gm, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
   if (!same) rc = enqueue_dual(c, *node, kbar, nullptr, c->nb.xbest, c->d_scal + 4);
   if (rc != PR_OK) return rc;
   PR_TRY(hipMemcpyAsync(c->h_scal, c->d_scal, 8 * sizeof(double), hipMemcpyDeviceToHost, s));
   PR_TRY(hipStreamSynchronize(s));
+  if (take_lost(c)) return PR_EDEVICE;
   double lb1, ub1, lb2, ub2;
   dual_values(c->h_scal, node->lambda2, &lb1, &ub1);
   dual_values(c->h_scal + (same ? 0 : 4), node->lambda2, &lb2, &ub2);
-  if (zeta_out && lb2 > lb1) PR_TRY(hipMemcpyAsync(zeta_out, c->B.gm, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+  if (zeta_out)
+    PR_TRY(hipMemcpyAsync(zeta_out, same || lb2 > lb1 ? c->B.gm : c->B.zbest, sizeof(double) * n,
+                          hipMemcpyDeviceToDevice, s));
   const double lb = lb2 > lb1 ? lb2 : lb1, ub = ub2;
   const double rel = (ub - lb) / fmax(fabs(ub), 1e-300);
   const int st = hs.done ? hs.status : kMaxIter;
@@ -2197,6 +2216,7 @@ int pr_dual_bound(pr_ctx *c, const pr_node *node, const double *zeta, const doub
   if (rc != PR_OK) return rc;
   PR_TRY(hipMemcpyAsync(c->h_scal, c->d_scal, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
   PR_TRY(hipStreamSynchronize(s));
+  if (take_lost(c)) return PR_EDEVICE;
   double ub;
   dual_values(c->h_scal, node->lambda2, lb_out, &ub);
   if (primal_out) *primal_out = beta ? ub : NAN;

@@ -135,12 +135,15 @@ struct BatchBufs {
 };
 
 // Exchange area of the kernels whose workgroups share one node (pr_xwg.h):
-// slots (zeroed once, kXwgWords 64-bit words) and the round reached so far.
+// slots and head {round reached so far, test switch}, zeroed once (kXwgWords
+// 64-bit words and one for the head).  A workgroup that loses the others writes
+// the launch's tag, never 0, to *lost (pinned host memory, or null).
 constexpr int kXwgMax = 64;          // workgroups of such a launch at most
 constexpr size_t kXwgWords = 2 * (2 * 16 + 2 * 64) * (size_t)kXwgMax;
 struct XBuf {
   uint64_t *slots;
-  uint32_t *round;
+  uint32_t *head;
+  uint64_t *lost;
 };
 
 // What a kernel of a context-free entry point hands back, in pinned host memory.

@@ -781,7 +781,8 @@ __global__ __launch_bounds__(NT) void k_prox_x(const double *v, double *out, int
 }
 
 // g_N(beta) (Algorithm 1, +inf off its domain) into out[0], g_N*(ascale alpha)
-// into out[1] (each if its input is given); counts and *flag as in k_prox_x.
+// into out[1] (each if its input is given; NaN where the workgroups lost each
+// other); counts and *flag as in k_prox_x.
 template <int EPT>
 __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__ beta,
                                                       const double *__restrict__ alpha, double ascale, int64_t p,
@@ -846,6 +847,7 @@ __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__
     }
     if (X.failed) err = 3;
   }
+  if (lead && err == 3) out[0] = out[1] = NAN;
   if (lead && flag) *flag = err;
   X.finish(xb);
 }

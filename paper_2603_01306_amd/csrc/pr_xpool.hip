@@ -14,12 +14,12 @@ constexpr int kSlots = 8;  // slot 0 belongs to pr_prox_noalloc
 constexpr int kDevices = 64;
 
 static __device__ uint64_t g_slots[kSlots][kXwgWords];
-static __device__ uint32_t g_round[kSlots];
+static __device__ uint32_t g_head[kSlots][2];
 static __device__ int32_t g_flag;  // pr_prox_noalloc's
 
 struct DeviceSlots {
   uint64_t *slots = nullptr;
-  uint32_t *round = nullptr;
+  uint32_t *head = nullptr;
   int32_t *flag = nullptr;
   unsigned busy = 0u;  // bit per leased slot
 };
@@ -33,11 +33,11 @@ bool find_slots(int dev) {
   if (d.flag) return true;
   void *a = nullptr, *b = nullptr, *c = nullptr;
   if (hipGetSymbolAddress(&a, HIP_SYMBOL(g_slots)) != hipSuccess ||
-      hipGetSymbolAddress(&b, HIP_SYMBOL(g_round)) != hipSuccess ||
+      hipGetSymbolAddress(&b, HIP_SYMBOL(g_head)) != hipSuccess ||
       hipGetSymbolAddress(&c, HIP_SYMBOL(g_flag)) != hipSuccess || !a || !b || !c)
     return false;
   d.slots = static_cast<uint64_t *>(a);
-  d.round = static_cast<uint32_t *>(b);
+  d.head = static_cast<uint32_t *>(b);
   d.flag = static_cast<int32_t *>(c);
   return true;
 }
@@ -59,7 +59,7 @@ int XLease::take(hipStream_t s) {
       if (d.busy & (1u << i)) continue;
       d.busy |= 1u << i;
       slot_ = i;
-      xb = XBuf{d.slots + (size_t)i * kXwgWords, d.round + i};
+      xb = XBuf{d.slots + (size_t)i * kXwgWords, d.head + 2 * i, nullptr};
       res = g_res + dev_ * kSlots + i;
       break;
     }
@@ -74,7 +74,7 @@ int XLease::take(hipStream_t s) {
       return PR_ENOMEM;
     }
     if (hipMemsetAsync(own_, 0, sizeof(uint64_t) * (kXwgWords + 1), s) != hipSuccess) return PR_EDEVICE;
-    xb = XBuf{own_, reinterpret_cast<uint32_t *>(own_ + kXwgWords)};
+    xb = XBuf{own_, reinterpret_cast<uint32_t *>(own_ + kXwgWords), nullptr};
   }
   *res = XResult{{0.0, 0.0}, -1};
   return PR_OK;
@@ -97,7 +97,7 @@ int xpool_noalloc(XBuf *xb, int32_t **flag) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return PR_EDEVICE;
   std::lock_guard<std::mutex> lock(g_mu);
   if (!find_slots(dev)) return PR_EDEVICE;
-  *xb = XBuf{g_dev[dev].slots, g_dev[dev].round};
+  *xb = XBuf{g_dev[dev].slots, g_dev[dev].head, nullptr};
   *flag = g_dev[dev].flag;
   return PR_OK;
 }

@@ -17,7 +17,10 @@
 //
 // All workgroups of the launch must be resident together; launches are
 // limited to kXwgMax = 64 workgroups of 512 threads on a 256-CU device.  A
-// wait that outlasts kXwgTicks ends with `failed` set instead of a hang.
+// wait that outlasts kXwgTicks ends with `failed` set instead of a hang, and the
+// workgroup reports it in *XBuf::lost: what such a launch wrote is not to be used.
+// A nonzero test switch e in the area's head lets the last workgroup give up
+// at exchange e of every launch and the others after kLostTicks.
 #pragma once
 #include "pr_device.h"
 
@@ -30,6 +33,7 @@ constexpr int kQ = 16;         // values per reduction at most
 constexpr int kWin = 16;       // values per workgroup in a small gather
 constexpr int kGat = 64;       // ... and in a large one
 constexpr long long kXwgTicks = 2000000000ll;  // 20 s of the 100 MHz clock
+constexpr long long kLostTicks = 200000ll;     // 2 ms
 
 __device__ __forceinline__ void put(uint64_t *w, uint32_t round, uint32_t half) {
   __hip_atomic_store(w, ((uint64_t)round << 32) | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -43,7 +47,8 @@ struct Lds {
 
 struct Group {
   uint64_t *slots;  // [2][kQ][kXwgMax][2] reductions, then [2][kXwgMax][kGat][2] gathers
-  uint32_t round;
+  uint32_t round, round0;  // current, at the start of the launch
+  uint32_t lose;    // test switch
   int W, w;         // workgroups, this one
   Lds *L;
   int ph;
@@ -52,7 +57,8 @@ struct Group {
   // Call once per workgroup, before any exchange (followed by a barrier inside).
   __device__ __forceinline__ void init(const XBuf &xb, Lds *lds) {
     slots = xb.slots;
-    round = *xb.round;
+    round = round0 = xb.head[0];
+    lose = xb.head[1];
     W = (int)gridDim.x;
     w = (int)blockIdx.x;
     L = lds;
@@ -90,7 +96,7 @@ struct Group {
       if ((++spin & 1023) == 0) {
         const long long now = (long long)__builtin_amdgcn_s_memrealtime();
         if (t0 == 0) t0 = now;
-        else if (now - t0 > kXwgTicks) {
+        else if (now - t0 > (lose ? kLostTicks : kXwgTicks)) {
           if (lane_id() == 0) L->bad = 1;
           break;
         }
@@ -146,7 +152,7 @@ struct Group {
     }
     take();
     lds_barrier();
-    failed = L->bad != 0;
+    failed = L->bad != 0 || (lose && w > 0 && w == W - 1 && round - round0 == lose);
     ph ^= 1;
   }
 
@@ -205,7 +211,10 @@ struct Group {
   // Last exchange done: the next launch continues after this one's rounds (a
   // launch that gave up skips far past any round its peers may have reached).
   __device__ __forceinline__ void finish(const XBuf &xb) const {
-    if (w == 0 && threadIdx.x == 0) *xb.round = round + (failed ? 1u << 24 : 0u);
+    if (threadIdx.x != 0) return;
+    if (failed && xb.lost)
+      __hip_atomic_store(xb.lost, (1ull << 32) | round0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (w == 0) *xb.head = round + (failed ? 1u << 24 : 0u);
   }
 };
 

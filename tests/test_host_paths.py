@@ -1,0 +1,117 @@
+"""Host paths of libpr.so that a healthy GPU rarely takes, over a stand-in for
+the HIP host runtime (hip_standin.c: kernels do nothing, failures are forced).
+Each body runs in a process of its own with the stand-in preloaded.  No GPU."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+sys.path.insert(0, {root!r})
+import paper_2603_01306_amd._binding as b
+P = ctypes.c_void_p
+si = ctypes.CDLL({so!r})
+si.si_log.restype = ctypes.c_char_p
+si.si_lose.argtypes = [ctypes.c_char_p]
+si.si_fail_above.argtypes = [ctypes.c_size_t]
+si.si_cost.argtypes = [ctypes.c_char_p, ctypes.c_double]
+lib = b.load()
+keep = []
+
+def mem(x):
+    a = np.ascontiguousarray(x)
+    keep.append(a)
+    return P(a.ctypes.data)
+
+def zeros(*shape):
+    return mem(np.zeros(shape))
+
+def context(n, p, loss=0, max_batch=1):
+    prob = b.PrProblem(X=mem(np.zeros((p, n), np.float32)).value, xdtype=b.F32, loss=loss, y=zeros(n).value, n=n, p=p)
+    h = P()
+    assert lib.pr_ctx_create(ctypes.byref(h), ctypes.byref(prob), max_batch, None) == 0
+    return h
+
+def nodes(m):
+    return (b.PrNode * m)(*[b.PrNode(k=3, lambda2=0.5, M=2.0) for _ in range(m)])
+
+def log():
+    return [ln.split() for ln in si.si_log().decode().splitlines()]
+
+def opts(**kw):
+    o = b.PrOpts()
+    lib.pr_opts_default(ctypes.byref(o))
+    o.L = 1.0
+    for k, v in kw.items():
+        setattr(o, k, v)
+    return ctypes.byref(o)
+
+res = b.PrResult()
+OK, EDEVICE, ENOMEM = 0, -3, -4
+"""
+
+
+@pytest.fixture(scope="session")
+def standin(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("standin") / "hip_standin.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "hip_standin.c")
+    subprocess.check_call(["gcc", "-std=gnu11", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, src])
+    return so
+
+
+def run(so, body):
+    env = dict(os.environ, LD_PRELOAD=so)
+    code = PRELUDE.format(root=ROOT, so=so) + textwrap.dedent(body)
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("p", [5000, 17000])
+def test_lost_exchange_fails_the_dual_bound(standin, p):
+    """A regulariser kernel whose workgroups lost each other leaves no bound."""
+    run(standin, f"""
+    p = {p}
+    h, lb, ub = context(8, p), ctypes.c_double(7.0), ctypes.c_double(7.0)
+    call = lambda: lib.pr_dual_bound(h, nodes(1), None, zeros(p), ctypes.byref(lb), ctypes.byref(ub))
+    assert call() == OK and lb.value != 7.0
+    lb.value = ub.value = 7.0
+    si.si_lose(b"k_regularizer_x")
+    assert call() == EDEVICE and lb.value == ub.value == 7.0
+    si.si_lose(b"")
+    assert call() == OK
+    """)
+
+
+@pytest.mark.parametrize("kernel", ["k_regularizer_x", "k_prox_x"])
+def test_lost_exchange_fails_the_warm_start(standin, kernel):
+    """... and no judged starting point, also where only the candidate's prox
+    was lost."""
+    run(standin, f"""
+    p = 5000
+    h, B0 = context(8, p), zeros(2, p)
+    call = lambda: lib.pr_mlp_warm_start(h, nodes(2), 2, None, zeros(2, p), B0, None, None)
+    assert call() == OK
+    si.si_lose({kernel.encode()!r})
+    assert call() == EDEVICE
+    si.si_lose(b"")
+    assert call() == OK
+    """)
+
+
+def test_lost_exchange_fails_the_gram_certificate(standin):
+    run(standin, """
+    h = context(32, 4224)
+    assert lib.pr_ctx_enable_gram(h) == OK
+    z = np.full(32, 7.0)
+    call = lambda: lib.pr_solve(h, nodes(1), opts(max_iter=0), None, None, P(z.ctypes.data), ctypes.byref(res))
+    si.si_lose(b"k_regularizer_x")
+    assert call() == EDEVICE and np.all(z == 7.0)
+    si.si_lose(b"")
+    assert call() == OK and np.all(z == 0.0)
+    """)
