@@ -402,7 +402,7 @@ hipError_t run_graph(pr_ctx *c, hipGraphExec_t g, int32_t units, int64_t max_uni
     *last = h;
     head ^= 1;
     inflight--;
-    if (h.done) break;
+    if (h.done || *c->xb.lost) break;
     // evaluations predicted before the stop: those the iteration limit leaves,
     // or fewer where the gap has fallen over the window
     const int64_t ev = (int64_t)h.iter + h.trials;
@@ -1552,8 +1552,9 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
   NodeState hs;
   PR_TRY(run_graph(c, c->gexec, c->graph_units, (is_bt(opts.method) ? 2 * launches : launches) * c->graph_units,
                    opts, &hs, c->gtail, kTailUnits));
-  if (hs.status == kFailed) {
+  if (*c->xb.lost) {
     PR_TRY(hipStreamSynchronize(c->stream));
+    (void)take_lost(c);
     return PR_EDEVICE;
   }
   if (c->gram) return gram_certify(c, node, kbar, &opts, hs, beta_out, zeta_out, out);
@@ -1610,10 +1611,10 @@ int pr_prox(void *stream, const double *v, int64_t p, double rho, int32_t k, dou
     XLease x;
     const int rc = x.take(s);
     if (rc != PR_OK) return rc;
-    PR_TRY(launch_prox_x(v, out, p, rho, k, M, status, &x.res->flag, x.xb, s));
+    PR_TRY(launch_prox_x(v, out, p, rho, k, M, status, x.res, x.xb, s));
     PR_TRY(hipStreamSynchronize(s));
-    const int32_t flag = x.res->flag;
-    return flag == 0 ? PR_OK : (flag == 1 || flag == 2 ? PR_EINVAL : PR_EDEVICE);
+    const int code = x.res->code();
+    return code == 0 ? PR_OK : (code == 1 || code == 2 ? PR_EINVAL : PR_EDEVICE);
   }
   int64_t n1, nf;
   const int rc = count_status(status, p, s, &n1, &nf);
@@ -1685,7 +1686,7 @@ int pr_time_prox(void *stream, const double *v, int64_t p, double rho, int32_t k
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(g2);
   (void)hipFree(abuf);
-  return e == hipSuccess ? PR_OK : PR_EDEVICE;
+  return e == hipSuccess && !(wide && x.res->lost) ? PR_OK : PR_EDEVICE;
 }
 
 int pr_regularizer(void *stream, const double *beta, const double *alpha, int64_t p, int32_t k,
@@ -1698,13 +1699,14 @@ int pr_regularizer(void *stream, const double *beta, const double *alpha, int64_
     XLease x;
     const int rc = x.take(s);
     if (rc != PR_OK) return rc;
-    PR_TRY(launch_regularizer_x(beta, alpha, 1.0, p, k, M, status, x.res->v, &x.res->flag, x.xb, s));
+    PR_TRY(launch_regularizer_x(beta, alpha, 1.0, p, k, M, status, x.res->v, x.res, x.xb, s));
     PR_TRY(hipStreamSynchronize(s));
     const XResult r = *x.res;
-    if (r.flag == 1) return PR_EINVAL;
-    if (r.flag != 0 && r.flag != 2) return PR_EDEVICE;
-    if (g_out) *g_out = r.flag == 2 ? INFINITY : r.v[0];
-    if (gstar_out) *gstar_out = r.flag == 2 ? -INFINITY : r.v[1];
+    const int code = r.code();
+    if (code == 1) return PR_EINVAL;
+    if (code != 0 && code != 2) return PR_EDEVICE;
+    if (g_out) *g_out = code == 2 ? INFINITY : r.v[0];
+    if (gstar_out) *gstar_out = code == 2 ? -INFINITY : r.v[1];
     return PR_OK;
   }
   int64_t n1, nf;

@@ -27,7 +27,6 @@ constexpr int32_t kJ0Flag = 1 << 29;
 constexpr int32_t kIdxMask = kJ0Flag - 1;
 enum : int32_t { kF64 = 0, kF32 = 1, kBF16 = 2 };
 enum : int32_t { kConverged = 1, kMaxIter = 2, kInfeasible = 3, kCutoffPrune = 4, kCutoffBranch = 5 };
-enum : int32_t { kFailed = -1 };  // NodeState::status: workgroups of a step lost each other (never in a result)
 
 // Per-node constants, device resident (written by the host before a solve).
 // iteration variants (pr_opts.method)
@@ -137,7 +136,8 @@ struct BatchBufs {
 // Exchange area of the kernels whose workgroups share one node (pr_xwg.h):
 // slots and head {round reached so far, test switch}, zeroed once (kXwgWords
 // 64-bit words and one for the head).  A workgroup that loses the others writes
-// the launch's tag, never 0, to *lost (pinned host memory, or null).
+// the launch's tag, never 0, to *lost (memory that the host reads after it has
+// waited for the launch).
 constexpr int kXwgMax = 64;          // workgroups of such a launch at most
 constexpr size_t kXwgWords = 2 * (2 * 16 + 2 * 64) * (size_t)kXwgMax;
 struct XBuf {
@@ -146,10 +146,15 @@ struct XBuf {
   uint64_t *lost;
 };
 
-// What a kernel of a context-free entry point hands back, in pinned host memory.
+// What a kernel of a context-free entry point hands back.  The first workgroup
+// writes `flag` (0; 1: a status code outside {free, J0, J1}; 2: |J1| > k) and the
+// launch's tag; any workgroup that lost the others writes the tag to `lost`
+// (XBuf::lost), which need not be cleared between launches.
 struct XResult {
   double v[2];
-  int32_t flag;  // -1 until the kernel has written it
+  uint64_t tag, lost;
+  int32_t flag;
+  int code() const { return lost == tag ? 3 : flag; }  // 3: not to be used
 };
 // An exchange area for one call of a context-free entry point on the current
 // device (pr_xpool.hip), given back by the destructor: the call has waited for
@@ -165,8 +170,8 @@ class XLease {
   int dev_ = 0, slot_ = 0;
   uint64_t *own_ = nullptr;
 };
-// pr_prox_noalloc's own area and error flag (device memory) on the current device
-int xpool_noalloc(XBuf *xb, int32_t **flag);
+// pr_prox_noalloc's own area and result (device memory) on the current device
+int xpool_noalloc(XBuf *xb, XResult **res);
 
 // AC-FGM state of a single-node solve (pr_variants.hip), device resident.
 struct AcState {
@@ -254,13 +259,13 @@ hipError_t launch_node_init_x(const NodeParams *prm, NodeState *S, NodeBufs nb, 
 hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B, const StepArgs &a,
                               XShape g, const XBuf &xb, hipStream_t s);
 // The standalone prox and regulariser over several workgroups, p <= reg_x_max();
-// kbar is counted from st.  *flag (optional): 0, 1 bad status code, 2 |J1| > k
-// (nothing else written then), 3 the workgroups lost each other.
+// kbar is counted from st.  res (optional) receives the flag and the tag; nothing
+// else is written where the flag is not 0.
 int64_t reg_x_max();
 hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
-                         int32_t *flag, const XBuf &xb, hipStream_t s);
+                         XResult *res, const XBuf &xb, hipStream_t s);
 hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,
-                                double M, const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s);
+                                double M, const int8_t *st, double *out2, XResult *res, const XBuf &xb, hipStream_t s);
 hipError_t launch_batch_init(const NodeParams *prm, NodeState *S, BatchBufs bb, const double *B0, double L,
                              int64_t p, hipStream_t s);
 hipError_t launch_batch_step(const NodeParams *prm, NodeState *S, BatchBufs bb, int64_t p, hipStream_t s);

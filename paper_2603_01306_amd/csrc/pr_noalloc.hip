@@ -52,24 +52,29 @@ int pr_prox_noalloc(void *stream, const double *v, int64_t p, double rho, int32_
   if (!v || !out || !status || p < 1 || !(rho > 0.0) || !isfinite(rho) || !(M > 0.0) || k < 1) return PR_EINVAL;
   if (p > kMaxP) return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  int32_t hflag = -1, *flag = nullptr;
   hipError_t e;
+  int code = -1;
   if (p <= reg_x_max()) {
     XBuf xb;
-    const int rc = xpool_noalloc(&xb, &flag);
+    XResult r{{0.0, 0.0}, 1, 0, -1}, *res = nullptr;
+    const int rc = xpool_noalloc(&xb, &res);
     if (rc != PR_OK) return rc;
-    e = launch_prox_x(v, out, p, rho, k, M, status, flag, xb, s);
+    e = launch_prox_x(v, out, p, rho, k, M, status, res, xb, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    code = r.code();
   } else {
     double *ws = nullptr;
     const int rc = scratch_of_current_device(&ws);
     if (rc != PR_OK) return rc;
-    flag = reinterpret_cast<int32_t *>(ws + kMaxP);
+    int32_t hflag = -1, *flag = reinterpret_cast<int32_t *>(ws + kMaxP);
     e = launch_prox_counted(v, out, p, rho, k, M, status, ws, flag, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(hflag), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    code = hflag;
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(hflag), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return PR_EDEVICE;
-  return hflag == 0 ? PR_OK : (hflag == 1 || hflag == 2 ? PR_EINVAL : PR_EDEVICE);
+  return code == 0 ? PR_OK : (code == 1 || code == 2 ? PR_EINVAL : PR_EDEVICE);
 }
 
 }  // extern "C"

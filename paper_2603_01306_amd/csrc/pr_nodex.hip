@@ -362,12 +362,10 @@ __device__ __forceinline__ int support_list_x(const double (&x)[EPT], const Code
   return (int)s[0];
 }
 
-// A launch whose workgroups lost each other stops the solve with an error.
+// A step whose workgroups lost each other ends the solve: the host finds
+// *XBuf::lost written, whatever the state says.
 __device__ __forceinline__ void give_up(NodeState *S, const Group &X, const XBuf &xb) {
-  if (threadIdx.x == 0) {
-    S->status = kFailed;
-    S->done = 1;
-  }
+  if (threadIdx.x == 0) S->done = 1;
   X.finish(xb);
 }
 
@@ -419,10 +417,10 @@ __global__ __launch_bounds__(NT) void k_node_init_x(const NodeParams *__restrict
     s.nsupp = ns;
     s.indom = in_domain(t, kbar, M);
     s.bt = is_bt(prm->method) ? 1 : 0;
+    s.done = X.failed ? 1 : 0;
     *S = s;
   }
-  if (X.failed) give_up(S, X, xb);
-  else X.finish(xb);
+  X.finish(xb);
 }
 
 // The node step of k_node_step (pr_node.hip) over W workgroups: the same
@@ -719,12 +717,11 @@ __global__ __launch_bounds__(NT) void k_node_step_x(const NodeParams *__restrict
 }
 
 // Standalone prox_{rho g_N}(v) (Algorithm 2 + Moreau, pooled-threshold form).
-// |J1| and |J_f| are counted here, kbar = min(k - |J1|, |J_f|).  *flag: 0, 1
-// for a status code outside {free, J0, J1}, 2 for |J1| > k (out is not written
-// then), 3 when the workgroups lost each other.
+// |J1| and |J_f| are counted here, kbar = min(k - |J1|, |J_f|).  out is not
+// written where XResult::flag is not 0.
 template <int EPT>
 __global__ __launch_bounds__(NT) void k_prox_x(const double *v, double *out, int64_t p, double rho, int k, double M,
-                                               const int8_t *__restrict__ st, int32_t *flag, XBuf xb) {
+                                               const int8_t *__restrict__ st, XResult *res, XBuf xb) {
   __shared__ xwg::Lds lds;
   Group X;
   X.init(xb, &lds);
@@ -776,18 +773,21 @@ __global__ __launch_bounds__(NT) void k_prox_x(const double *v, double *out, int
       }
     }
   }
-  if (lead && flag) *flag = err;
+  if (lead && res) {
+    res->flag = err;
+    res->tag = X.tag();
+  }
   X.finish(xb);
 }
 
 // g_N(beta) (Algorithm 1, +inf off its domain) into out[0], g_N*(ascale alpha)
 // into out[1] (each if its input is given; NaN where the workgroups lost each
-// other); counts and *flag as in k_prox_x.
+// other); counts and flag as in k_prox_x.
 template <int EPT>
 __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__ beta,
                                                       const double *__restrict__ alpha, double ascale, int64_t p,
                                                       int k, double M, const int8_t *__restrict__ st, double *out,
-                                                      int32_t *flag, XBuf xb) {
+                                                      XResult *res, XBuf xb) {
   __shared__ NodeXLds lds;
   Group X;
   X.init(xb, &lds.x);
@@ -848,7 +848,10 @@ __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__
     if (X.failed) err = 3;
   }
   if (lead && err == 3) out[0] = out[1] = NAN;
-  if (lead && flag) *flag = err;
+  if (lead && res) {
+    res->flag = err;
+    res->tag = X.tag();
+  }
   X.finish(xb);
 }
 
@@ -916,18 +919,18 @@ int64_t reg_x_max() { return (int64_t)kXwgMax * 16 * NT; }
     default: return hipErrorInvalidValue; \
   }
 hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
-                         int32_t *flag, const XBuf &xb, hipStream_t s) {
+                         XResult *res, const XBuf &xb, hipStream_t s) {
   const XShape g = reg_xshape(p);
-#define PR_CALL(E) k_prox_x<E><<<g.wgs, NT, 0, s>>>(v, out, p, rho, k, M, st, flag, xb)
+#define PR_CALL(E) k_prox_x<E><<<g.wgs, NT, 0, s>>>(v, out, p, rho, k, M, st, res, xb)
   PR_REGX(PR_CALL)
 #undef PR_CALL
   return hipGetLastError();
 }
 
 hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,
-                                double M, const int8_t *st, double *out2, int32_t *flag, const XBuf &xb, hipStream_t s) {
+                                double M, const int8_t *st, double *out2, XResult *res, const XBuf &xb, hipStream_t s) {
   const XShape g = reg_xshape(p);
-#define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, ascale, p, k, M, st, out2, flag, xb)
+#define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, ascale, p, k, M, st, out2, res, xb)
   PR_REGX(PR_CALL)
 #undef PR_CALL
   return hipGetLastError();

@@ -15,12 +15,12 @@ constexpr int kDevices = 64;
 
 static __device__ uint64_t g_slots[kSlots][kXwgWords];
 static __device__ uint32_t g_head[kSlots][2];
-static __device__ int32_t g_flag;  // pr_prox_noalloc's
+static __device__ XResult g_result;  // pr_prox_noalloc's
 
 struct DeviceSlots {
   uint64_t *slots = nullptr;
   uint32_t *head = nullptr;
-  int32_t *flag = nullptr;
+  XResult *result = nullptr;
   unsigned busy = 0u;  // bit per leased slot
 };
 std::mutex g_mu;
@@ -30,15 +30,15 @@ XResult *g_res = nullptr;  // pinned, kDevices * kSlots entries (written by the 
 // Device addresses of this device's slots (looked up once; g_mu held).
 bool find_slots(int dev) {
   DeviceSlots &d = g_dev[dev];
-  if (d.flag) return true;
+  if (d.result) return true;
   void *a = nullptr, *b = nullptr, *c = nullptr;
   if (hipGetSymbolAddress(&a, HIP_SYMBOL(g_slots)) != hipSuccess ||
       hipGetSymbolAddress(&b, HIP_SYMBOL(g_head)) != hipSuccess ||
-      hipGetSymbolAddress(&c, HIP_SYMBOL(g_flag)) != hipSuccess || !a || !b || !c)
+      hipGetSymbolAddress(&c, HIP_SYMBOL(g_result)) != hipSuccess || !a || !b || !c)
     return false;
   d.slots = static_cast<uint64_t *>(a);
   d.head = static_cast<uint32_t *>(b);
-  d.flag = static_cast<int32_t *>(c);
+  d.result = static_cast<XResult *>(c);
   return true;
 }
 
@@ -76,7 +76,8 @@ int XLease::take(hipStream_t s) {
     if (hipMemsetAsync(own_, 0, sizeof(uint64_t) * (kXwgWords + 1), s) != hipSuccess) return PR_EDEVICE;
     xb = XBuf{own_, reinterpret_cast<uint32_t *>(own_ + kXwgWords), nullptr};
   }
-  *res = XResult{{0.0, 0.0}, -1};
+  *res = XResult{{0.0, 0.0}, 1, 0, -1};
+  xb.lost = &res->lost;
   return PR_OK;
 }
 
@@ -92,13 +93,13 @@ XLease::~XLease() {
   }
 }
 
-int xpool_noalloc(XBuf *xb, int32_t **flag) {
+int xpool_noalloc(XBuf *xb, XResult **res) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return PR_EDEVICE;
   std::lock_guard<std::mutex> lock(g_mu);
   if (!find_slots(dev)) return PR_EDEVICE;
-  *xb = XBuf{g_dev[dev].slots, g_dev[dev].head, nullptr};
-  *flag = g_dev[dev].flag;
+  *xb = XBuf{g_dev[dev].slots, g_dev[dev].head, &g_dev[dev].result->lost};
+  *res = g_dev[dev].result;
   return PR_OK;
 }
 

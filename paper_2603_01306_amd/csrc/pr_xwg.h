@@ -208,12 +208,13 @@ struct Group {
     run<KS, KM, false>(s, m, nullptr, [] {}, [] {});
   }
 
+  __device__ __forceinline__ uint64_t tag() const { return (1ull << 32) | round0; }
+
   // Last exchange done: the next launch continues after this one's rounds (a
   // launch that gave up skips far past any round its peers may have reached).
   __device__ __forceinline__ void finish(const XBuf &xb) const {
     if (threadIdx.x != 0) return;
-    if (failed && xb.lost)
-      __hip_atomic_store(xb.lost, (1ull << 32) | round0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (failed) __hip_atomic_store(xb.lost, tag(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (w == 0) *xb.head = round + (failed ? 1u << 24 : 0u);
   }
 };

@@ -12,6 +12,7 @@
 
 typedef struct { uint32_t x, y, z; } dim3;
 typedef struct { void *slots; void *head; uint64_t *lost; } xbuf;
+typedef struct { double v[2]; uint64_t tag, lost; int32_t flag; } result;
 
 #define MAXF 4096
 static struct { const void *f; char name[256]; double us; } fn[MAXF];
@@ -40,7 +41,7 @@ void si_cost(const char *kernel, double us) {
 }
 
 /* launches */
-typedef struct { int id; uint64_t *lost; } node;
+typedef struct { int id; uint64_t *lost; result *res; } node;
 typedef struct { node *v; int n; } graph;
 static graph *capture;
 static dim3 cfg_grid, cfg_block;
@@ -48,8 +49,11 @@ static size_t cfg_shm;
 static void *cfg_stream;
 
 static void run(node k) {
+  static uint64_t tag;
+  tag++;
   clock_us += fn[k.id].us;
-  if (k.lost && lose[0] && strstr(fn[k.id].name, lose)) *k.lost = 1;
+  if (k.res) k.res->tag = tag, k.res->flag = 0;
+  if (k.lost && lose[0] && strstr(fn[k.id].name, lose)) *k.lost = tag;
 }
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t shm, void *s) {
   cfg_grid = g, cfg_block = b, cfg_shm = shm, cfg_stream = s;
@@ -79,12 +83,10 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t shm, void
   while (id < nfn && fn[id].f != f) id++;
   if (id == nfn) abort();
   const char *nm = fn[id].name;
-  node k = {id, NULL};
-  if (strstr(nm, "k_regularizer_x")) k.lost = ((xbuf *)args[9])->lost;
-  else if (strstr(nm, "k_prox_x")) k.lost = ((xbuf *)args[8])->lost;
+  node k = {id, NULL, NULL};
+  if (strstr(nm, "k_regularizer_x")) k.lost = ((xbuf *)args[9])->lost, k.res = *(result **)args[8];
+  else if (strstr(nm, "k_prox_x")) k.lost = ((xbuf *)args[8])->lost, k.res = *(result **)args[7];
   else if (strstr(nm, "k_node_init_x") || strstr(nm, "k_node_step_x")) k.lost = ((xbuf *)args[5])->lost;
-  if (strstr(nm, "k_prox_x") && *(int32_t **)args[7]) **(int32_t **)args[7] = 0;
-  if (strstr(nm, "k_regularizer_x") && *(int32_t **)args[8]) **(int32_t **)args[8] = 0;
   if (strstr(nm, "k_feat_prep"))
     for (int i = 3; i < 6; i++) nulls += *(void **)args[i] == NULL;
   if (loglen + 320 < sizeof logbuf) loglen += (size_t)sprintf(logbuf + loglen, "%s %u %u\n", nm, g.x, g.y);

@@ -60,3 +60,25 @@ def test_lost_exchange_in_the_gram_certificate(dev):
     again = ctx.solve(node, want_zeta=True, max_iter=40)
     assert again["lower_bound"] == good["lower_bound"] and torch.equal(again["zeta"], good["zeta"])
     ctx.close()
+
+
+@pytest.mark.parametrize("p,loss", [(16385, 0), (20000, 1), (262145, 1)])
+def test_lost_exchange_in_the_solve(dev, p, loss):
+    """beta = 0: the start's only exchange is lost by the last workgroup alone,
+    the first one completes."""
+    import torch
+    import paper_2603_01306_amd as pr
+    print(f"lost exchange solve p={p} loss={loss}", flush=True)
+    ctx, beta = _context(dev, p, n=16, loss=loss)
+    node = pr.Node(5, 1.0, 2.0)
+    kw = dict(max_iter=12, rel_gap_tol=0.0, L=50.0)
+    good = [ctx.solve(node, beta0=b0, **kw) for b0 in (None, beta)]
+    ctx.set_debug(pr.DEBUG_LOSE_EXCHANGE)
+    for b0 in (None, beta):
+        _edevice(lambda: ctx.solve(node, beta0=b0, **kw))
+    ctx.set_debug(0)
+    for b0, g in zip((None, beta), good):
+        again = ctx.solve(node, beta0=b0, **kw)
+        assert (again["lower_bound"], again["primal"]) == (g["lower_bound"], g["primal"])
+        assert torch.equal(again["beta"], g["beta"])
+    ctx.close()

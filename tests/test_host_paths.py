@@ -115,3 +115,39 @@ def test_lost_exchange_fails_the_gram_certificate(standin):
     si.si_lose(b"")
     assert call() == OK and np.all(z == 0.0)
     """)
+
+
+@pytest.mark.parametrize("kernel", ["k_node_init_x", "k_node_step_x"])
+def test_lost_exchange_fails_the_solve(standin, kernel):
+    """... whatever the first workgroup wrote into the node's state."""
+    run(standin, f"""
+    p = 17000
+    h, x = context(8, p), np.full(p, 7.0)
+    call = lambda: lib.pr_solve(h, nodes(1), opts(max_iter=3), None, P(x.ctypes.data), None, ctypes.byref(res))
+    si.si_lose({kernel.encode()!r})
+    assert call() == EDEVICE and np.all(x == 7.0)
+    si.si_lose(b"")
+    assert call() == OK and np.all(x == 0.0)
+    """)
+
+
+@pytest.mark.parametrize("p", [5000, 17000, 524288])
+def test_lost_exchange_fails_the_calls_without_a_context(standin, p):
+    """Any workgroup's loss counts, in every call and only in its own."""
+    run(standin, f"""
+    p = {p}
+    v, st, x = zeros(p), mem(np.zeros(p, np.int8)), zeros(p)
+    d = ctypes.c_double
+    ref, t0, t1, g, gs = ctypes.byref, d(), d(), d(), d()
+    calls = [(b"k_prox_x", lambda: lib.pr_prox(None, v, p, d(0.5), 3, d(2.0), st, x)),
+             (b"k_prox_x", lambda: lib.pr_prox_noalloc(None, v, p, d(0.5), 3, d(2.0), st, x)),
+             (b"k_prox_x", lambda: lib.pr_time_prox(None, v, p, d(0.5), 3, d(2.0), st, x, 2, ref(t0), ref(t1))),
+             (b"k_regularizer_x", lambda: lib.pr_regularizer(None, v, v, p, 3, d(2.0), st, ref(g), ref(gs)))]
+    for kernel, call in calls:
+        for _ in range(2):
+            assert call() == OK
+            g.value = gs.value = 7.0
+            si.si_lose(kernel)
+            assert call() == EDEVICE and g.value == gs.value == 7.0
+            si.si_lose(b"")
+    """)
