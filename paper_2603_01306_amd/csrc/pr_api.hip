@@ -302,7 +302,7 @@ hipError_t enqueue_unit(pr_ctx *c, hipStream_t s, int unit) {
                     &c->d_state->done, s, reg ? c->d_prm : nullptr, c->d_state, c->nb.sidx, c->nb.sval,
                     &c->d_state->nsupp, (reg && c->step_bt) ? c->B.dsum : nullptr, c->B.nfin);
   if (e != hipSuccess) return e;
-  if (const XShape g = node_xshape(c->P.p); g.wgs)
+  if (const XShape g = node_xshape(c->P.p, c->xb.cap); g.wgs)
     return launch_node_step_x(c->d_prm, c->d_state, c->nb, c->B, a, g, c->xb, s);
   return launch_node_step(c->d_prm, c->d_state, c->nb, c->B, c->P.p, s, &a);
 }
@@ -1030,13 +1030,13 @@ int batch_products(pr_ctx *c, int32_t m, int32_t *kst_out) {
 // The prox and the terms g_N(beta), g_N*(ascale alpha) of the feasible node whose
 // status is in c->d_status, on the context's stream.
 hipError_t ctx_prox(pr_ctx *c, const pr_node &node, int32_t kbar, double rho, const double *v, double *out) {
-  if (c->P.p <= reg_x_max())
+  if (reg_xshape(c->P.p, c->xb.cap).wgs)
     return launch_prox_x(v, out, c->P.p, rho, node.k, node.M, c->d_status, nullptr, c->xb, c->stream);
   return launch_prox(v, out, c->P.p, rho, kbar, node.M, c->d_status, c->d_regscratch, nullptr, c->stream);
 }
 hipError_t ctx_regularizer(pr_ctx *c, const pr_node &node, int32_t kbar, const double *beta, const double *alpha,
                            double ascale, double *out2) {
-  if (c->P.p <= reg_x_max())
+  if (reg_xshape(c->P.p, c->xb.cap).wgs)
     return launch_regularizer_x(beta, alpha, ascale, c->P.p, node.k, node.M, c->d_status, out2, nullptr, c->xb,
                                 c->stream);
   if (alpha) {
@@ -1218,6 +1218,7 @@ int pr_ctx_create(pr_ctx **out, const pr_problem *prob, int32_t max_batch, void 
   ok = ok && dalloc(&c->d_lam, 2 * kLanczosMax) == hipSuccess && dalloc(&c->d_vprev, p) == hipSuccess;
   ok = ok && dalloc(&c->d_regscratch, 3 * (size_t)p) == hipSuccess;
   ok = ok && dalloc(&c->xb.slots, kXwgWords + 1) == hipSuccess;
+  c->xb.cap = xwg_cap(c->stream);
   if (ok) c->xb.head = reinterpret_cast<uint32_t *>(c->xb.slots + kXwgWords);
   ok = ok && hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) == hipSuccess;
@@ -1540,7 +1541,7 @@ int pr_solve(pr_ctx *c, const pr_node *node, const pr_opts *opts_in, const doubl
   PR_TRY(hipMemcpyAsync(c->d_stage, c->h_stage, c->stage_st + (size_t)p, hipMemcpyHostToDevice, c->stream));
   if (opts.method == kAcfgmGap || opts.method == kAcfgm)
     return solve_acfgm(c, &opts, L, beta0, beta_out, zeta_out, out);
-  if (const XShape g = node_xshape(p); g.wgs)
+  if (const XShape g = node_xshape(p, c->xb.cap); g.wgs)
     PR_TRY(launch_node_init_x(c->d_prm, c->d_state, c->nb, beta0, L_init, g, c->xb, c->stream));
   else
     PR_TRY(launch_node_init(c->d_prm, c->d_state, c->nb, beta0, L_init, p, c->stream));
@@ -1586,7 +1587,7 @@ int pr_gemm(void *stream, const uint16_t *A, int64_t lda, const double *B, int64
   return PR_OK;
 }
 
-// Status counts of a context-free call on vectors past reg_x_max(): the status
+// Status counts of a context-free call on vectors that one workgroup takes from memory: the status
 // comes to the host, n1 = |J1|, nf = |J_f|.
 static int count_status(const int8_t *status, int64_t p, hipStream_t s, int64_t *n1, int64_t *nf) {
   std::vector<int8_t> st((size_t)p);
@@ -1607,9 +1608,10 @@ int pr_prox(void *stream, const double *v, int64_t p, double rho, int32_t k, dou
       !(M > 0.0) || k < 1)
     return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (p <= reg_x_max()) {
+  const int cap = reg_x_cap(p, s);
+  if (reg_xshape(p, cap).wgs) {
     XLease x;
-    const int rc = x.take(s);
+    const int rc = x.take(s, cap);
     if (rc != PR_OK) return rc;
     PR_TRY(launch_prox_x(v, out, p, rho, k, M, status, x.res, x.xb, s));
     PR_TRY(hipStreamSynchronize(s));
@@ -1642,10 +1644,11 @@ int pr_time_prox(void *stream, const double *v, int64_t p, double rho, int32_t k
   if (n1 > k) return PR_EINVAL;
   int64_t kb = (int64_t)k - n1;
   if (kb > nf) kb = nf;
-  const bool wide = p <= reg_x_max();
+  const int cap = reg_x_cap(p, s);
+  const bool wide = reg_xshape(p, cap).wgs != 0;
   XLease x;
   if (wide) {
-    const int rx = x.take(s);
+    const int rx = x.take(s, cap);
     if (rx != PR_OK) return rx;
   }
   double *abuf = nullptr, *g2 = nullptr;
@@ -1695,9 +1698,10 @@ int pr_regularizer(void *stream, const double *beta, const double *alpha, int64_
     return PR_EINVAL;
   if ((beta && !g_out) || (alpha && !gstar_out)) return PR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (p <= reg_x_max()) {
+  const int cap = reg_x_cap(p, s);
+  if (reg_xshape(p, cap).wgs) {
     XLease x;
-    const int rc = x.take(s);
+    const int rc = x.take(s, cap);
     if (rc != PR_OK) return rc;
     PR_TRY(launch_regularizer_x(beta, alpha, 1.0, p, k, M, status, x.res->v, x.res, x.xb, s));
     PR_TRY(hipStreamSynchronize(s));

@@ -144,7 +144,16 @@ struct XBuf {
   uint64_t *slots;
   uint32_t *head;
   uint64_t *lost;
+  int32_t cap;  // workgroups that may share a vector (xwg_cap; read by the host)
 };
+// Workgroups that wait for one another have to be resident together.  One of 512
+// threads fits any compute unit that has no other (256 VGPRs per lane at most), so
+// a launch takes at most a quarter of the compute units that its stream may use:
+// a process runs kernels from four hardware queues at once, and four such
+// launches then still fit.  All 256 compute units give kXwgMax; a stream with a
+// compute-unit mask or a partition of the device gives less, and vectors that do
+// not fit go through one workgroup.
+int xwg_cap(hipStream_t s);
 
 // What a kernel of a context-free entry point hands back.  The first workgroup
 // writes `flag` (0; 1: a status code outside {free, J0, J1}; 2: |J1| > k) and the
@@ -161,7 +170,7 @@ struct XResult {
 // its stream by then.
 class XLease {
  public:
-  int take(hipStream_t s);  // PR_OK or an error code
+  int take(hipStream_t s, int cap);  // PR_OK or an error code
   ~XLease();
   XBuf xb{};
   XResult *res = nullptr;
@@ -171,7 +180,7 @@ class XLease {
   uint64_t *own_ = nullptr;
 };
 // pr_prox_noalloc's own area and result (device memory) on the current device
-int xpool_noalloc(XBuf *xb, XResult **res);
+int xpool_noalloc(XBuf *xb, XResult **res, int cap);
 
 // AC-FGM state of a single-node solve (pr_variants.hip), device resident.
 struct AcState {
@@ -253,15 +262,16 @@ hipError_t launch_node_step(const NodeParams *prm, NodeState *S, NodeBufs nb, co
 struct XShape {
   int wgs, ept;  // workgroups, entries per thread; {0, 0}: one workgroup takes the step (pr_node.hip)
 };
-XShape node_xshape(int64_t p);
+XShape node_xshape(int64_t p, int cap);
 hipError_t launch_node_init_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const double *beta0, double L,
                               XShape g, const XBuf &xb, hipStream_t s);
 hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, const ProbBufs &B, const StepArgs &a,
                               XShape g, const XBuf &xb, hipStream_t s);
-// The standalone prox and regulariser over several workgroups, p <= reg_x_max();
-// kbar is counted from st.  res (optional) receives the flag and the tag; nothing
+// The standalone prox and regulariser over reg_xshape(p, xb.cap), which is not
+// {0, 0}; kbar is counted from st.  res (optional) receives the flag and the tag; nothing
 // else is written where the flag is not 0.
-int64_t reg_x_max();
+int reg_x_cap(int64_t p, hipStream_t s);  // xwg_cap(s), not asked for where one workgroup takes p anyway
+XShape reg_xshape(int64_t p, int cap);
 hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
                          XResult *res, const XBuf &xb, hipStream_t s);
 hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,

@@ -1,6 +1,6 @@
 // pr_prox_noalloc: the prox of g_N without any allocation, for callers that
 // cannot allocate device memory (code under stream capture, tight serving
-// loops, harnesses that forbid hipMalloc).  Vectors up to reg_x_max() stay in
+// loops, harnesses that forbid hipMalloc).  Vectors that reg_xshape has a shape for stay in
 // the registers of the workgroups that share them and need only the exchange
 // area this entry point owns; longer ones stage their magnitudes in a
 // file-scope device array.  Every GPU the library runs on holds its own copy of
@@ -54,10 +54,11 @@ int pr_prox_noalloc(void *stream, const double *v, int64_t p, double rho, int32_
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   int code = -1;
-  if (p <= reg_x_max()) {
+  const int cap = reg_x_cap(p, s);
+  if (reg_xshape(p, cap).wgs) {
     XBuf xb;
     XResult r{{0.0, 0.0}, 1, 0, -1}, *res = nullptr;
-    const int rc = xpool_noalloc(&xb, &res);
+    const int rc = xpool_noalloc(&xb, &res, cap);
     if (rc != PR_OK) return rc;
     e = launch_prox_x(v, out, p, rho, k, M, status, res, xb, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, s);

@@ -857,17 +857,17 @@ __global__ __launch_bounds__(NT) void k_regularizer_x(const double *__restrict__
 
 }  // namespace
 
-// Workgroups and entries per thread for a vector of p; {0, 0} where one
-// workgroup takes the step (pr_node.hip): up to 16384 entries its registers
-// hold the vector, and past kXwgMax * 16 * 512 the vector is too long for
-// this kernel's.  Between, few entries per thread are worth more workgroups:
+// Workgroups (at most cap) and entries per thread for a vector of p; {0, 0} where
+// one workgroup takes the step (pr_node.hip): up to 16384 entries its registers
+// hold the vector, and past cap * 16 * 512 (524288 with kXwgMax) the vector is
+// too long for this kernel's.  Between, few entries per thread are worth more workgroups:
 // p = 89989, 300 iterations, 56.5 ms with 4 (44 workgroups), 57.3 with 8, 59.6
 // with 16.
-XShape node_xshape(int64_t p) {
+XShape node_xshape(int64_t p, int cap) {
   if (p <= kXMin) return XShape{0, 0};
   for (int e = 4; e <= 16; e *= 2) {
     const int64_t w = (p + (int64_t)e * NT - 1) / ((int64_t)e * NT);
-    if (w <= kXwgMax) return XShape{(int)w, e};
+    if (w <= cap) return XShape{(int)w, e};
   }
   return XShape{0, 0};
 }
@@ -896,18 +896,17 @@ hipError_t launch_node_step_x(const NodeParams *prm, NodeState *S, NodeBufs nb, 
 }
 
 // Shape of the standalone kernels: one workgroup up to kXOne entries (its
-// reductions stay in LDS), then few entries per thread as above.
+// reductions stay in LDS), then few entries per thread and the same limits as above.
 constexpr int64_t kXOne = 4096;
-static XShape reg_xshape(int64_t p) {
+int reg_x_cap(int64_t p, hipStream_t s) { return p <= kXOne ? 1 : xwg_cap(s); }
+XShape reg_xshape(int64_t p, int cap) {
   for (int e = 1; e <= 16; e *= 2) {
     const int64_t w = (p + (int64_t)e * NT - 1) / ((int64_t)e * NT);
     if (w == 1 && p <= kXOne) return XShape{1, e};
-    if (p > kXOne && e >= 4 && w <= kXwgMax) return XShape{(int)w, e};
+    if (p > kXOne && e >= 4 && w <= cap) return XShape{(int)w, e};
   }
   return XShape{0, 0};
 }
-
-int64_t reg_x_max() { return (int64_t)kXwgMax * 16 * NT; }
 
 #define PR_REGX(CALL)        \
   switch (g.ept) {           \
@@ -920,7 +919,7 @@ int64_t reg_x_max() { return (int64_t)kXwgMax * 16 * NT; }
   }
 hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, int32_t k, double M, const int8_t *st,
                          XResult *res, const XBuf &xb, hipStream_t s) {
-  const XShape g = reg_xshape(p);
+  const XShape g = reg_xshape(p, xb.cap);
 #define PR_CALL(E) k_prox_x<E><<<g.wgs, NT, 0, s>>>(v, out, p, rho, k, M, st, res, xb)
   PR_REGX(PR_CALL)
 #undef PR_CALL
@@ -929,7 +928,7 @@ hipError_t launch_prox_x(const double *v, double *out, int64_t p, double rho, in
 
 hipError_t launch_regularizer_x(const double *beta, const double *alpha, double ascale, int64_t p, int32_t k,
                                 double M, const int8_t *st, double *out2, XResult *res, const XBuf &xb, hipStream_t s) {
-  const XShape g = reg_xshape(p);
+  const XShape g = reg_xshape(p, xb.cap);
 #define PR_CALL(E) k_regularizer_x<E><<<g.wgs, NT, 0, s>>>(beta, alpha, ascale, p, k, M, st, out2, res, xb)
   PR_REGX(PR_CALL)
 #undef PR_CALL

@@ -44,7 +44,19 @@ bool find_slots(int dev) {
 
 }  // namespace
 
-int XLease::take(hipStream_t s) {
+int xwg_cap(hipStream_t s) {
+  int cus = 0;
+  uint32_t mask[32] = {};
+  if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
+    for (uint32_t w : mask) cus += __builtin_popcount(w);
+  } else {
+    (void)hipGetLastError();
+  }
+  const int cap = cus / 4;
+  return cap < 1 ? 1 : (cap < kXwgMax ? cap : kXwgMax);
+}
+
+int XLease::take(hipStream_t s, int cap) {
   if (hipGetDevice(&dev_) != hipSuccess || dev_ < 0 || dev_ >= kDevices) return PR_EDEVICE;
   {
     std::lock_guard<std::mutex> lock(g_mu);
@@ -59,7 +71,7 @@ int XLease::take(hipStream_t s) {
       if (d.busy & (1u << i)) continue;
       d.busy |= 1u << i;
       slot_ = i;
-      xb = XBuf{d.slots + (size_t)i * kXwgWords, d.head + 2 * i, nullptr};
+      xb = XBuf{d.slots + (size_t)i * kXwgWords, d.head + 2 * i, nullptr, cap};
       res = g_res + dev_ * kSlots + i;
       break;
     }
@@ -74,7 +86,7 @@ int XLease::take(hipStream_t s) {
       return PR_ENOMEM;
     }
     if (hipMemsetAsync(own_, 0, sizeof(uint64_t) * (kXwgWords + 1), s) != hipSuccess) return PR_EDEVICE;
-    xb = XBuf{own_, reinterpret_cast<uint32_t *>(own_ + kXwgWords), nullptr};
+    xb = XBuf{own_, reinterpret_cast<uint32_t *>(own_ + kXwgWords), nullptr, cap};
   }
   *res = XResult{{0.0, 0.0}, 1, 0, -1};
   xb.lost = &res->lost;
@@ -93,12 +105,12 @@ XLease::~XLease() {
   }
 }
 
-int xpool_noalloc(XBuf *xb, XResult **res) {
+int xpool_noalloc(XBuf *xb, XResult **res, int cap) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return PR_EDEVICE;
   std::lock_guard<std::mutex> lock(g_mu);
   if (!find_slots(dev)) return PR_EDEVICE;
-  *xb = XBuf{g_dev[dev].slots, g_dev[dev].head, &g_dev[dev].result->lost};
+  *xb = XBuf{g_dev[dev].slots, g_dev[dev].head, &g_dev[dev].result->lost, cap};
   *res = g_dev[dev].result;
   return PR_OK;
 }

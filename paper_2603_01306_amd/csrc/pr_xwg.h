@@ -15,8 +15,7 @@
 // threads, up to 8 values, the reduction inside the workgroups included): 1.25
 // us per exchange with 8 workgroups, 1.37 with 16, 1.6 with 32, 2.1 with 64.
 //
-// All workgroups of the launch must be resident together; launches are
-// limited to kXwgMax = 64 workgroups of 512 threads on a 256-CU device.  A
+// All workgroups of the launch must be resident together (xwg_cap).  A
 // wait that outlasts kXwgTicks ends with `failed` set instead of a hang, and the
 // workgroup reports it in *XBuf::lost: what such a launch wrote is not to be used.
 // A nonzero test switch e in the area's head lets the last workgroup give up

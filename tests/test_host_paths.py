@@ -151,3 +151,40 @@ def test_lost_exchange_fails_the_calls_without_a_context(standin, p):
             assert call() == EDEVICE and g.value == gs.value == 7.0
             si.si_lose(b"")
     """)
+
+
+@pytest.mark.parametrize("cus", [256, 128, 32, 20, 4, 1])
+def test_shared_vectors_fit_the_compute_units(standin, cus):
+    """Workgroups that wait for one another number at most a quarter of the
+    compute units the stream may use, cover the vector, and keep the shapes of
+    the whole device where that is available; other vectors go through one
+    workgroup."""
+    run(standin, f"""
+    cus = {cus}
+    si.si_cus(cus)
+    d = ctypes.c_double
+    full = {{16385: (9, 4), 65536: (32, 4), 131072: (64, 4), 131073: (33, 8), 262145: (33, 16), 524288: (64, 16)}}
+    for p in (1, 4096, 4097, 16384, *full, 524289):
+        v, st, x, g = zeros(p), mem(np.zeros(p, np.int8)), zeros(p), d()
+        h = context(8, p)
+        si.si_clear()
+        assert lib.pr_solve(h, nodes(1), opts(max_iter=3), None, None, None, ctypes.byref(res)) == OK
+        assert lib.pr_dual_bound(h, nodes(1), None, v, ctypes.byref(g), ctypes.byref(g)) == OK
+        assert lib.pr_prox(None, v, p, d(0.5), 3, d(2.0), st, x) == OK
+        noalloc = lib.pr_prox_noalloc(None, v, p, d(0.5), 3, d(2.0), st, x)
+        assert lib.pr_regularizer(None, v, None, p, 3, d(2.0), st, ctypes.byref(g), None) == OK
+        shared = [(k, int(w)) for k, w, _ in log() if any(s in k for s in ("k_prox_x", "k_regularizer_x",
+                                                                           "k_node_init_x", "k_node_step_x"))]
+        one = [k for k, _, _ in log() if any(s in k for s in ("k_proxE", "k_prox_counted", "k_regularizerE"))]
+        for k, w in shared:
+            e = int(k.split("ILi")[1].split("E")[0])
+            assert w == 1 or 4 * w <= cus, (p, k, w)
+            assert w * e * 512 >= p > (w - 1) * e * 512, (p, k, w)
+            if cus == 256 and p in full:
+                assert (w, e) == full[p], (p, k, w)
+        fits = p <= 4096 or any(-(-p // (512 * e)) <= max(1, cus // 4) for e in (4, 8, 16))
+        assert bool(shared) == fits, (p, shared)
+        assert bool(one) == (not fits), (p, one)
+        lib.pr_ctx_destroy(h)
+        del keep[:]
+    """)
