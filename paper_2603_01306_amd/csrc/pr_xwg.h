@@ -16,12 +16,13 @@
 // us per exchange with 8 workgroups, 1.37 with 16, 1.6 with 32, 2.1 with 64.
 //
 // All workgroups of the launch must be resident together (xwg_cap).  A
-// wait that outlasts kXwgTicks ends with `failed` set instead of a hang, and the
+// wait of more than kXwgTicks (pr_wait.h) ends with `failed` set instead of a hang, and the
 // workgroup reports it in *XBuf::lost: what such a launch wrote is not to be used.
 // A nonzero test switch e in the area's head lets the last workgroup give up
 // at exchange e of every launch and the others after kLostTicks.
 #pragma once
 #include "pr_device.h"
+#include "pr_wait.h"
 
 namespace pr {
 namespace {
@@ -84,7 +85,7 @@ struct Group {
     uint64_t a = 0, b = 0;
     bool ok = !want;
     int spin = 0;
-    long long t0 = 0;
+    WaitClock t;
     for (;;) {
       if (!ok) {
         a = __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -92,13 +93,10 @@ struct Group {
         ok = (uint32_t)(a >> 32) == round && (uint32_t)(b >> 32) == round;
       }
       if (__all(ok)) break;
-      if ((++spin & 1023) == 0) {
-        const long long now = (long long)__builtin_amdgcn_s_memrealtime();
-        if (t0 == 0) t0 = now;
-        else if (now - t0 > (lose ? kLostTicks : kXwgTicks)) {
-          if (lane_id() == 0) L->bad = 1;
-          break;
-        }
+      if ((++spin & 1023) == 0 &&
+          t.expired((long long)__builtin_amdgcn_s_memrealtime(), lose ? kLostTicks : kXwgTicks)) {
+        if (lane_id() == 0) L->bad = 1;
+        break;
       }
     }
     return __longlong_as_double((long long)((a & 0xffffffffull) | (b << 32)));

@@ -188,3 +188,32 @@ def test_shared_vectors_fit_the_compute_units(standin, cus):
         lib.pr_ctx_destroy(h)
         del keep[:]
     """)
+
+
+def test_wait_clock_counts_polling_time(tmp_path):
+    """20 s of the limit are 20 s of looks a millisecond apart; an hour in which
+    the wave did not run adds 10 ms."""
+    src = tmp_path / "wait.cpp"
+    src.write_text(r"""
+#include "pr_wait.h"
+int main() {
+  const long long ms = 100000, limit = 20000 * ms;
+  pr::WaitClock a, b;
+  long long now = 5 * ms;
+  int looks = 0;
+  while (!a.expired(now, limit)) now += ms, looks++;
+  if (looks != 20001) return 1;
+  now = 7;
+  for (int i = 0; i < 100; i++, now += ms)
+    if (b.expired(now, limit)) return 2;
+  now += 3600ll * 1000 * ms;
+  if (b.expired(now, limit)) return 3;
+  for (int i = 0; i < 1000; i++)
+    if (b.expired(now += 3600ll * 1000 * ms, limit)) return 4;
+  return b.spent == 99 * ms + 1001 * pr::kWaitStep ? 0 : 5;
+}
+""")
+    exe = tmp_path / "wait"
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2603_01306_amd", "csrc"),
+                           str(src), "-o", str(exe)])
+    assert subprocess.run([str(exe)]).returncode == 0
