@@ -18,8 +18,8 @@
 // All workgroups of the launch must be resident together (xwg_cap).  A
 // wait of more than kXwgTicks (pr_wait.h) ends with `failed` set instead of a hang, and the
 // workgroup reports it in *XBuf::lost: what such a launch wrote is not to be used.
-// A nonzero test switch e in the area's head lets the last workgroup give up
-// at exchange e of every launch and the others after kLostTicks.
+// A test switch in the area's head lets the last workgroup give up the first
+// exchange of every launch and the others after kLostTicks.
 #pragma once
 #include "pr_device.h"
 #include "pr_wait.h"
@@ -42,13 +42,13 @@ __device__ __forceinline__ void put(uint64_t *w, uint32_t round, uint32_t half) 
 struct Lds {
   double red[2][NW * kQ];
   double res[2][kQ + 1];
-  int bad;
+  int bad;          // a wait of this workgroup was given up
+  long long ticks;  // limit of a wait
 };
 
 struct Group {
   uint64_t *slots;  // [2][kQ][kXwgMax][2] reductions, then [2][kXwgMax][kGat][2] gathers
   uint32_t round, round0;  // current, at the start of the launch
-  uint32_t lose;    // test switch
   int W, w;         // workgroups, this one
   Lds *L;
   int ph;
@@ -58,13 +58,16 @@ struct Group {
   __device__ __forceinline__ void init(const XBuf &xb, Lds *lds) {
     slots = xb.slots;
     round = round0 = xb.head[0];
-    lose = xb.head[1];
     W = (int)gridDim.x;
     w = (int)blockIdx.x;
     L = lds;
     ph = 0;
     failed = false;
-    if (threadIdx.x == 0) lds->bad = 0;
+    if (threadIdx.x == 0) {
+      const bool lose = xb.head[1] != 0;
+      lds->bad = lose && w > 0 && w == W - 1;
+      lds->ticks = lose ? kLostTicks : kXwgTicks;
+    }
   }
 
   __device__ __forceinline__ uint64_t *red_slot(int q, int v) const {
@@ -94,7 +97,7 @@ struct Group {
       }
       if (__all(ok)) break;
       if ((++spin & 1023) == 0 &&
-          t.expired((long long)__builtin_amdgcn_s_memrealtime(), lose ? kLostTicks : kXwgTicks)) {
+          t.expired((long long)__builtin_amdgcn_s_memrealtime(), L->ticks)) {
         if (lane_id() == 0) L->bad = 1;
         break;
       }
@@ -149,7 +152,7 @@ struct Group {
     }
     take();
     lds_barrier();
-    failed = L->bad != 0 || (lose && w > 0 && w == W - 1 && round - round0 == lose);
+    failed = L->bad != 0;
     ph ^= 1;
   }
 
