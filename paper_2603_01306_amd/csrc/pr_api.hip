@@ -1948,17 +1948,19 @@ int grad_images(pr_ctx *c, int32_t m, const double *Bp) {
   return PR_OK;
 }
 
-// Whether m images go faster together: the two GEMMs at m rows (the tables hold
-// whole tiles of 64 rows; one tile of 16 / 32 / 48 rows takes 0.37 / 0.58 / 0.79
-// of one) against two passes over X per node (16384 x 8192 in BF16: 0.2 ms up
-// to 16 nodes and 0.55 at 64, against 0.1 per node).
+// Whether m images go faster together, by the two GEMMs, than by two passes over
+// X each.  From two nodes on they do, for every storage type, loss and shape
+// tried (a call for 2 nodes together / one by one: 16384 x 8192 in BF16 288 / 317
+// us, FP32 330 / 437, FP64 451 / 804; 32768 x 16384 logistic BF16 866 / 912; 2048
+// x 16384 BF16 139 / 198; 131072 x 128 151 / 532; 512 x 512 FP64 74 / 83 to 102).
+// For one node two passes cost less than the two products (176 against 290 us at
+// 16384 x 8192 in BF16, 231 / 334 in FP32, 57 / 70 at 256 x 1152), but not where X^T r
+// has few columns to share out (131072 x 128: 278 / 150): the times measured for
+// the context decide, of one tile of 64 rows, or of fewer where the context
+// batches fewer nodes.
 bool images_pay(const pr_ctx *c, int32_t m) {
   if (!c->batch_ok) return false;
-  auto cost = [&](int table, int rows) {
-    const int r16 = (rows + 15) / 16, nta = std::min(nr_of(rows) / 64, kTuneMax - 1);
-    return c->h_tbest[table * kTuneMax + nta] * (r16 < 4 ? 0.16 + 0.21 * r16 : 1.0);
-  };
-  return 2.0 * m * c->t_gemv_ms >= cost(0, m) + cost(1, c->rs * m);
+  return m > 1 || 2.0 * c->t_gemv_ms >= c->h_tbest[1] + c->h_tbest[kTuneMax + 1];
 }
 
 }  // namespace

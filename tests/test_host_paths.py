@@ -217,3 +217,22 @@ int main() {
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2603_01306_amd", "csrc"),
                            str(src), "-o", str(exe)])
     assert subprocess.run([str(exe)]).returncode == 0
+
+
+@pytest.mark.parametrize("max_batch", [8, 256])
+@pytest.mark.parametrize("loss", [0, 1])
+def test_route_of_the_feature_images(standin, max_batch, loss):
+    """One node goes through the batch's GEMMs only where two passes over X cost
+    more than those, as timed for the context; two or more always."""
+    run(standin, f"""
+    for gemm, together in ((10.0, False), (100.0, False), (2.0, True)):
+        si.si_cost(b"k_gemv", 6.0)
+        si.si_cost(b"k_spfwd", 0.0)
+        si.si_cost(b"k_gemm", gemm)
+        h, F = context(128, 1024, loss={loss}, max_batch={max_batch}), mem(np.zeros((3, 1024, 8), np.uint16))
+        for m in (1, 2, 3):
+            si.si_clear()
+            assert lib.pr_mlp_features(h, nodes(m), m, zeros(m, 1024), None, F, None) == OK
+            assert any("k_gemm" in ln[0] for ln in log()) == (together or m > 1), (gemm, m)
+        lib.pr_ctx_destroy(h)
+    """)
