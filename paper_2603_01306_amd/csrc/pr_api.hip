@@ -1990,7 +1990,9 @@ int pr_mlp_features(pr_ctx *c, const pr_node *nodes, int32_t m, const double *Bp
     const double *bp = Bparent + (int64_t)i * p, *w = c->d_w;
     int8_t *dst = batch ? c->bstatus : c->d_status;
     PR_TRY(hipMemcpyAsync(dst, sts.data() + (size_t)i * p, (size_t)mq * p, hipMemcpyHostToDevice, s));
-    PR_TRY(hipMemcpyAsync(c->fb.sc, scs.data() + i, sizeof(FeatScalars) * mq, hipMemcpyHostToDevice, s));
+    // a second upload waits for the first: 25 us
+    const FeatScalars *one = mq == 1 ? &scs[(size_t)i] : nullptr;
+    if (!one) PR_TRY(hipMemcpyAsync(c->fb.sc, scs.data() + i, sizeof(FeatScalars) * mq, hipMemcpyHostToDevice, s));
     if (batch) {
       rc = grad_images(c, mq, bp);
       w = c->mWb;
@@ -1998,7 +2000,7 @@ int pr_mlp_features(pr_ctx *c, const pr_node *nodes, int32_t m, const double *Bp
       rc = grad_image(c, bp);
     }
     if (rc != PR_OK) return rc;
-    PR_TRY(launch_features(bp, w, dst, p, mq, c->fb, Bchild ? Bchild + (int64_t)i * p : nullptr,
+    PR_TRY(launch_features(bp, w, dst, p, mq, c->fb, one, Bchild ? Bchild + (int64_t)i * p : nullptr,
                            F + (int64_t)i * p * 8, T ? T + (int64_t)i * p : nullptr, s));
     i += mq;
   }
@@ -2103,7 +2105,7 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
       fsc[(size_t)q] = feat_scalars(&nodes[i], p, n1s[i], pbars[i], kbars[i]);
     }
     PR_TRY(hipMemcpyAsync(c->fb.sc, fsc.data(), sizeof(FeatScalars) * mb, hipMemcpyHostToDevice, s));
-    PR_TRY(launch_features(c->mVb, c->mWb, c->bstatus, p, mb, c->fb, nullptr, c->mFb, nullptr, s));
+    PR_TRY(launch_features(c->mVb, c->mWb, c->bstatus, p, mb, c->fb, nullptr, nullptr, c->mFb, nullptr, s));
     PR_TRY(launch_mlp_forward(params, c->mFb, (int64_t)mb * p, c->moutb, s));
     PR_TRY(launch_mlp_propose(c->mVb, c->moutb, (int64_t)mb * p, c->mVb, s));
     PR_TRY(launch_prox_batch(c->d_bprm, c->mVb, c->bxbest, c->cert_a, p, mb, 1.0 / L, s));
@@ -2170,8 +2172,7 @@ int pr_mlp_warm_start(pr_ctx *c, const pr_node *nodes, int32_t m, const float *p
       if (params) {  // the network's proposal first: d_w still holds X^T zeta at the parent
         const FeatScalars sc =
             feat_scalars(&nodes[i], p, n1s[(size_t)i], pbars[(size_t)i], kbars[(size_t)i]);
-        PR_TRY(hipMemcpyAsync(c->fb.sc, &sc, sizeof(sc), hipMemcpyHostToDevice, s));
-        PR_TRY(launch_features(bp, c->d_w, c->d_status, p, 1, c->fb, nullptr, c->mF, nullptr, s));
+        PR_TRY(launch_features(bp, c->d_w, c->d_status, p, 1, c->fb, &sc, nullptr, c->mF, nullptr, s));
         PR_TRY(launch_mlp_forward(params, c->mF, p, c->mout, s));
         PR_TRY(launch_mlp_propose(bp, c->mout, p, c->mvhat, s));
         PR_TRY(ctx_prox(c, nodes[i], kbars[(size_t)i], rho, c->mvhat, c->mvhat));

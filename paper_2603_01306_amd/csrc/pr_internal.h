@@ -350,9 +350,11 @@ struct FeatBufs {
   int cap;
 };
 // feature rows (and with beta_child the targets) of m <= fb.cap nodes, vectors
-// node-major [m][p], fb.sc filled
+// node-major [m][p]; their scalars are in fb.sc, or those of a single node in
+// *one, which goes with the launch and needs no upload
 hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, int m,
-                           const FeatBufs &fb, const double *beta_child, uint16_t *F, float *T, hipStream_t s);
+                           const FeatBufs &fb, const FeatScalars *one, const double *beta_child, uint16_t *F, float *T,
+                           hipStream_t s);
 hipError_t launch_mlp_propose(const double *beta, const float *out, int64_t p, double *vhat, hipStream_t s);
 hipError_t launch_zbest_final(const NodeState *S, const ProbBufs &B, int32_t loss, int64_t n,
                               hipStream_t s);

@@ -520,14 +520,14 @@ __global__ __launch_bounds__(256) void k_feat_rank(const double *__restrict__ nz
 __global__ __launch_bounds__(256) void k_feat_rows(const double *__restrict__ beta, const double *__restrict__ w,
                                                    const int8_t *__restrict__ st, int64_t p,
                                                    const int32_t *__restrict__ rank, const double *__restrict__ fs,
-                                                   const FeatScalars *__restrict__ scs,
+                                                   const FeatScalars *__restrict__ scs, FeatScalars one,
                                                    const double *__restrict__ beta_child, uint16_t *__restrict__ F,
                                                    float *__restrict__ T) {
   const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (jj >= p) return;
   const int64_t j = (int64_t)blockIdx.y * p + jj;
   const double hm = fs[2 * blockIdx.y], nnz = fs[2 * blockIdx.y + 1];
-  const FeatScalars sc = scs[blockIdx.y];
+  const FeatScalars sc = scs ? scs[blockIdx.y] : one;
   const double b = beta[j];
   const int s = st[j];
   double f[kNF];
@@ -589,8 +589,9 @@ hipError_t launch_mlp_adam(float *P, const float *g, float *m1, float *m2, float
 }
 
 hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, int m,
-                           const FeatBufs &fb, const double *beta_child, uint16_t *F, float *T, hipStream_t s) {
-  if (m < 1 || m > 65535) return hipErrorInvalidValue;
+                           const FeatBufs &fb, const FeatScalars *one, const double *beta_child, uint16_t *F, float *T,
+                           hipStream_t s) {
+  if (m < 1 || m > 65535 || (one && m != 1)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((p + 255) / 256), (unsigned)m);
   k_feat_prep<<<(unsigned)m, dev::NT, 0, s>>>(beta, w, p, fb.nzv, fb.nzi, fb.fs);
   hipError_t e = hipGetLastError();
@@ -598,7 +599,8 @@ hipError_t launch_features(const double *beta, const double *w, const int8_t *st
   k_feat_rank<<<grid, 256, 0, s>>>(fb.nzv, fb.nzi, fb.fs, p, fb.rank);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_feat_rows<<<grid, 256, 0, s>>>(beta, w, st, p, fb.rank, fb.fs, fb.sc, beta_child, F, T);
+  k_feat_rows<<<grid, 256, 0, s>>>(beta, w, st, p, fb.rank, fb.fs, one ? nullptr : fb.sc, one ? *one : FeatScalars{},
+                                    beta_child, F, T);
   return hipGetLastError();
 }
 

@@ -236,3 +236,14 @@ def test_route_of_the_feature_images(standin, max_batch, loss):
             assert any("k_gemm" in ln[0] for ln in log()) == (together or m > 1), (gemm, m)
         lib.pr_ctx_destroy(h)
     """)
+
+
+def test_one_nodes_features_take_one_upload(standin):
+    """The status of the node; its scalars go with the launch."""
+    run(standin, """
+    h, F = context(8, 300), mem(np.zeros((3, 300, 8), np.uint16))
+    for m in (1, 3):
+        si.si_clear()
+        assert lib.pr_mlp_features(h, nodes(m), m, zeros(m, 300), None, F, None) == OK
+        assert si.si_copies() == m
+    """)
