@@ -1954,7 +1954,7 @@ int grad_images(pr_ctx *c, int32_t m, const double *Bp) {
 // us, FP32 330 / 437, FP64 451 / 804; 32768 x 16384 logistic BF16 866 / 912; 2048
 // x 16384 BF16 139 / 198; 131072 x 128 151 / 532; 512 x 512 FP64 74 / 83 to 102).
 // For one node two passes cost less than the two products (176 against 290 us at
-// 16384 x 8192 in BF16, 231 / 334 in FP32, 57 / 70 at 256 x 1152), but not where X^T r
+// 16384 x 8192 in BF16, 231 / 334 in FP32, 43 / 70 at 256 x 1152), but not where X^T r
 // has few columns to share out (131072 x 128: 278 / 150): the times measured for
 // the context decide, of one tile of 64 rows, or of fewer where the context
 // batches fewer nodes.

@@ -517,23 +517,44 @@ __global__ __launch_bounds__(256) void k_feat_rank(const double *__restrict__ nz
   }
 }
 
+// The rows.  With RANK the ranks are counted here, every lane's against LDS tiles
+// of the whole list, and there is no launch of k_feat_rank.
+template <bool RANK>
 __global__ __launch_bounds__(256) void k_feat_rows(const double *__restrict__ beta, const double *__restrict__ w,
                                                    const int8_t *__restrict__ st, int64_t p,
-                                                   const int32_t *__restrict__ rank, const double *__restrict__ fs,
+                                                   const double *__restrict__ nzv, const int32_t *__restrict__ rank,
+                                                   const double *__restrict__ fs,
                                                    const FeatScalars *__restrict__ scs, FeatScalars one,
                                                    const double *__restrict__ beta_child, uint16_t *__restrict__ F,
                                                    float *__restrict__ T) {
   const int64_t jj = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (jj >= p) return;
   const int64_t j = (int64_t)blockIdx.y * p + jj;
   const double hm = fs[2 * blockIdx.y], nnz = fs[2 * blockIdx.y + 1];
   const FeatScalars sc = scs ? scs[blockIdx.y] : one;
-  const double b = beta[j];
+  const double b = jj < p ? beta[j] : 0.0;
+  int r = 0;
+  if constexpr (RANK) {
+    __shared__ __align__(16) double tile[kRankTile];
+    const double *list = nzv + (int64_t)blockIdx.y * p;
+    const int len = (int)nnz;
+    const double a = fabs(b);
+    const bool any = __any(b != 0.0);
+    for (int t0 = 0; t0 < len; t0 += kRankTile) {
+      __syncthreads();
+      for (int t = threadIdx.x; t < kRankTile; t += 256) tile[t] = t0 + t < len ? list[t0 + t] : 0.0;
+      __syncthreads();
+      const int e = any ? ((len - t0 < kRankTile ? len - t0 : kRankTile) + 7) & ~7 : 0;
+#pragma unroll 8
+      for (int t = 0; t < e; t++) r += tile[t] > a;
+    }
+  }
+  if (jj >= p) return;
+  if constexpr (!RANK) r = b != 0.0 ? rank[j] : 0;
   const int s = st[j];
   double f[kNF];
   f[0] = b;
   f[1] = hm > 0.0 ? w[j] / hm : 0.0;
-  f[2] = (b != 0.0 ? (double)rank[j] : nnz) / (double)p;
+  f[2] = (b != 0.0 ? (double)r : nnz) / (double)p;
   f[3] = s == kZero ? -1.0 : (s == kOne ? 1.0 : 0.0);
   f[4] = sc.lambda2;
   f[5] = (double)sc.n1 / sc.k;
@@ -588,6 +609,13 @@ hipError_t launch_mlp_adam(float *P, const float *g, float *m1, float *m2, float
   return hipGetLastError();
 }
 
+// A single node of p <= 4096 has its ranks counted by the kernel that writes its
+// rows: the launch of k_feat_rank was the eighth operation of a one-node call, and
+// from the eighth on the runtime's wait takes some 20 us longer (512 x 512: 40-44 us
+// with neither it nor a second upload, 67 with the launch, 41 so; 256 x 1152 54,
+// 68, 43; 512 x 4096 94, 67, 53).  At 8192 both take 70 us, at 16384 (a seventh of
+// the entries nonzero) 91 with the launch and 100 without.
+constexpr int64_t kRankRows = 4096;
 hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, int m,
                            const FeatBufs &fb, const FeatScalars *one, const double *beta_child, uint16_t *F, float *T,
                            hipStream_t s) {
@@ -596,11 +624,15 @@ hipError_t launch_features(const double *beta, const double *w, const int8_t *st
   k_feat_prep<<<(unsigned)m, dev::NT, 0, s>>>(beta, w, p, fb.nzv, fb.nzi, fb.fs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (one && p <= kRankRows) {
+    k_feat_rows<true><<<grid, 256, 0, s>>>(beta, w, st, p, fb.nzv, nullptr, fb.fs, nullptr, *one, beta_child, F, T);
+    return hipGetLastError();
+  }
   k_feat_rank<<<grid, 256, 0, s>>>(fb.nzv, fb.nzi, fb.fs, p, fb.rank);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_feat_rows<<<grid, 256, 0, s>>>(beta, w, st, p, fb.rank, fb.fs, one ? nullptr : fb.sc, one ? *one : FeatScalars{},
-                                    beta_child, F, T);
+  k_feat_rows<false><<<grid, 256, 0, s>>>(beta, w, st, p, fb.nzv, fb.rank, fb.fs, one ? nullptr : fb.sc,
+                                          one ? *one : FeatScalars{}, beta_child, F, T);
   return hipGetLastError();
 }
 

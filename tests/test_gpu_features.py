@@ -54,3 +54,29 @@ def test_features_of_many_nodes(dev, max_batch, m, loss):
     with pytest.raises(pr.PrError):
         ctx.mlp_features([nodes[0], pr.Node(k, 0.3, 2.0, J0=[p])], torch.from_numpy(Bp[:2]).to(dev))
     ctx.close()
+
+
+@pytest.mark.parametrize("p", [1, 257, 1152, 4096, 4097])
+def test_features_of_one_node(dev, p):
+    """One node's rows on both sides of the size from which its ranks get a
+    launch of their own (4096 | 4097), supports of every size around the list's
+    tiles: against the oracle as above, ranks exactly."""
+    import torch
+    import paper_2603_01306_amd as pr
+    print(f"features of one node p={p}", flush=True)
+    n, k = 8, 6
+    rng = np.random.default_rng(p)
+    X = rng.standard_normal((p, n)).astype(np.float32)
+    y = X[:4].astype(np.float64).sum(axis=0) + rng.standard_normal(n)
+    ctx = pr.Context(torch.from_numpy(X).to(dev), torch.from_numpy(y).to(dev), 0)
+    X64 = X.astype(np.float64)
+    for nnz in sorted({min(v, p) for v in (0, 1, 255, 1023, 1024, 1025, p)}):
+        at = rng.permutation(p)
+        b = np.zeros(p)
+        b[at[:nnz]] = np.round(0.02 * rng.standard_normal(nnz), 3)  # ties and more zeros
+        nd = pr.Node(k, 0.3, 2.0, J0=at[: min(3, p - 1)], J1=at[3:5])
+        F = ctx.mlp_features([nd], torch.from_numpy(b[None]).to(dev))[0].float().cpu().numpy().astype(np.float64)
+        ref = omlp.features(b, X64 @ (2.0 * (y - b @ X64)), nd.status(p), nd.lambda2, nd.k)
+        assert np.all(np.abs(F - _bf16(ref)) <= 2 * U * np.abs(ref) + 1e-30), nnz
+        assert np.array_equal(F[:, 2], _bf16(ref[:, 2])), nnz
+    ctx.close()

@@ -247,3 +247,15 @@ def test_one_nodes_features_take_one_upload(standin):
         assert lib.pr_mlp_features(h, nodes(m), m, zeros(m, 300), None, F, None) == OK
         assert si.si_copies() == m
     """)
+
+
+@pytest.mark.parametrize("p,ops", [(300, 7), (4096, 7), (4097, 8)])
+def test_operations_of_a_one_node_feature_call(standin, p, ops):
+    """Upload and launches together: seven, as many as the runtime waits for
+    without a detour; longer vectors have their ranks counted in a launch."""
+    run(standin, f"""
+    h, F = context(8, {p}), mem(np.zeros((1, {p}, 8), np.uint16))
+    si.si_clear()
+    assert lib.pr_mlp_features(h, nodes(1), 1, zeros(1, {p}), None, F, None) == OK
+    assert si.si_copies() + len(log()) == {ops}
+    """)
