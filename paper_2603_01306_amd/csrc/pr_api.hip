@@ -150,7 +150,7 @@ struct pr_ctx {
   // learned warm start (allocated on first use)
   uint16_t *mF = nullptr;  // [p][8] features of one node
   float *mout = nullptr;   // [p] network outputs
-  FeatBufs fb{};           // feature scratch, fb.cap nodes (one, or max_batch on the batched path)
+  FeatBufs fb{};           // feature scratch, fb.cap nodes (one, or up to max_batch on the batched path)
   double *mvhat = nullptr, *mx = nullptr;  // [p] proposal before / after the prox step
   // batched warm start: proposals, w = X^T zeta at the parents [max_batch padded][p],
   // feature rows [..][p][8], network outputs [..][p]
@@ -1902,7 +1902,7 @@ int ensure_mlp(pr_ctx *c) {
   if (c->mF) return PR_OK;
   const int64_t p = c->P.p;
   bool ok = dalloc(&c->mF, (size_t)p * 8) == hipSuccess && dalloc(&c->mout, (size_t)p) == hipSuccess;
-  const int cap = c->batch_ok ? c->max_batch : 1;
+  const int cap = c->batch_ok ? std::min(c->max_batch, kFeatNodes) : 1;
   FeatBufs &f = c->fb;
   ok = ok && dalloc(&f.nzv, (size_t)cap * p) == hipSuccess && dalloc(&f.nzi, (size_t)cap * p) == hipSuccess;
   ok = ok && dalloc(&f.rank, (size_t)cap * p) == hipSuccess && dalloc(&f.fs, 2 * (size_t)cap) == hipSuccess;
@@ -2104,8 +2104,13 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
       const size_t i = (size_t)slot_of[(size_t)q];
       fsc[(size_t)q] = feat_scalars(&nodes[i], p, n1s[i], pbars[i], kbars[i]);
     }
-    PR_TRY(hipMemcpyAsync(c->fb.sc, fsc.data(), sizeof(FeatScalars) * mb, hipMemcpyHostToDevice, s));
-    PR_TRY(launch_features(c->mVb, c->mWb, c->bstatus, p, mb, c->fb, nullptr, nullptr, c->mFb, nullptr, s));
+    for (int32_t q = 0; q < mb; q += c->fb.cap) {
+      const int32_t cnt = std::min(mb - q, c->fb.cap);
+      const int64_t o = (int64_t)q * p;
+      PR_TRY(hipMemcpyAsync(c->fb.sc, fsc.data() + q, sizeof(FeatScalars) * cnt, hipMemcpyHostToDevice, s));
+      PR_TRY(launch_features(c->mVb + o, c->mWb + o, c->bstatus + o, p, cnt, c->fb, nullptr, nullptr, c->mFb + o * 8,
+                             nullptr, s));
+    }
     PR_TRY(launch_mlp_forward(params, c->mFb, (int64_t)mb * p, c->moutb, s));
     PR_TRY(launch_mlp_propose(c->mVb, c->moutb, (int64_t)mb * p, c->mVb, s));
     PR_TRY(launch_prox_batch(c->d_bprm, c->mVb, c->bxbest, c->cert_a, p, mb, 1.0 / L, s));

@@ -340,6 +340,7 @@ hipError_t launch_mlp_grad(const float *P, const uint16_t *F, const float *T, in
                            float *grad, hipStream_t s);
 hipError_t launch_mlp_adam(float *P, const float *g, float *m1, float *m2, float lr, float beta1, float beta2,
                            float eps, float c1, float c2, hipStream_t s);
+constexpr int kFeatNodes = 65535;  // nodes of one launch of the feature kernels at most (their grid.y)
 // Scratch of the feature kernels for up to `cap` nodes: nonzero magnitudes and
 // their coordinates, ranks [cap][p], {max |w|, nnz} and the scalars per node.
 struct FeatBufs {

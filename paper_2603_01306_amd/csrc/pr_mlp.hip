@@ -619,7 +619,7 @@ constexpr int64_t kRankRows = 4096;
 hipError_t launch_features(const double *beta, const double *w, const int8_t *st, int64_t p, int m,
                            const FeatBufs &fb, const FeatScalars *one, const double *beta_child, uint16_t *F, float *T,
                            hipStream_t s) {
-  if (m < 1 || m > 65535 || (one && m != 1)) return hipErrorInvalidValue;
+  if (m < 1 || m > kFeatNodes || (one && m != 1)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((p + 255) / 256), (unsigned)m);
   k_feat_prep<<<(unsigned)m, dev::NT, 0, s>>>(beta, w, p, fb.nzv, fb.nzi, fb.fs);
   hipError_t e = hipGetLastError();

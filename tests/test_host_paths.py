@@ -259,3 +259,18 @@ def test_operations_of_a_one_node_feature_call(standin, p, ops):
     assert lib.pr_mlp_features(h, nodes(1), 1, zeros(1, {p}), None, F, None) == OK
     assert si.si_copies() + len(log()) == {ops}
     """)
+
+
+def test_features_of_more_nodes_than_a_launch_takes(standin):
+    run(standin, """
+    m, p = 65600, 128
+    h, F = context(128, p, max_batch=m), mem(np.zeros((m, p, 8), np.uint16))
+    si.si_clear()
+    assert lib.pr_mlp_features(h, nodes(m), m, zeros(m, p), None, F, None) == OK
+    rows = [int(y) for k, _, y in log() if "k_feat_rows" in k]
+    assert sum(rows) == m and max(int(y) for _, _, y in log()) <= 65535
+    params = mem(np.zeros(b.MLP_NPARAM, np.float32))
+    si.si_clear()
+    lib.pr_mlp_warm_start(h, nodes(m), m, params, zeros(m, p), zeros(m, p), None, None)
+    assert sum(int(y) for k, _, y in log() if "k_feat_rows" in k) == m
+    """)
