@@ -25,7 +25,18 @@ size_t esize(int xdt) { return xdt == kF64 ? 8 : (xdt == kF32 ? 4 : 2); }
 
 template <typename T>
 hipError_t dalloc(T **p, size_t count) {
-  return hipMalloc((void **)p, sizeof(T) * (count > 0 ? count : 1));
+  const hipError_t e = hipMalloc((void **)p, sizeof(T) * (count > 0 ? count : 1));
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();  // reported here, not by a later launch
+  }
+  return e;
+}
+// A buffer allocated on first use.  Where one of several cannot be, the call
+// ends with PR_ENOMEM; the others stay, and a later call asks for the rest.
+template <typename T>
+bool need(T **p, size_t count) {
+  return *p || dalloc(p, count) == hipSuccess;
 }
 
 constexpr int kLanczosMax = 512;   // Lanczos steps for ||X||_2^2 at most
@@ -967,14 +978,10 @@ int build_union(pr_ctx *c, int32_t m, bool fresh, bool *changed) {
   *changed = false;
   if (fresh) c->union_on = false;
   if (kpmax < gran) return PR_OK;
-  if (!c->d_umask) {
-    bool ok = dalloc(&c->d_umask, p) == hipSuccess && dalloc(&c->d_ulist, p) == hipSuccess;
-    ok = ok && dalloc(&c->d_olist, p) == hipSuccess && dalloc(&c->d_ocnt, NrMax) == hipSuccess;
-    ok = ok && dalloc(&c->d_oidx, (size_t)NrMax * p) == hipSuccess;
-    ok = ok && dalloc(&c->d_oval, (size_t)NrMax * p) == hipSuccess;
-    ok = ok && dalloc(&c->BxU, (size_t)NrMax * (3 * p / 4)) == hipSuccess;
-    if (!ok) return PR_ENOMEM;
-  }
+  if (!need(&c->d_umask, p) || !need(&c->d_ulist, p) || !need(&c->d_olist, p) || !need(&c->d_ocnt, NrMax) ||
+      !need(&c->d_oidx, (size_t)NrMax * p) || !need(&c->d_oval, (size_t)NrMax * p) ||
+      !need(&c->BxU, (size_t)NrMax * (3 * p / 4)))
+    return PR_ENOMEM;
   if (c->gram && !c->GU && dalloc(&c->GU, (size_t)p * (3 * p / 4)) != hipSuccess) return PR_ENOMEM;
   if (!c->gram && !c->XrU && hipMalloc(&c->XrU, esize(c->P.xdt) * (size_t)n * (3 * p / 4)) != hipSuccess)
     return PR_ENOMEM;
@@ -1089,10 +1096,7 @@ int certify_batch(pr_ctx *c, int32_t m, std::vector<double> &lb, std::vector<dou
   const int64_t p = c->P.p;
   const int NrMax = nr_of(c->max_batch), NrT = nr_of(c->rs * m);
   hipStream_t s = c->stream;
-  if (!c->cert_a) {
-    bool ok = dalloc(&c->cert_a, (size_t)NrMax * p) == hipSuccess && dalloc(&c->d_cert, 2 * (size_t)NrMax) == hipSuccess;
-    if (!ok) return PR_ENOMEM;
-  }
+  if (!need(&c->cert_a, (size_t)NrMax * p) || !need(&c->d_cert, 2 * (size_t)NrMax)) return PR_ENOMEM;
   PR_TRY(hipMemcpyAsync(c->Bx, c->bxbest, sizeof(double) * m * p, hipMemcpyDeviceToDevice, s));
   int32_t kst = 1;
   const int rc = batch_products(c, m, &kst);
@@ -1899,17 +1903,25 @@ int pr_time_batch_gemm(pr_ctx *c, int32_t m, int32_t reps, double *ms_fwd, doubl
 namespace {
 
 int ensure_mlp(pr_ctx *c) {
-  if (c->mF) return PR_OK;
+  if (c->fb.cap) return PR_OK;
   const int64_t p = c->P.p;
-  bool ok = dalloc(&c->mF, (size_t)p * 8) == hipSuccess && dalloc(&c->mout, (size_t)p) == hipSuccess;
-  const int cap = c->batch_ok ? std::min(c->max_batch, kFeatNodes) : 1;
-  FeatBufs &f = c->fb;
-  ok = ok && dalloc(&f.nzv, (size_t)cap * p) == hipSuccess && dalloc(&f.nzi, (size_t)cap * p) == hipSuccess;
-  ok = ok && dalloc(&f.rank, (size_t)cap * p) == hipSuccess && dalloc(&f.fs, 2 * (size_t)cap) == hipSuccess;
-  ok = ok && dalloc(&f.sc, (size_t)cap) == hipSuccess;
-  f.cap = cap;
-  ok = ok && dalloc(&c->mvhat, (size_t)p) == hipSuccess && dalloc(&c->mx, (size_t)p) == hipSuccess;
-  return ok ? PR_OK : PR_ENOMEM;
+  if (!need(&c->mF, (size_t)p * 8) || !need(&c->mout, (size_t)p) || !need(&c->mvhat, (size_t)p) ||
+      !need(&c->mx, (size_t)p))
+    return PR_ENOMEM;
+  // scratch for a batch of nodes, or for one where there is no room for that
+  for (int cap = c->batch_ok ? std::min(c->max_batch, kFeatNodes) : 1;; cap = 1) {
+    FeatBufs f{};
+    const size_t cp = (size_t)cap * p;
+    if (need(&f.nzv, cp) && need(&f.nzi, cp) && need(&f.rank, cp) && need(&f.fs, 2 * (size_t)cap) &&
+        need(&f.sc, (size_t)cap)) {
+      c->fb = f;
+      c->fb.cap = cap;
+      return PR_OK;
+    }
+    for (void *b : {(void *)f.nzv, (void *)f.nzi, (void *)f.rank, (void *)f.fs, (void *)f.sc})
+      if (b) (void)hipFree(b);
+    if (cap == 1) return PR_ENOMEM;
+  }
 }
 
 FeatScalars feat_scalars(const pr_node *node, int64_t p, int64_t n1, int64_t pbar, int32_t kbar) {
@@ -1934,11 +1946,10 @@ int grad_image(pr_ctx *c, const double *beta) {
 }
 
 // The same of m nodes (rows of Bp) in the rows of c->mWb, from one pass of the
-// batch's two FP64 GEMMs.
+// batch's two FP64 GEMMs; c->mWb is there.
 int grad_images(pr_ctx *c, int32_t m, const double *Bp) {
   const int64_t p = c->P.p;
   hipStream_t s = c->stream;
-  if (!c->mWb && dalloc(&c->mWb, (size_t)nr_of(c->max_batch) * p) != hipSuccess) return PR_ENOMEM;
   PR_TRY(hipMemcpyAsync(c->Bx, Bp, sizeof(double) * m * p, hipMemcpyDeviceToDevice, s));
   int32_t kst = 1;
   const int rc = batch_products(c, m, &kst);
@@ -1985,7 +1996,7 @@ int pr_mlp_features(pr_ctx *c, const pr_node *nodes, int32_t m, const double *Bp
   hipStream_t s = c->stream;
   for (int32_t i = 0; i < m;) {
     const int32_t mc = m - i < c->fb.cap ? m - i : c->fb.cap;
-    const bool batch = images_pay(c, mc);
+    const bool batch = images_pay(c, mc) && need(&c->mWb, (size_t)nr_of(c->max_batch) * p);
     const int32_t mq = batch ? mc : 1;
     const double *bp = Bparent + (int64_t)i * p, *w = c->d_w;
     int8_t *dst = batch ? c->bstatus : c->d_status;
@@ -2073,13 +2084,9 @@ static int warm_start_batched(pr_ctx *c, const pr_node *nodes, int32_t m, const 
     return PR_OK;
   }
   const int NrMax = nr_of(c->max_batch);
-  if (!c->mVb) {
-    bool ok = dalloc(&c->mVb, (size_t)NrMax * p) == hipSuccess;
-    ok = ok && (c->mWb || dalloc(&c->mWb, (size_t)NrMax * p) == hipSuccess);
-    ok = ok && dalloc(&c->mFb, (size_t)NrMax * p * 8) == hipSuccess && dalloc(&c->moutb, (size_t)NrMax * p) == hipSuccess;
-    ok = ok && dalloc(&c->mPb, (size_t)NrMax * p) == hipSuccess;
-    if (!ok) return PR_ENOMEM;
-  }
+  const size_t np = (size_t)NrMax * p;
+  if (!need(&c->mVb, np) || !need(&c->mWb, np) || !need(&c->mFb, np * 8) || !need(&c->moutb, np) || !need(&c->mPb, np))
+    return PR_ENOMEM;
   pr_opts o;
   pr_opts_default(&o);
   int rc = stage_batch_nodes(c, nodes, slot_of, sts, kbars, pbars, o, Bparent);  // parents -> bxbest

@@ -64,6 +64,7 @@ int XLease::take(hipStream_t s, int cap) {
     if (!g_res &&
         hipHostMalloc((void **)&g_res, sizeof(XResult) * kDevices * kSlots, hipHostMallocPortable) != hipSuccess) {
       g_res = nullptr;
+      (void)hipGetLastError();
       return PR_ENOMEM;
     }
     DeviceSlots &d = g_dev[dev_];
@@ -79,10 +80,12 @@ int XLease::take(hipStream_t s, int cap) {
   if (slot_ == 0) {
     if (hipMalloc((void **)&own_, sizeof(uint64_t) * (kXwgWords + 1)) != hipSuccess) {
       own_ = nullptr;
+      (void)hipGetLastError();
       return PR_ENOMEM;
     }
     if (hipHostMalloc((void **)&res, sizeof(XResult), hipHostMallocPortable) != hipSuccess) {
       res = nullptr;
+      (void)hipGetLastError();
       return PR_ENOMEM;
     }
     if (hipMemsetAsync(own_, 0, sizeof(uint64_t) * (kXwgWords + 1), s) != hipSuccess) return PR_EDEVICE;

@@ -27,6 +27,7 @@ static char lose[64];
 static char logbuf[1 << 20];
 static size_t loglen;
 static double clock_us;
+static int last_error;
 
 void si_fail_above(size_t bytes) { fail_above = bytes; }
 void si_cus(int n) { cus = n; }
@@ -119,7 +120,7 @@ int hipGraphExecDestroy(void *g) { return hipGraphDestroy(g); }
 /* memory */
 int hipMalloc(void **p, size_t n) {
   *p = NULL;
-  if (fail_above && n > fail_above) return 2;
+  if (fail_above && n > fail_above) return last_error = 2;
   return (*p = calloc(1, n ? n : 1)) ? 0 : 2;
 }
 int hipFree(void *p) { free(p); return 0; }
@@ -145,7 +146,11 @@ int hipGetSymbolAddress(void **p, const void *v) {
 
 /* streams, events, device */
 int hipGetDevice(int *d) { *d = 0; return 0; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) {
+  const int e = last_error;
+  last_error = 0;
+  return e;
+}
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return 0; }
 int hipStreamDestroy(void *s) { free(s); return 0; }
 int hipStreamSynchronize(void *s) { (void)s; return 0; }

@@ -274,3 +274,36 @@ def test_features_of_more_nodes_than_a_launch_takes(standin):
     lib.pr_mlp_warm_start(h, nodes(m), m, params, zeros(m, p), zeros(m, p), None, None)
     assert sum(int(y) for k, _, y in log() if "k_feat_rows" in k) == m
     """)
+
+
+def test_features_without_room_for_a_batch(standin):
+    """No room for a batch's scratch: the nodes go one by one, as they do on a
+    context without the batched path."""
+    run(standin, """
+    h, F = context(128, 1024, max_batch=256), mem(np.zeros((3, 1024, 8), np.uint16))
+    si.si_fail_above(1 << 20)
+    for _ in range(2):
+        si.si_clear()
+        assert lib.pr_mlp_features(h, nodes(3), 3, zeros(3, 1024), None, F, None) == OK
+        assert si.si_nulls() == 0 and not any("k_gemm" in ln[0] for ln in log())
+        assert sum("k_feat_rows" in ln[0] for ln in log()) == 3
+    """)
+
+
+@pytest.mark.parametrize("max_batch", [1, 64])
+@pytest.mark.parametrize("limit", [4000, 10000, 20000, 50000, 300000, 600000])
+def test_first_use_allocations_that_fail_once(standin, max_batch, limit):
+    """A call that could not get all its buffers says so each time, and the
+    next one that can gets them all."""
+    run(standin, f"""
+    h, F, params = context(128, 1024, max_batch={max_batch}), mem(np.zeros((3, 1024, 8), np.uint16)), zeros(4801)
+    feat = lambda: lib.pr_mlp_features(h, nodes(3), 3, zeros(3, 1024), None, F, None)
+    warm = lambda: lib.pr_mlp_warm_start(h, nodes(3), 3, params, zeros(3, 1024), zeros(3, 1024), None, None)
+    for call in (feat, warm, feat):
+        si.si_fail_above({limit})
+        first = call()
+        assert first in (OK, ENOMEM) and call() == first
+        si.si_fail_above(0)
+        assert call() == OK and si.si_nulls() == 0
+        h = context(128, 1024, max_batch={max_batch})
+    """)
