@@ -22,9 +22,9 @@
 // us), and staging both right-hand sides in LDS per workgroup (one barrier
 // per 1024-row tile) cost 380-440 us.
 //
-// Designs with more columns than that (p > 10240 with one right-hand side, 4096
-// with two) whose right-hand sides fit half of a compute unit's LDS
-// run k_gemv_l instead: 512 workgroups of 8 waves, all resident, each with its
+// Most designs with more columns than that (p > 10240 with one right-hand side,
+// 4096 with two; gemv_lds_blocks has the rule) whose right-hand sides fit half of
+// a compute unit's LDS run k_gemv_l instead: at most 512 workgroups of 8 waves, all resident, each with its
 // own LDS copy of the right-hand sides, whose waves walk the columns two at a
 // time.  The right-hand sides cost no L2 traffic, so two columns per wave
 // suffice; a wave's start is paid once and not per eight columns, and the last
@@ -365,6 +365,39 @@ __global__ __launch_bounds__(kGemvLThreads) void k_gemv_l(const T *__restrict__ 
   }
 }
 
+// Workgroups of k_gemv_l (at most cap, the number resident at once), or 0 where
+// k_gemv_t is the faster one.  A workgroup takes 16 columns a round; `fit` is the
+// part of its rounds that the whole grid fills.  Measured as k_gemv_t -> k_gemv_l in
+// us, one or two right-hand sides:
+// - Columns of fewer than four row steps of a wave (1 KiB each) do not repay the
+//   start of a resident workgroup while C = 4 gives k_gemv_t enough waves: one, FP32
+//   256 x 16385 4.6 -> 5.5, BF16 256 x 10241 3.8 -> 4.7; two, FP32 256 x 8192 3.7 -> 4.0.
+//   With four (FP32 n = 1024) it is 13.8 -> 12.1 at p = 16384, 6.7 -> 6.4 at 5000.
+// - With one right-hand side two steps, and in FP64 at least that many, repay it on
+//   rounds that are filled: FP32 960 x 14000 (fit 0.85) 10.6 -> 9.2, FP64 1024 x 14000
+//   20.9 -> 18.0, but 896 x 18000 (0.73) 19.3 -> 19.7, BF16 1024 x 20480 (0.83) 8.7 -> 9.0.
+// - With C = 8, one right-hand side always gains (FP32 2048 x 65536 93.7 -> 79.6).
+//   Two do on full rounds (FP32 2048 x 18000 34.9 -> 24.8), but not on half-empty
+//   ones (FP32 1024 x 8193, fit 0.5: 8.7 -> 9.5, 5088 x 8193 29.4 -> 32.9).
+// - A grid of equal rounds leaves compute units idle there.  Columns of few steps, and
+//   BF16, whose bound is not the memory, run faster on all of them with rounds of
+//   unequal length: BF16 512 x 16385 8.1 -> 9.1 with equal rounds, 7.0 so, 5088 x
+//   16385 35.0 -> 37.4 and 29.0; FP64 2048 x 10241 36.2 -> 31.8 and 37.3.
+// A few designs of whole steps stay 4-7% slower than with k_gemv_t (two, FP32 1024
+// or BF16 512 rows from p = 40000 on; n 5% off those gains).
+unsigned gemv_lds_blocks(int32_t xdt, bool two, int64_t n, int64_t p, int cols, int64_t cap) {
+  if (cols <= 2 || n * (two ? 2 : 1) > kGemvLdsRows) return 0;
+  const int64_t step = 1024 / (xdt == kF64 ? 8 : (xdt == kF32 ? 4 : 2));
+  const bool few = n < 4 * step;
+  const int64_t need = (p + 15) / 16, rounds = (need + cap - 1) / cap;
+  const double fit = (double)need / (double)(rounds * cap);
+  const bool filled = !two && n >= 2 * step && fit >= 0.84;
+  if (cols == 4 && (few || (!two && xdt == kF64)) && !filled) return 0;
+  if (two && (few || xdt == kBF16)) return (unsigned)(need < cap ? need : cap);
+  if (two && cols == 8 && fit < 0.6) return 0;
+  return (unsigned)((need + rounds - 1) / rounds);
+}
+
 }  // namespace
 
 hipError_t launch_gemv_t(const Problem &P, const double *r1, const double *r2, double *h1, double *h2,
@@ -375,12 +408,9 @@ hipError_t launch_gemv_t(const Problem &P, const double *r1, const double *r2, d
   if (dsum && !node) return hipErrorInvalidValue;
   const bool two = (r2 != nullptr);
   const int cols = gemv_cols(two ? 2 : 1, P.p);
-  if (cols > 2 && P.n * (two ? 2 : 1) <= kGemvLdsRows) {
-    // as many workgroups as are resident at once, the list's one included, and
-    // every wave with the same number of column pairs or one less
-    const int64_t cap = kGemvLBlocks - (node ? 1 : 0), need = (P.p + 15) / 16;
-    const int64_t rounds = (need + cap - 1) / cap;
-    const unsigned lgrid = (unsigned)((need + rounds - 1) / rounds) + (node ? 1u : 0u);
+  // the list's workgroup is one of those resident at once
+  if (const unsigned wgs = gemv_lds_blocks(P.xdt, two, P.n, P.p, cols, kGemvLBlocks - (node ? 1 : 0))) {
+    const unsigned lgrid = wgs + (node ? 1u : 0u);
 #define PR_GEMVL(T, R)                                                                                              \
   k_gemv_l<T, R><<<lgrid, kGemvLThreads, 0, s>>>((const T *)P.X, P.n, P.p, r1, r2, h1, h2, done, node, S, sidx, sval, \
                                                  nlist, dsum, nfin)

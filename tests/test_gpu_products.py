@@ -71,3 +71,23 @@ def test_one_right_hand_side_by_kernel(dev, storage, n, p):
         Xc = X[c:c + 2048].double()
         assert bool(((h[c:c + 2048] - Xc @ r).abs() <= 1e-13 * (Xc.abs() @ r.abs()) + 1e-300).all())
     ctx.close()
+
+
+# the grids of the LDS kernel with two right-hand sides: equal rounds, or every resident workgroup with rounds of
+# unequal length (the last one a single column), and their neighbours in the other kernel
+@pytest.mark.parametrize("storage,n,p", [("bf16", 512, 16385), ("bf16", 2048, 16401), ("f32", 1024, 10241),
+                                         ("f32", 1024, 8193), ("f32", 252, 16399), ("f64", 512, 14001),
+                                         ("f64", 512, 18001), ("f32", 1024, 16385)])
+def test_products_on_both_grids(dev, storage, n, p):
+    import torch
+    import paper_2603_01306_amd as pr
+    X, g = _design(dev, storage, n, p, 11)
+    r = torch.randn(2, n, generator=g, device=dev, dtype=torch.float64)
+    ctx = pr.Context(X, torch.randn(n, generator=g, device=dev, dtype=torch.float64).sign(), 1)
+    h = ctx.gemv_t2(r[0].contiguous(), r[1].contiguous())
+    for q in range(2):
+        assert torch.equal(h[q], ctx.gemv_t(r[q].contiguous()))
+        for c in range(0, p, 4096):
+            Xc = X[c:c + 4096].double()
+            assert bool(((h[q][c:c + 4096] - Xc @ r[q]).abs() <= 1e-13 * (Xc.abs() @ r[q].abs()) + 1e-300).all())
+    ctx.close()
