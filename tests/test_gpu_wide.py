@@ -135,3 +135,33 @@ def test_prox_from_many_threads_and_streams(dev):
         t.join()
     for (x, g), (y, h) in zip(serial, got):
         assert torch.equal(x, y) and g == h
+
+
+@pytest.mark.parametrize("p,k,n0,n1,M,warm", [
+    (524288, 25, 64, 24, 2.0, False),          # the longest vector that workgroups share
+    (524289, 25, 64, 24, 2.0, False),          # one workgroup over global memory
+    (524289, 40, 0, 0, float("inf"), True),
+])
+@pytest.mark.parametrize("loss", [0, 1])
+def test_node_traces_at_the_longest_shared_vector(dev, p, k, n0, n1, M, warm, loss):
+    test_wide_node_traces(dev, p, k, n0, n1, M, warm, loss)
+
+
+@pytest.mark.parametrize("p", [524288, 524289, 1048576])
+@pytest.mark.parametrize("M", [2.0, float("inf")])
+def test_noalloc_prox_at_the_longest_shared_vector(dev, p, M):
+    """The prox without allocation over shared vectors and, past them, over its
+    own scratch: pr_prox's output bit for bit."""
+    import torch
+    import paper_2603_01306_amd as pr
+    print(f"noalloc prox p={p} M={M}", flush=True)
+    rng = np.random.default_rng(p)
+    v = np.round(rng.standard_normal(p), 3)
+    st = np.zeros(p, dtype=np.int8)
+    idx = rng.permutation(p)
+    st[idx[:50]] = oracle.ZERO
+    st[idx[50:57]] = oracle.ONE
+    dv, ds = torch.from_numpy(v).to(dev), torch.from_numpy(st).to(dev)
+    x = pr.prox(dv, 0.8, 300, M, ds)
+    assert torch.equal(pr.prox_noalloc(dv, 0.8, 300, M, ds, out=torch.full_like(dv, float("nan"))), x)
+    assert 250 < int((x != 0).sum()) < p and float(x[ds == oracle.ZERO].abs().max()) == 0.0
