@@ -1591,8 +1591,8 @@ int pr_gemm(void *stream, const uint16_t *A, int64_t lda, const double *B, int64
   return PR_OK;
 }
 
-// Status counts of a context-free call on vectors that one workgroup takes from memory: the status
-// comes to the host, n1 = |J1|, nf = |J_f|.
+// Status counts of a context-free call on vectors that one workgroup takes from
+// memory: the status comes to the host, n1 = |J1|, nf = |J_f|.
 static int count_status(const int8_t *status, int64_t p, hipStream_t s, int64_t *n1, int64_t *nf) {
   std::vector<int8_t> st((size_t)p);
   PR_TRY(hipMemcpyAsync(st.data(), status, (size_t)p, hipMemcpyDeviceToHost, s));

@@ -24,9 +24,9 @@
 //
 // Most designs with more columns than that (p > 10240 with one right-hand side,
 // 4096 with two; gemv_lds_blocks has the rule) whose right-hand sides fit half of
-// a compute unit's LDS run k_gemv_l instead: at most 512 workgroups of 8 waves, all resident, each with its
-// own LDS copy of the right-hand sides, whose waves walk the columns two at a
-// time.  The right-hand sides cost no L2 traffic, so two columns per wave
+// a compute unit's LDS run k_gemv_l instead: at most 512 workgroups of 8 waves,
+// all resident, each with its own LDS copy of the right-hand sides, whose waves
+// walk the columns two at a time.  The right-hand sides cost no L2 traffic, so two columns per wave
 // suffice; a wave's start is paid once and not per eight columns, and the last
 // round of workgroups, partly empty before, is gone.  A column's sum is formed in
 // the same order, whatever C.  FP32, two right-hand sides: 2300 x 89989 134 ->

@@ -1,8 +1,8 @@
 // pr_prox_noalloc: the prox of g_N without any allocation, for callers that
 // cannot allocate device memory (code under stream capture, tight serving
-// loops, harnesses that forbid hipMalloc).  Vectors that reg_xshape has a shape for stay in
-// the registers of the workgroups that share them and need only the exchange
-// area this entry point owns; longer ones stage their magnitudes in a
+// loops, harnesses that forbid hipMalloc).  Vectors that reg_xshape has a shape
+// for stay in the registers of the workgroups that share them and need only the
+// exchange area this entry point owns; longer ones stage their magnitudes in a
 // file-scope device array.  Every GPU the library runs on holds its own copy of
 // both until the process ends, and every call on that GPU shares them.
 #include <math.h>

@@ -10,7 +10,8 @@
 //
 // Two variants: register-resident (p <= 16384, coordinates j = tid + e*512
 // held in registers across all passes) and a global-memory one, for vectors
-// beyond the reach of the kernels that share a node among workgroups (p > 524288).
+// beyond the reach of the kernels that share a node among workgroups (p > 524288,
+// less on a stream that may use few compute units).
 #include "pr_device.h"
 
 #include "pr_regularizer.h"

@@ -15,11 +15,11 @@
 // threads, up to 8 values, the reduction inside the workgroups included): 1.25
 // us per exchange with 8 workgroups, 1.37 with 16, 1.6 with 32, 2.1 with 64.
 //
-// All workgroups of the launch must be resident together (xwg_cap).  A
-// wait of more than kXwgTicks (pr_wait.h) ends with `failed` set instead of a hang, and the
-// workgroup reports it in *XBuf::lost: what such a launch wrote is not to be used.
-// A test switch in the area's head lets the last workgroup give up the first
-// exchange of every launch and the others after kLostTicks.
+// All workgroups of the launch must be resident together (xwg_cap).  A wait of
+// more than kXwgTicks (pr_wait.h) ends with `failed` set instead of a hang, and
+// the workgroup reports it in *XBuf::lost: what such a launch wrote is not to be
+// used.  A test switch in the area's head lets the last workgroup give up the
+// first exchange of every launch and the others after kLostTicks.
 #pragma once
 #include "pr_device.h"
 #include "pr_wait.h"

@@ -313,13 +313,16 @@ def test_first_use_allocations_that_fail_once(standin, max_batch, limit):
     # few row steps, enough waves without LDS
     ("F32", 256, 16385, 0, 512), ("F32", 256, 10240, 0, 512), ("F32", 256, 8192, 0, 0), ("F32", 256, 8193, 0, 512),
     ("F32", 1020, 20480, 0, 512), ("F32", 1020, 20481, 427, 512),
-    ("F32", 512, 14000, 438, 512), ("F32", 508, 14000, 0, 512), ("F64", 256, 16384, 512, 512), ("F64", 512, 20480, 0, 427),
+    ("F32", 512, 14000, 438, 512), ("F32", 508, 14000, 0, 512), ("F64", 256, 16384, 512, 512),
+    ("F64", 512, 20480, 0, 427),
     # four row steps: whole rounds, of two only if they fill the grid
-    ("F32", 1024, 16385, 342, 342), ("F32", 1024, 8192, 0, 512), ("F32", 1024, 8193, 0, 0), ("F32", 1024, 10241, 321, 321),
+    ("F32", 1024, 16385, 342, 342), ("F32", 1024, 8192, 0, 512), ("F32", 1024, 8193, 0, 0),
+    ("F32", 1024, 10241, 321, 321),
     ("F32", 2300, 89989, 512, 512), ("F32", 5088, 4097, 0, 257), ("F32", 5092, 4097, 0, 0),
     ("F64", 1024, 14000, 438, 438), ("F64", 1024, 18000, 0, 375), ("F64", 512, 65536, 512, 512),
     # BF16 with two: every workgroup that is resident
-    ("BF16", 5088, 16385, 342, 512), ("BF16", 2040, 8192, 0, 0), ("BF16", 2048, 8192, 0, 512), ("BF16", 10176, 10241, 321, 0),
+    ("BF16", 5088, 16385, 342, 512), ("BF16", 2040, 8192, 0, 0), ("BF16", 2048, 8192, 0, 512),
+    ("BF16", 10176, 10241, 321, 0),
 ])
 def test_kernel_of_the_transposed_product(standin, dtype, n, p, one, two):
     """Workgroups of the kernel with its right-hand sides in LDS, 0: the other."""
