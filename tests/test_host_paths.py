@@ -66,7 +66,7 @@ def standin(tmp_path_factory):
 
 
 def run(so, body):
-    env = dict(os.environ, LD_PRELOAD=so)
+    env = dict(os.environ, LD_PRELOAD=":".join(filter(None, (so, os.environ.get("LD_PRELOAD")))))
     code = PRELUDE.format(root=ROOT, so=so) + textwrap.dedent(body)
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
