@@ -594,12 +594,62 @@ int lanczos_norm2(pr_ctx *c) {
 
 int nr_of(int32_t m) { return (m + 63) / 64 * 64; }
 
+// One product's extra split factor: of f = 1, 2, .. fmax the largest whose cost,
+// the measured time plus plane_ms per split for the partial planes that the next
+// kernel reads, is within 1.5% of the least.  The split fixes how sums associate,
+// so what noise decides changes an iterate's last bits from context to context: the
+// 1024 x 512 products at 16 rows cost 10.45 us with 16 splits and 10.40 with 32,
+// each +-0.05 and now and then 2 more.  (The larger one: it is also used at fewer
+// rows, where more splits pay more.)  Those short of 0.1 ms that are in question are
+// timed twice more.
+template <class S, class L>
+int choose_split(pr_ctx *c, int fmax, double plane_ms, S set, L launch, int32_t *bestf, double *best) {
+  double ms[8];
+  int cnt = 0;
+  auto time = [&](int f, double *out) -> int {
+    PR_TRY(set(f));
+    PR_TRY(launch());
+    PR_TRY(hipEventRecord(c->tev[0], c->stream));
+    for (int r = 0; r < kTuneReps; r++) PR_TRY(launch());
+    PR_TRY(hipEventRecord(c->tev[1], c->stream));
+    PR_TRY(hipEventSynchronize(c->tev[1]));
+    float t = 0.0f;
+    PR_TRY(hipEventElapsedTime(&t, c->tev[0], c->tev[1]));
+    *out = (double)t / kTuneReps;
+    return PR_OK;
+  };
+  auto cost = [&](int i) { return ms[i] + plane_ms * (1 << i); };
+  auto least = [&] {
+    double b = INFINITY;
+    for (int i = 0; i < cnt; i++) b = fmin(b, cost(i));
+    return b;
+  };
+  for (int f = 1; f <= fmax; f *= 2) {
+    const int rc = time(f, &ms[cnt++]);
+    if (rc != PR_OK) return rc;
+  }
+  const double first = least();
+  for (int i = 0; i < cnt; i++)
+    for (int r = 0; r < 2 && ms[i] < 0.1 && cost(i) <= 1.25 * first; r++) {
+      double t;
+      const int rc = time(1 << i, &t);
+      if (rc != PR_OK) return rc;
+      ms[i] = fmin(ms[i], t);
+    }
+  const double bound = 1.015 * least();
+  for (int i = 0; i < cnt; i++)
+    if (cost(i) <= bound) {
+      *bestf = 1 << i;
+      *best = cost(i);
+    }
+  return PR_OK;
+}
+
 // Autotuner of the batched GEMMs (run once per context).  For every count of
 // active 64-row tiles, each extra split factor f of each GEMM (a tile's extent
 // along the reduction dimension is K / (base * f)) is timed with HIP events in
-// the solve's launch configuration (persistent grid, row map, tile counter);
-// the chosen f minimises the measured time plus the modelled cost of the
-// split partial planes that the next kernel reads (bytes / kTunePlaneBW).
+// the solve's launch configuration (persistent grid, row map, tile counter) and
+// one is chosen (choose_split; the planes' cost is bytes / kTunePlaneBW).
 // The table goes to the device, where the per-iteration row-map kernel reads
 // it.
 int tune_batch(pr_ctx *c) {
@@ -620,35 +670,23 @@ int tune_batch(pr_ctx *c) {
     int32_t *rmap = (!fwd && c->d_rowmap2) ? c->d_rowmap2 : c->d_rowmap;
     for (int nta = 1; nta <= ntmax; nta++) {
       const int32_t nrow = nta * 64 < rows ? nta * 64 : rows;
-      double best = INFINITY;
-      int bestf = 1;
-      for (int f = 1; f <= fmax; f *= 2) {
+      auto set = [&](int f) -> hipError_t {
         const int32_t sp[3] = {nrow, base * f, base * f};
-        PR_TRY(hipMemcpyAsync(c->d_split, sp, sizeof(sp), hipMemcpyHostToDevice, s));
-        auto launch = [&]() -> hipError_t {
-          hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
-          if (e != hipSuccess) return e;
-          if (fwd)
-            return launch_gemm_any(c->P.xdt, c->Xrow, p, kF64, c->Bx, p, c->CF, n, NrMax, p, base, nullptr,
-                                   c->d_rowmap, c->d_split, c->d_split + 1, base * fmax, cnt, s);
-          return launch_gemm_any(c->P.xdt, c->P.X, n, kF64, c->Rd, n, c->CT, p, NrMaxT, n, base, nullptr, rmap,
-                                 c->d_split, c->d_split + 2, base * fmax, cnt, s);
-        };
-        PR_TRY(launch());
-        PR_TRY(hipEventRecord(c->tev[0], s));
-        for (int r = 0; r < kTuneReps; r++) PR_TRY(launch());
-        PR_TRY(hipEventRecord(c->tev[1], s));
-        PR_TRY(hipEventSynchronize(c->tev[1]));
-        float ms = 0.0f;
-        PR_TRY(hipEventElapsedTime(&ms, c->tev[0], c->tev[1]));
-        const double cost = ms / kTuneReps + 1e3 * (double)(base * f) * nrow * plane_bytes / kTunePlaneBW;
-        if (cost < best) {
-          best = cost;
-          bestf = f;
-        }
-      }
-      c->h_ftab[g * kTuneMax + nta] = bestf;
-      c->h_tbest[g * kTuneMax + nta] = best;
+        return hipMemcpyAsync(c->d_split, sp, sizeof(sp), hipMemcpyHostToDevice, s);
+      };
+      auto launch = [&]() -> hipError_t {
+        hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
+        if (e != hipSuccess) return e;
+        if (fwd)
+          return launch_gemm_any(c->P.xdt, c->Xrow, p, kF64, c->Bx, p, c->CF, n, NrMax, p, base, nullptr,
+                                 c->d_rowmap, c->d_split, c->d_split + 1, base * fmax, cnt, s);
+        return launch_gemm_any(c->P.xdt, c->P.X, n, kF64, c->Rd, n, c->CT, p, NrMaxT, n, base, nullptr, rmap,
+                               c->d_split, c->d_split + 2, base * fmax, cnt, s);
+      };
+      const int at = g * kTuneMax + nta;
+      const int rc = choose_split(c, fmax, 1e3 * (double)base * nrow * plane_bytes / kTunePlaneBW, set, launch,
+                                  &c->h_ftab[at], &c->h_tbest[at]);
+      if (rc != PR_OK) return rc;
     }
     for (int nta = ntmax + 1; nta < kTuneMax; nta++) {
       c->h_ftab[g * kTuneMax + nta] = c->h_ftab[g * kTuneMax + ntmax];
@@ -799,32 +837,20 @@ int tune_gram_batch(pr_ctx *c) {
   const double plane_bytes = 8.0 * (double)p;
   for (int nta = 1; nta <= ntmax; nta++) {
     const int32_t nrow = nta * 64 < c->max_batch ? nta * 64 : c->max_batch;
-    double best = INFINITY;
-    int bestf = 1;
-    for (int f = 1; f <= fG; f *= 2) {
+    auto set = [&](int f) -> hipError_t {
       const int32_t sp[3] = {nrow, KSG * f, KSG * f};
-      PR_TRY(hipMemcpyAsync(c->d_split, sp, sizeof(sp), hipMemcpyHostToDevice, s));
-      auto launch = [&]() -> hipError_t {
-        hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
-        if (e != hipSuccess) return e;
-        return launch_gemm_any(kF64, c->G, p, kF64, c->Bx, p, c->CG, p, NrMax, p, KSG, nullptr, c->d_rowmap,
-                               c->d_split, c->d_split + 2, KSG * fG, cnt, s);
-      };
-      PR_TRY(launch());
-      PR_TRY(hipEventRecord(c->tev[0], s));
-      for (int r = 0; r < kTuneReps; r++) PR_TRY(launch());
-      PR_TRY(hipEventRecord(c->tev[1], s));
-      PR_TRY(hipEventSynchronize(c->tev[1]));
-      float ms = 0.0f;
-      PR_TRY(hipEventElapsedTime(&ms, c->tev[0], c->tev[1]));
-      const double cost = ms / kTuneReps + 1e3 * (double)(KSG * f) * nrow * plane_bytes / kTunePlaneBW;
-      if (cost < best) {
-        best = cost;
-        bestf = f;
-      }
-    }
-    c->h_ftab[2 * kTuneMax + nta] = bestf;
-    c->h_tbest[2 * kTuneMax + nta] = best;
+      return hipMemcpyAsync(c->d_split, sp, sizeof(sp), hipMemcpyHostToDevice, s);
+    };
+    auto launch = [&]() -> hipError_t {
+      hipError_t e = hipMemsetAsync(cnt, 0, sizeof(int32_t), s);
+      if (e != hipSuccess) return e;
+      return launch_gemm_any(kF64, c->G, p, kF64, c->Bx, p, c->CG, p, NrMax, p, KSG, nullptr, c->d_rowmap,
+                             c->d_split, c->d_split + 2, KSG * fG, cnt, s);
+    };
+    const int at = 2 * kTuneMax + nta;
+    const int rc = choose_split(c, fG, 1e3 * (double)KSG * nrow * plane_bytes / kTunePlaneBW, set, launch,
+                                &c->h_ftab[at], &c->h_tbest[at]);
+    if (rc != PR_OK) return rc;
   }
   for (int nta = ntmax + 1; nta < kTuneMax; nta++) {
     c->h_ftab[2 * kTuneMax + nta] = c->h_ftab[2 * kTuneMax + ntmax];

@@ -238,6 +238,19 @@ def test_route_of_the_feature_images(standin, max_batch, loss):
     """)
 
 
+@pytest.mark.parametrize("us,split", [(200.0, 32), (20.0, 32), (5.0, 16)])
+def test_split_of_equal_times(standin, us, split):
+    """Candidates whose cost differs by less than timing noise: always the larger
+    split, so that a repeated run repeats its sums; not where its planes cost more."""
+    run(standin, f"""
+    si.si_cost(b"k_gemm", {us})
+    h = context(1024, 512, max_batch=16)
+    f, t = (ctypes.c_int32 * 1)(), (ctypes.c_int32 * 1)()
+    assert lib.pr_batch_tuning(h, 1, f, t) == OK
+    assert list(t) == [{split}], list(t)
+    """)
+
+
 def test_one_nodes_features_take_one_upload(standin):
     """The status of the node; its scalars go with the launch."""
     run(standin, """
