@@ -257,13 +257,26 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_t(const T *__restrict__ X
   // then the right-hand side once the first column has arrived) measured
   // faster: 316 vs 340 us on a 32768 x 16384 FP32 design, 89.8 vs 94.0 on
   // 16000 x 16000 BF16, equal on 16384 x 8192.
+  // Of those loads the right-hand sides go first, fixed by a barrier of their own:
+  // X first takes 3-6% longer in BF16 (1048576 x 128 1391 -> 1478 us, 16384 x 8192
+  // 67.8 -> 71.3), 1% in FP32 with C < 8 (65536 x 1024 157 -> 160) and up to 8% in
+  // FP64 (6000 x 40000 290 -> 312).  FP32 with C = 8 gains from X first where it
+  // differs (6000 x 40000 178 -> 167, 8192 x 20000 128 -> 127).
+  constexpr bool kRhsFirst = NRHS > 1 && !(C == 8 && std::is_same<T, float>::value);
   for (; i + VEC <= n; i += step) {
     typename XLoad<T>::raw_t xr[C];
     double rv[NRHS][VEC];
+    if constexpr (kRhsFirst) {
+      load_rhs<VEC>(r1, i, rv[0]);
+      load_rhs<VEC>(r2, i, rv[NRHS - 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int q = 0; q < C; q++) xr[q] = XLoad<T>::raw(c[q] + i);
-    load_rhs<VEC>(r1, i, rv[0]);
-    if (NRHS > 1) load_rhs<VEC>(r2, i, rv[NRHS - 1]);
+    if constexpr (!kRhsFirst) {
+      load_rhs<VEC>(r1, i, rv[0]);
+      if (NRHS > 1) load_rhs<VEC>(r2, i, rv[NRHS - 1]);
+    }
     if constexpr (NRHS > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < C; q++) {
