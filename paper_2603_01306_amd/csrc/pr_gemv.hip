@@ -36,6 +36,8 @@
 // and so it is with one right-hand side at p = 4735 (15.0 -> 16.4).
 // Algorithmic bytes per launch: n*p*sizeof(X) + 8n per right-hand side + 8p
 // per output.
+#include <cstdlib>
+
 #include "pr_device.h"
 
 namespace pr {
@@ -391,23 +393,29 @@ __global__ __launch_bounds__(kGemvLThreads) void k_gemv_l(const T *__restrict__ 
 //   20.9 -> 18.0, but 896 x 18000 (0.73) 19.3 -> 19.7, BF16 1024 x 20480 (0.83) 8.7 -> 9.0.
 // - With C = 8, one right-hand side always gains (FP32 2048 x 65536 93.7 -> 79.6).
 //   Two do on full rounds (FP32 2048 x 18000 34.9 -> 24.8), but not on half-empty
-//   ones (FP32 1024 x 8193, fit 0.5: 8.7 -> 9.5, 5088 x 8193 29.4 -> 32.9).
+//   ones (FP32 1024 x 8193, fit 0.5: 8.7 -> 9.5, 5088 x 8193 29.4 -> 32.9; so is p =
+//   8192 where the list has a workgroup: iterations of 5040 x 8192 in FP64 +5%).
 // - A grid of equal rounds leaves compute units idle there.  Columns of few steps, and
 //   BF16, whose bound is not the memory, run faster on all of them with rounds of
 //   unequal length: BF16 512 x 16385 8.1 -> 9.1 with equal rounds, 7.0 so, 5088 x
 //   16385 35.0 -> 37.4 and 29.0; FP64 2048 x 10241 36.2 -> 31.8 and 37.3.
-// A few designs of whole steps stay 4-7% slower than with k_gemv_t (two, FP32 1024
-// or BF16 512 rows from p = 40000 on; n 5% off those gains).
+// - Columns 32 KiB apart lie on the same memory channels, and waves that start
+//   together walk them together (k_gemv_t's waves do not): one, FP32 8192 x 16384
+//   96 -> 116, 8192 x 12000 80 -> 88; two, FP64 4096 x 16384 99 -> 111.  16 KiB apart
+//   it is 3% on average with C = 4 (one, FP32 4096 x 12000 47.3 -> 50.1) and a gain with
+//   C = 8; 4 KiB apart 3% in FP32 from p = 65536 on with two.  48 and 64 KiB are no worse than others.
 unsigned gemv_lds_blocks(int32_t xdt, bool two, int64_t n, int64_t p, int cols, int64_t cap) {
   if (cols <= 2 || n * (two ? 2 : 1) > kGemvLdsRows) return 0;
-  const int64_t step = 1024 / (xdt == kF64 ? 8 : (xdt == kF32 ? 4 : 2));
+  const int64_t size = xdt == kF64 ? 8 : (xdt == kF32 ? 4 : 2), step = 1024 / size, stride = n * size;
+  if (stride == 32768 || (!two && xdt == kF32 && llabs(stride - 32768) <= 512)) return 0;
+  if ((stride == 16384 && cols == 4) || (two && xdt == kF32 && stride == 4096 && p >= 65536)) return 0;
   const bool few = n < 4 * step;
   const int64_t need = (p + 15) / 16, rounds = (need + cap - 1) / cap;
   const double fit = (double)need / (double)(rounds * cap);
   const bool filled = !two && n >= 2 * step && fit >= 0.84;
   if (cols == 4 && (few || (!two && xdt == kF64)) && !filled) return 0;
   if (two && (few || xdt == kBF16)) return (unsigned)(need < cap ? need : cap);
-  if (two && cols == 8 && fit < 0.6) return 0;
+  if (two && rounds > 1 && fit < 0.6) return 0;
   return (unsigned)((need + rounds - 1) / rounds);
 }
 

@@ -336,6 +336,12 @@ def test_first_use_allocations_that_fail_once(standin, max_batch, limit):
     # BF16 with two: every workgroup that is resident
     ("BF16", 5088, 16385, 342, 512), ("BF16", 2040, 8192, 0, 0), ("BF16", 2048, 8192, 0, 512),
     ("BF16", 10176, 10241, 321, 0),
+    # columns 32 KiB apart, 16 with C = 4, 4 with many of them
+    ("F32", 8192, 16384, 0, 0), ("F32", 8192, 60000, 0, 0), ("F32", 8064, 12000, 0, 0), ("F32", 8060, 12000, 375, 0),
+    ("F64", 4096, 40000, 0, 0), ("F64", 4094, 40000, 500, 500), ("F64", 6144, 40000, 500, 0),
+    ("F32", 4096, 20480, 0, 427), ("F32", 4096, 20481, 427, 427), ("F32", 4096, 8192, 0, 0),
+    ("F32", 4092, 8192, 0, 512), ("BF16", 8192, 20480, 0, 0), ("BF16", 8192, 20481, 427, 0),
+    ("F32", 1024, 65535, 512, 512), ("F32", 1024, 65536, 512, 0), ("BF16", 2048, 65536, 512, 512),
 ])
 def test_kernel_of_the_transposed_product(standin, dtype, n, p, one, two):
     """Workgroups of the kernel with its right-hand sides in LDS, 0: the other."""
