@@ -47,6 +47,7 @@ bool find_slots(int dev) {
 int xwg_cap(hipStream_t s) {
   int cus = 0;
   uint32_t mask[32] = {};
+  if (s == hipStreamLegacy) s = nullptr;  // the same stream; the query reads through that handle
   if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess) {
     for (uint32_t w : mask) cus += __builtin_popcount(w);
   } else {

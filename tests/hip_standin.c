@@ -162,7 +162,7 @@ int hipEventSynchronize(void *e) { (void)e; return 0; }
 int hipEventElapsedTime(float *ms, void *a, void *b) { *ms = (float)((*(double *)b - *(double *)a) * 1e-3); return 0; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a, (void)d; *v = cus; return 0; }
 int hipExtStreamGetCUMask(void *s, uint32_t n, uint32_t *m) {
-  (void)s;
+  if (s == (void *)1) abort(); /* hipStreamLegacy: the runtime takes it for a pointer */
   for (uint32_t i = 0; i < n; i++) {
     const int left = cus - 32 * (int)i;
     m[i] = left >= 32 ? 0xffffffffu : (left > 0 ? (1u << left) - 1u : 0u);

@@ -190,6 +190,21 @@ def test_shared_vectors_fit_the_compute_units(standin, cus):
     """)
 
 
+@pytest.mark.parametrize("stream", [1, 2])
+def test_default_streams_by_handle(standin, stream):
+    """hipStreamLegacy and hipStreamPerThread are streams like others."""
+    run(standin, f"""
+    s, p, d = P({stream}), 20000, ctypes.c_double
+    v, st, x, g = zeros(p), mem(np.zeros(p, np.int8)), zeros(p), d()
+    assert lib.pr_prox(s, v, p, d(0.5), 3, d(2.0), st, x) == OK
+    assert lib.pr_prox_noalloc(s, v, p, d(0.5), 3, d(2.0), st, x) == OK
+    assert lib.pr_regularizer(s, v, None, p, 3, d(2.0), st, ctypes.byref(g), None) == OK
+    prob = b.PrProblem(X=mem(np.zeros((p, 8), np.float32)).value, xdtype=b.F32, loss=0, y=zeros(8).value, n=8, p=p)
+    assert lib.pr_ctx_create(ctypes.byref(P()), ctypes.byref(prob), 1, s) == OK
+    assert all(int(w) > 1 for k, w, _ in log() if "k_prox_x" in k or "k_regularizer_x" in k)
+    """)
+
+
 def test_wait_clock_counts_polling_time(tmp_path):
     """20 s of the limit are 20 s of looks a millisecond apart; an hour in which
     the wave did not run adds 10 ms."""
