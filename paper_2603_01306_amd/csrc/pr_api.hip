@@ -600,8 +600,8 @@ int nr_of(int32_t m) { return (m + 63) / 64 * 64; }
 // so what noise decides changes an iterate's last bits from context to context: the
 // 1024 x 512 products at 16 rows cost 10.45 us with 16 splits and 10.40 with 32,
 // each +-0.05 and now and then 2 more.  (The larger one: it is also used at fewer
-// rows, where more splits pay more.)  Those short of 0.1 ms that are in question are
-// timed twice more.
+// rows, where more splits pay more.)  One that misses by no more than such an outlier is
+// timed again, up to twice.
 template <class S, class L>
 int choose_split(pr_ctx *c, int fmax, double plane_ms, S set, L launch, int32_t *bestf, double *best) {
   double ms[8];
@@ -619,29 +619,25 @@ int choose_split(pr_ctx *c, int fmax, double plane_ms, S set, L launch, int32_t 
     return PR_OK;
   };
   auto cost = [&](int i) { return ms[i] + plane_ms * (1 << i); };
-  auto least = [&] {
-    double b = INFINITY;
-    for (int i = 0; i < cnt; i++) b = fmin(b, cost(i));
-    return b;
-  };
+  double least = INFINITY;
   for (int f = 1; f <= fmax; f *= 2) {
-    const int rc = time(f, &ms[cnt++]);
+    const int rc = time(f, &ms[cnt]);
     if (rc != PR_OK) return rc;
+    least = fmin(least, cost(cnt++));
   }
-  const double first = least();
-  for (int i = 0; i < cnt; i++)
-    for (int r = 0; r < 2 && ms[i] < 0.1 && cost(i) <= 1.25 * first; r++) {
+  const double bound = 1.015 * least;
+  int at = cnt - 1;
+  for (; at > 0 && cost(at) > bound; at--) {
+    for (int r = 0; r < 2 && cost(at) > bound && cost(at) <= bound + 0.003; r++) {
       double t;
-      const int rc = time(1 << i, &t);
+      const int rc = time(1 << at, &t);
       if (rc != PR_OK) return rc;
-      ms[i] = fmin(ms[i], t);
+      ms[at] = fmin(ms[at], t);
     }
-  const double bound = 1.015 * least();
-  for (int i = 0; i < cnt; i++)
-    if (cost(i) <= bound) {
-      *bestf = 1 << i;
-      *best = cost(i);
-    }
+    if (cost(at) <= bound) break;
+  }
+  *bestf = 1 << at;
+  *best = cost(at);
   return PR_OK;
 }
 
