@@ -261,8 +261,8 @@ int pr_prox(void *stream, const double *v, int64_t p, double rho, int32_t k, dou
  * library, one copy per GPU, held until the process ends (for p <= 524288, less
  * on a stream that may use few compute units, the 160 KiB through which the
  * workgroups sharing the vector exchange partial sums, above that 8 bytes per
- * coordinate of PR_PROX_NOALLOC_MAX_P plus 256 bytes, 8 MiB).  |J1| and |J_f| are counted on the device from `status`, so the
- * host never reads it.
+ * coordinate of PR_PROX_NOALLOC_MAX_P plus 256 bytes, 8 MiB).  |J1| and |J_f| are
+ * counted on the device from `status`, so the host never reads it.
  *   Arguments as pr_prox; additionally p <= PR_PROX_NOALLOC_MAX_P.
  *   Returns PR_EINVAL for a bad argument, p > PR_PROX_NOALLOC_MAX_P, a status
  *   code outside {PR_FREE, PR_ZERO, PR_ONE} or |J1| > k (then `out` is not

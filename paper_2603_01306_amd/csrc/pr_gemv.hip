@@ -26,9 +26,9 @@
 // 4096 with two; gemv_lds_blocks has the rule) whose right-hand sides fit half of
 // a compute unit's LDS run k_gemv_l instead: at most 512 workgroups of 8 waves,
 // all resident, each with its own LDS copy of the right-hand sides, whose waves
-// walk the columns two at a time.  The right-hand sides cost no L2 traffic, so two columns per wave
-// suffice; a wave's start is paid once and not per eight columns, and the last
-// round of workgroups, partly empty before, is gone.  A column's sum is formed in
+// walk the columns two at a time.  The right-hand sides cost no L2 traffic, so two
+// columns per wave suffice; a wave's start is paid once and not per eight columns,
+// and the last round of workgroups, partly empty before, is gone.  A column's sum is formed in
 // the same order, whatever C.  FP32, two right-hand sides: 2300 x 89989 134 ->
 // 127 us (6.5 TB/s), 3000 x 20000 44.8 -> 38.4, 2000 x 8192 11.0 -> 9.9, 4460 x
 // 4735 21.2 -> 19.0; one: 2300 x 89989 130 -> 124, BF16 10000 x 40000 148 -> 123.
@@ -403,7 +403,8 @@ __global__ __launch_bounds__(kGemvLThreads) void k_gemv_l(const T *__restrict__ 
 //   together walk them together (k_gemv_t's waves do not): one, FP32 8192 x 16384
 //   96 -> 116, 8192 x 12000 80 -> 88; two, FP64 4096 x 16384 99 -> 111.  16 KiB apart
 //   it is 3% on average with C = 4 (one, FP32 4096 x 12000 47.3 -> 50.1) and a gain with
-//   C = 8; 4 KiB apart 3% in FP32 from p = 65536 on with two.  48 and 64 KiB are no worse than others.
+//   C = 8; 4 KiB apart 3% in FP32 from p = 65536 on with two.  48 and 64 KiB are no
+//   worse than others.
 unsigned gemv_lds_blocks(int32_t xdt, bool two, int64_t n, int64_t p, int cols, int64_t cap) {
   if (cols <= 2 || n * (two ? 2 : 1) > kGemvLdsRows) return 0;
   const int64_t size = xdt == kF64 ? 8 : (xdt == kF32 ? 4 : 2), step = 1024 / size, stride = n * size;

@@ -290,8 +290,9 @@ hipError_t launch_batch_resid(const double *U, const int32_t *ksp, int64_t n, in
 hipError_t launch_gemm_f64(const uint16_t *A, int64_t lda, const double *B, int64_t ldb, double *C, int64_t Mc,
                            int64_t Nr, int64_t K, int KS, const int32_t *active, const int32_t *rowmap,
                            const int32_t *nrow, const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s);
-// Same product, of the first `rows` rows of B (0: all Nr; a row map takes precedence), with operand types adt, bdt in {kBF16, kF32, kF64}: supported
-// pairs (BF16, FP64), (FP32, FP64), (BF16, BF16), (FP32, FP32), (FP64, FP64).
+// Same product, of the first `rows` rows of B (0: all Nr; a row map takes precedence),
+// with operand types adt, bdt in {kBF16, kF32, kF64}: supported pairs (BF16, FP64),
+// (FP32, FP64), (BF16, BF16), (FP32, FP32), (FP64, FP64).
 hipError_t launch_gemm_any(int adt, const void *A, int64_t lda, int bdt, const void *B, int64_t ldb, double *C,
                            int64_t Mc, int64_t Nr, int64_t K, int KS, const int32_t *active, const int32_t *rowmap,
                            const int32_t *nrow, const int32_t *ksp, int ks_max, int32_t *counter, hipStream_t s,
